@@ -65,7 +65,7 @@ def copy_calibration(nbytes):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("gemm.hip", "common.h", "kernels.h"):
+    for f in ("gen.hip", "gemm_device.h", "split16.h", "common.h", "kernels.h"):
         h.update(open(os.path.join(ROOT, "paper_1805_11462_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -142,13 +142,13 @@ PEAK_HBM_GBS = 8000.0
 
 
 def issued_mfma(w, achieved_tflops):
-    """What the generator's matrix cores execute: its products run as bf16 MFMAs on bf16 term planes. fp32
-    models: weights and activations as three bf16 terms each, six term products per fp32 product
-    (fp32-accurate); bf16 models: two activation terms against the exact bf16 weights. `frac` is the issued
-    bf16 MFMA rate against the bf16 dense peak."""
-    products = 6 if w.wdtype == "fp32" else 2
+    """What the generator's matrix cores execute: its products run as fp16 MFMAs on two-term fp16 operands.
+    fp32 models: three term products per fp32 product (fp32-accurate); bf16 models: two activation terms
+    against the weights, which one term holds exactly. `frac` is the issued rate against the dense 16-bit
+    peak."""
+    products = 3 if w.wdtype == "fp32" else 2
     rate = achieved_tflops * products
-    return {"mfma": "v_mfma_f32_16x16x32_bf16", "term_products": products, "achieved": round(rate, 1),
+    return {"mfma": "v_mfma_f32_16x16x32_f16", "term_products": products, "achieved": round(rate, 1),
             "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(rate / PEAK_BF16_TFLOPS, 4)}
 
 
@@ -287,7 +287,7 @@ def main():
                    "target_tokens_per_step": tokens // max(args.steps, 1)},
         "step_ms": {"min": round(min(step_s) * 1e3, 3), "median": round(sorted(step_s)[len(step_s) // 2] * 1e3, 3),
                     "max": round(max(step_s) * 1e3, 3)},
-        "roofline": {"kernel": "k_gemm_gen_lds (generator GEMM + fused log-softmax/top-K partials)",
+        "roofline": {"kernel": "k_gen_wide (generator GEMM + fused log-softmax partials)",
                      "bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(achieved / peak, 4), "traffic": traffic_from_counters(w.name),
                      "launches_timed": n_gen, "avg_launch_us": round(avg_gen_s * 1e6, 2),
@@ -381,7 +381,7 @@ def bench_score(args, w, weights, tr, src, lens, src_d, lens_d):
         "data": "synthetic (seeded weights, bounded-Zipf source and target tokens)",
         "config": {"workload": f"{w.name} teacher-forced scoring, batch {B}, target length {T}",
                    "global_batch": B, "target_len": T},
-        "roofline": {"kernel": "k_gemm_gen_lds (generator GEMM + fused log-softmax partials)", "bound": "mfma",
+        "roofline": {"kernel": "k_gen_wide (generator GEMM + fused log-softmax partials)", "bound": "mfma",
                      "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(achieved / peak, 4), "traffic": None, "launches_timed": n_gen,
                      "avg_launch_us": round(avg_gen_s * 1e6, 2), "flops_per_launch": gen_flops,

@@ -59,10 +59,11 @@ typedef struct {
   int emb, hidden;
   int src_vocab, tgt_vocab;
   int wdtype;                      /* 0 = fp32 weights and fp32-accurate products (the vocabulary
-                                      projection runs them as six bf16 term products of three-term
-                                      splits of both operands, accumulated in fp32); 1 = bf16 weights
-                                      and MFMA operands (activations as bf16 terms), fp32 accumulation,
-                                      cell state and softmax */
+                                      projection runs them as three fp16 term products of two-term
+                                      scaled splits of both operands, accumulated in fp32, closer to
+                                      64 bits than fp32 products); 1 = bf16 weights and MFMA operands
+                                      (activations as bf16 or fp16 terms), fp32 accumulation, cell
+                                      state and softmax */
   int pad_id, unk_id, bos_id, eos_id;
   int attn_type;                   /* attention score (Section 4.2 names three types, none with biases):
                                       ONMT_ATTN_GENERAL e_s = q . W_a m_s;
@@ -190,11 +191,12 @@ int onmt_device_status(onmt_model* model, int* code);
 /* ---- Decoder step without allocation ------------------------------------------------------------------
  * For callers that cannot allocate memory or synchronize per call (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): onmt_decode_step without the step_ws argument. Its
- * scratch (what step_ws holds) is a device array of ONMT_NOALLOC_SCRATCH_BYTES built into the library,
+ * scratch is a device array of ONMT_NOALLOC_SCRATCH_BYTES built into the library,
  * one per GPU, located when a model is created on that device (or at the first call on it); the call
  * itself allocates nothing and never waits. Inputs are validated on the device as with
- * ONMT_VALIDATE_DEVICE (check onmt_device_status). A step whose onmt_step_ws_bytes(model, B, S_max, K)
- * exceeds ONMT_NOALLOC_SCRATCH_BYTES is refused with ONMT_EUNSUPPORTED (16 MiB holds every workload of
+ * ONMT_VALIDATE_DEVICE (check onmt_device_status). The scratch holds per-tile top-K lists (8 K bytes per row
+ * and 128 vocabulary entries) where step_ws holds the step's logits; a step that needs more than
+ * ONMT_NOALLOC_SCRATCH_BYTES is refused with ONMT_EUNSUPPORTED (16 MiB holds every workload of
  * this library's benchmarks: 320 rows over a 50000-word vocabulary at beam 5 take 7.3 MB). All calls on
  * one GPU share its array, which keeps the last call's contents: calls that overlap on one GPU (on
  * different streams, or from different threads) race and must not be issued. Arguments, outputs and

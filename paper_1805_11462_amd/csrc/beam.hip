@@ -5,28 +5,25 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "split16.h"
 
 namespace onmt {
 
 // ------------------------------------------------------------------ softmax merge
-// One wave merges one row's generator partials (per column tile: max, sum of exp, top-K list) into the
-// row's logsumexp and top-K (larger logit first, smaller id on ties).
+// One wave merges one row's generator partials (per column tile: max, sum of exp) and logits into the row's
+// logsumexp and top-K (larger logit first, smaller id on ties).
 //
 // theta = the K-th largest of the 64 per-lane tile maxima is a lower bound on the row's K-th largest
 // logit (those K values are maxima of K distinct tiles), so only tiles whose maximum reaches theta can
-// contribute. Their lists are loaded in one batch (one qualifying tile per lane), the entries >= theta
-// are appended to LDS, and each survivor's position in the result is the number of survivors that come
-// before it, which every lane counts for its own entry independently. Rows with more qualifying tiles
-// or survivors than fit (ties at theta) are merged by the same rank rule over all entries instead.
+// contribute: K tiles or a few more. Their logits are read (a tile's 128 in one access of the wave, four tiles in
+// flight), the allowed entries >= theta are appended to LDS, and each survivor's position in the result is the
+// number of survivors that come before it, which every lane counts for its own entry independently. Rows with
+// more qualifying tiles or survivors than fit (ties at theta) take K rounds of an argmax over all columns.
 constexpr int kMaxTilesPerLane = 16;          // tiles per row <= 64 * 16 (vocabulary <= 131072)
 constexpr int kSurvivorCap = 256;
 constexpr int kQualCap = 256;                 // qualifying tiles listed per row
+constexpr int kTileCols = 128;
 
-// Row partials start at pmax/psum + row * ntiles (loaded by row_tiles_load) and pval/pid + row * ntiles * K. Lane 0 writes
-// out_val[k] = logit - lse (K entries), out_id[k] and *out_lse. sv/si/cnt/qt: this wave's LDS scratch
-// (kSurvivorCap survivors, kQualCap qualifying tile ids).
-// pfmax (optional, filters active): per-tile largest allowed logit, which then replaces the tile maximum
-// in the bound (the lists hold allowed entries only; the logsumexp still covers every column).
 // The row's tile maxima and sums (lane l holds tiles l + 64 j), every load issued before the first use.
 __device__ __forceinline__ void row_tiles_load(const float* __restrict__ pmax, const float* __restrict__ psum,
                                                int ntiles, float (&tm)[kMaxTilesPerLane],
@@ -40,13 +37,19 @@ __device__ __forceinline__ void row_tiles_load(const float* __restrict__ pmax, c
   }
 }
 
-// tm / tq: the row's tile maxima and sums from row_tiles_load (tm is overwritten).
+// Whether column c of a row is no candidate (blocked_unk: the row's hypothesis has used up its UNKs).
+__device__ inline bool filtered(const GenPartials& gp, bool blocked_unk, int c) {
+  return (gp.banned_bits && ((gp.banned_bits[c >> 5] >> (c & 31)) & 1u)) || (blocked_unk && c == gp.unk_id);
+}
+
+// tm / tq: the row's tile maxima and sums from row_tiles_load (tm is overwritten). The wave writes out_val[k] =
+// logit - lse and out_id[k] for k < K (-inf and the largest id where fewer candidates exist), lane 0 *out_lse.
+// sv / si / qt: this wave's LDS scratch (kSurvivorCap survivors, kQualCap qualifying tile ids).
 __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], const float (&tq)[kMaxTilesPerLane],
-                                               const float* __restrict__ pval, const int32_t* __restrict__ pid,
-                                               const float* __restrict__ pfmax, int ntiles, int K, float* sv,
-                                               int* si, int* cnt, int* qt, float* out_val, int32_t* out_id,
-                                               float* out_lse) {
+                                               const GenPartials& gp, int row, int K, float* sv, int* si, int* qt,
+                                               float* out_val, int32_t* out_id, float* out_lse) {
   const int lane = threadIdx.x & 63;
+  const int ntiles = gp.ntiles;
   const float ninf = -__builtin_inff();
   float mx = ninf;
 #pragma unroll
@@ -59,15 +62,19 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
     if (t < ntiles) sm += tq[j] * __expf(tm[j] - gmx);
   }
   const float lse = gmx + __logf(wave_sum(sm));
-  if (pfmax) {
+  if (lane == 0 && out_lse) *out_lse = lse;
+  if (K == 0) return;
+  if (gp.pfmax) {           // the largest allowed logits bound the top-K (the logsumexp covers every column)
+    const float* pf = gp.pfmax + (size_t)row * ntiles;
     mx = ninf;
 #pragma unroll
     for (int j = 0; j < kMaxTilesPerLane; ++j) {
       const int t = lane + j * kWave;
-      tm[j] = t < ntiles ? pfmax[t] : ninf;
+      tm[j] = t < ntiles ? pf[t] : ninf;
       mx = fmaxf(mx, tm[j]);
     }
   }
+  const bool blocked_unk = gp.pfmax && gp.unk_cnt && gp.max_unk >= 0 && gp.unk_cnt[row] >= gp.max_unk;
 
   // theta: K rounds of a wave maximum, each removing the (lowest) lane that holds it
   float cur = mx, theta = ninf;
@@ -92,37 +99,56 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
     }
     nq += __popcll(m);
   }
-  if (lane == 0) *cnt = 0;
+  if (lane < K) {
+    out_val[lane] = ninf;
+    if (out_id) out_id[lane] = 0x7fffffff;
+  }
   __builtin_amdgcn_wave_barrier();
 
-  // survivors: the lists of the qualifying tiles, one tile per lane, loaded in one batch
-  if (nq <= kQualCap) {
-    for (int q0 = 0; q0 < nq; q0 += kWave) {
-      const int qi = q0 + lane;
-      if (qi < nq) {
-        const size_t o = (size_t)qt[qi] * K;
-        float v[kMaxBeam];
-        int id[kMaxBeam];
+  // survivors, in no particular order
+  int n = 0;
+  auto add = [&](bool keep, float v, int id) {
+    const unsigned long long m = __ballot(keep);
+    if (keep) {
+      const int pos = n + __popcll(m & below);
+      if (pos < kSurvivorCap) {
+        sv[pos] = v;
+        si[pos] = id;
+      }
+    }
+    n += __popcll(m);
+  };
+  const float* lrow = gp.logits ? gp.logits + (size_t)row * gp.ld_logits : nullptr;
+  if (nq <= kQualCap && lrow) {
+    constexpr int kBatch = 4;
+    for (int q0 = 0; q0 < nq && n <= kSurvivorCap; q0 += kBatch) {
+      float v[kBatch][2];
+      int c0[kBatch];
 #pragma unroll
-        for (int i = 0; i < kMaxBeam; ++i) {
-          v[i] = i < K ? pval[o + i] : ninf;
-          id[i] = i < K ? pid[o + i] : 0;
-        }
+      for (int u = 0; u < kBatch; ++u) {
+        c0[u] = q0 + u < nq ? qt[q0 + u] * kTileCols + lane : gp.V;
+        v[u][0] = c0[u] < gp.V ? lrow[c0[u]] : ninf;
+        v[u][1] = c0[u] + kWave < gp.V ? lrow[c0[u] + kWave] : ninf;
+      }
 #pragma unroll
-        for (int i = 0; i < kMaxBeam; ++i) {
-          if (i < K && v[i] >= theta) {
-            const int pos = atomicAdd(cnt, 1);
-            if (pos < kSurvivorCap) {
-              sv[pos] = v[i];
-              si[pos] = id[i];
-            }
-          }
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int c = c0[u] + kWave * i;
+          add(c < gp.V && v[u][i] > ninf && v[u][i] >= theta && !(gp.pfmax && filtered(gp, blocked_unk, c)), v[u][i], c);
         }
+    }
+  } else if (nq <= kQualCap) {         // top-K lists, one tile per lane
+    for (int q0 = 0; q0 < nq && n <= kSurvivorCap; q0 += kWave) {
+      const size_t o = q0 + lane < nq ? ((size_t)row * ntiles + qt[q0 + lane]) * K : 0;
+      for (int i = 0; i < K; ++i) {
+        const float v = q0 + lane < nq ? gp.pval[o + i] : ninf;
+        const int id = q0 + lane < nq ? gp.pid[o + i] : 0x7fffffff;
+        add(id != 0x7fffffff && v >= theta, v, id);
       }
     }
   }
   __builtin_amdgcn_wave_barrier();
-  const int n = *cnt;
   if (nq <= kQualCap && n <= kWave) {
     // one survivor per lane, ranked against the others through the scalar unit
     const float v = lane < n ? sv[lane] : ninf;
@@ -145,51 +171,67 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
       }
     }
   } else {
-    // many ties at theta: rank every list entry against every other (slow, but only for degenerate rows)
-    for (int c = lane; c < ntiles * K; c += kWave) {
-      const float v = pval[c];
-      const int id = pid[c];
-      if (v < theta) continue;
-      int r = 0;
-      for (int d = 0; d < ntiles * K && r < K; ++d) r += before(pval[d], pid[d], v, id) ? 1 : 0;
-      if (r < K) {
-        out_val[r] = v - lse;
-        if (out_id) out_id[r] = id;
+    // many ties at theta: K rounds of an argmax over everything that comes after the previous round's choice
+    const size_t lo = (size_t)row * ntiles * K;
+    const int total = lrow ? gp.V : ntiles * K;
+    float pv = __builtin_inff();
+    int pi = -1;
+    for (int k = 0; k < K; ++k) {
+      float bv = ninf;
+      int bi = 0x7fffffff;
+      for (int c = lane; c < total; c += kWave) {
+        const float v = lrow ? lrow[c] : gp.pval[lo + c];
+        const int id = lrow ? c : gp.pid[lo + c];
+        if (id == 0x7fffffff || !(v > ninf) || (gp.pfmax && filtered(gp, blocked_unk, id))) continue;
+        if (before(pv, pi, v, id) && before(v, id, bv, bi)) {
+          bv = v;
+          bi = id;
+        }
       }
+#pragma unroll
+      for (int o = kWave / 2; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, kWave);
+        const int oi = __shfl_xor(bi, o, kWave);
+        if (before(ov, oi, bv, bi)) {
+          bv = ov;
+          bi = oi;
+        }
+      }
+      if (bi == 0x7fffffff) break;
+      if (lane == 0) {
+        out_val[k] = bv - lse;
+        if (out_id) out_id[k] = bi;
+      }
+      pv = bv;
+      pi = bi;
     }
   }
-  if (lane == 0 && out_lse) *out_lse = lse;
 }
 
 constexpr int kMergeWaves = 4;
 
-__global__ __launch_bounds__(kMergeWaves * kWave) void k_lse_topk(const float* __restrict__ pmax,
-                                                                  const float* __restrict__ psum,
-                                                                  const float* __restrict__ pval,
-                                                                  const int32_t* __restrict__ pid, int M, int ntiles,
-                                                                  int K, float* __restrict__ out_val,
+__global__ __launch_bounds__(kMergeWaves * kWave) void k_lse_topk(GenPartials gp, int M, int K,
+                                                                  float* __restrict__ out_val,
                                                                   int32_t* __restrict__ out_id,
                                                                   float* __restrict__ out_lse) {
   __shared__ float sv[kMergeWaves][kSurvivorCap];
   __shared__ int si[kMergeWaves][kSurvivorCap];
   __shared__ int qt[kMergeWaves][kQualCap];
-  __shared__ int cnt[kMergeWaves];
   const int w = threadIdx.x >> 6;
   const int row = blockIdx.x * kMergeWaves + w;
   if (row >= M) return;
-  const size_t base = (size_t)row * ntiles;
+  const size_t base = (size_t)row * gp.ntiles;
   float tm[kMaxTilesPerLane], tq[kMaxTilesPerLane];
-  row_tiles_load(pmax + base, psum + base, ntiles, tm, tq);
-  row_merge_wave(tm, tq, pval + base * K, pid + base * K, nullptr, ntiles, K, sv[w], si[w], &cnt[w], qt[w],
-                 out_val + (size_t)row * K, out_id ? out_id + (size_t)row * K : nullptr,
-                 out_lse ? out_lse + row : nullptr);
+  row_tiles_load(gp.pmax + base, gp.psum + base, gp.ntiles, tm, tq);
+  row_merge_wave(tm, tq, gp, row, K, sv[w], si[w], qt[w], out_val + (size_t)row * K,
+                 out_id ? out_id + (size_t)row * K : nullptr, out_lse ? out_lse + row : nullptr);
 }
 
-hipError_t lse_topk_merge(const float* pmax, const float* psum, const float* pval, const int32_t* pid, int M,
-                          int ntiles, int K, float* out_val, int32_t* out_id, float* out_lse, hipStream_t st) {
-  if (ntiles > kWave * kMaxTilesPerLane || K > kMaxBeam) return hipErrorInvalidValue;
+hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, int32_t* out_id, float* out_lse,
+                          hipStream_t st) {
+  if (gp.ntiles > kWave * kMaxTilesPerLane || K > kMaxBeam || (K > 0 && !gp.logits && !gp.pval)) return hipErrorInvalidValue;
   const dim3 grid((M + kMergeWaves - 1) / kMergeWaves), block(kMergeWaves * kWave);
-  hipLaunchKernelGGL(k_lse_topk, grid, block, 0, st, pmax, psum, pval, pid, M, ntiles, K, out_val, out_id, out_lse);
+  hipLaunchKernelGGL(k_lse_topk, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
   return hipGetLastError();
 }
 
@@ -316,7 +358,6 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
   __shared__ float sv[kMaxBeam][kSurvivorCap];
   __shared__ int si[kMaxBeam][kSurvivorCap];
   __shared__ int qt[kMaxBeam][kQualCap];
-  __shared__ int cnt[kMaxBeam];
   __shared__ float tkv[kMaxBeam][kMaxBeam];
   __shared__ int tki[kMaxBeam][kMaxBeam];
   const int b = blockIdx.x;
@@ -341,9 +382,7 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
     best_t0 = p.best_t[b];
   }
   if (my_score > ninf) {
-    row_merge_wave(tm, tq, gp.pval + base * K, gp.pid + base * K,
-                   gp.pfmax ? gp.pfmax + base : nullptr, gp.ntiles, K, sv[w], si[w], &cnt[w], qt[w], tkv[w], tki[w],
-                   nullptr);
+    row_merge_wave(tm, tq, gp, r0 + w, K, sv[w], si[w], qt[w], tkv[w], tki[w], nullptr);
   }
   __syncthreads();
   if (w != 0) return;

@@ -4,19 +4,19 @@
 // row-mapped segments (embedding rows by token id, state rows by beam parent, plain activations)
 // and W is a packed weight matrix. Tiles are staged through two LDS buffers; global loads run two
 // K stages ahead in registers so that a stage's loads have a full stage of MFMA work to hide behind.
-// Where the bf16 operands are pre-split term planes (the bf16 generator and decoder layers), buffer
-// loads with an LDS destination move them straight into the stage buffers instead.
+// LSTM tiles whose operands are plain fp32 rows or stored bf16 term planes load them straight into LDS
+// instead.
 // Products use 16x16 MFMA tiles: v_mfma_f32_16x16x4_f32 for fp32 operands and
 // v_mfma_f32_16x16x32_bf16 for bf16 operands, always accumulating in fp32. Waves may split K
 // inside the workgroup (WK > 1); their partial tiles are summed in LDS before the epilogue.
 //
-// Epilogues: plain bias(+tanh) store; LSTM gate nonlinearities and cell update (Section 2 item
-// (a) of the OpenNMT paper) over gate-blocked columns; and the generator's per-tile row max,
-// sum of exponentials and top-K, so the vocabulary logits never need to reach memory.
+// Epilogues: plain bias(+tanh) store, and LSTM gate nonlinearities and cell update (Section 2
+// item (a) of the OpenNMT paper) over gate-blocked columns.
 
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_device.h"
 #include "kernels.h"
 
 namespace onmt {
@@ -59,76 +59,9 @@ struct Tile {
   __device__ static int swz(int row) { return (row >> RSH) & SMASK; }
 };
 
-// XCD-aware tile order: blocks are dealt round-robin to the 8 XCDs, so renumber them so that each
-// XCD receives a contiguous range of logical tiles; M varies fastest, so the M tiles that share a
-// weight tile run on the same XCD and share its L2.
-__device__ inline int xcd_remap(int bid, int nblocks) {
-  const int xcd = bid & 7, local = bid >> 3;
-  const int full = nblocks >> 3, rem = nblocks & 7;
-  return xcd * full + (xcd < rem ? xcd : rem) + local;
-}
-
-__device__ inline uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
-
-// Split 8 fp32 values into three bf16 terms p0 = RNE(x), p1 = RNE(x - p0), p2 = RNE(x - p0 - p1). Each
-// remainder is exact in fp32 (it drops leading bits of x), so p0 + p1 + p2 keeps about 24 significant
-// bits of x: the fp32 value itself, as the bf16 products see it. (Two terms keep ~16 bits, which over the
-// 120 steps of the 4 x 1000 decoder recurrence let a hypothesis's log-prob drift to the bf16 tolerance.)
-// The conversions are gfx950's packed fp32 -> bf16 (round to nearest even), two values per instruction.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ inline void split_bf16x8(const float4& a, const float4& b, uint4& p0, uint4& p1, uint4& p2) {
-  const f32x2_t x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
-  uint32_t t0[4], t1[4], t2[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const bf16x2_t v0 = __builtin_convertvector(x[i], bf16x2_t);
-    const f32x2_t r1 = x[i] - __builtin_convertvector(v0, f32x2_t);
-    const bf16x2_t v1 = __builtin_convertvector(r1, bf16x2_t);
-    const f32x2_t r2 = r1 - __builtin_convertvector(v1, f32x2_t);
-    const bf16x2_t v2 = __builtin_convertvector(r2, bf16x2_t);
-    t0[i] = __builtin_bit_cast(uint32_t, v0);
-    t1[i] = __builtin_bit_cast(uint32_t, v1);
-    t2[i] = __builtin_bit_cast(uint32_t, v2);
-  }
-  p0 = make_uint4(t0[0], t0[1], t0[2], t0[3]);
-  p1 = make_uint4(t1[0], t1[1], t1[2], t1[3]);
-  p2 = make_uint4(t2[0], t2[1], t2[2], t2[3]);
-}
-
-__device__ inline void split_bf16(float x, uint16_t& p0, uint16_t& p1, uint16_t& p2) {
-  uint4 a, b, c;
-  split_bf16x8(make_float4(x, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f), a, b, c);
-  p0 = (uint16_t)(a.x & 0xffffu);
-  p1 = (uint16_t)(b.x & 0xffffu);
-  p2 = (uint16_t)(c.x & 0xffffu);
-}
-
-// Buffer resource descriptor (gfx9 family word 3). Loads through it return zeros past num_records, so
-// an invalid row is given an offset beyond every buffer instead of a branch.
-constexpr int kBufWord3 = 0x00020000;
-constexpr uint32_t kNoRow = 0x80000000u;      // byte offset past the end of any buffer (buffers < 2 GiB)
-
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, kBufWord3);
-}
-
-// LDS address of a byte in a __shared__ array, as the LDS-destination buffer loads take it. (Declared at
-// file scope: a local typedef of this pointer type inside a kernel template stops the host stub from
-// being emitted.)
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-__device__ inline lds_ptr_t lds_at(char* p) { return (lds_ptr_t)p; }
-
-__device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
-
 // Main loop: leaves the (WK-way partial) fp32 output tile in LDS at smem, layout [WK][BM][CROW].
-// CBIAS (single-K-group tiles): cb[y] is added to the lane's column of output block y as the tile is
-// written (the generator's bias, loaded before the main loop by gen_col_bias).
-template <class T, class C, int NSEG, bool CBIAS = false>
-__device__ inline void gemm_tile(const AOp& a, const BOp& b, int m0, int n0, char* smem, const float* cb = nullptr) {
-  static_assert(!CBIAS || C::WK == 1, "a bias is added to whole sums only");
+template <class T, class C, int NSEG>
+__device__ inline void gemm_tile(const AOp& a, const BOp& b, int m0, int n0, char* smem) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -349,11 +282,8 @@ __device__ inline void gemm_tile(const AOp& a, const BOp& b, int m0, int n0, cha
 #pragma unroll
     for (int y = 0; y < C::TN; ++y)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float o = acc[x][y][v];
-        if constexpr (CBIAS) o += cb[y];
-        Ct[(wm * C::TM * 16 + x * 16 + 4 * g + v) * C::CROW + wn * C::TN * 16 + y * 16 + i16] = o;
-      }
+      for (int v = 0; v < 4; ++v)
+        Ct[(wm * C::TM * 16 + x * 16 + 4 * g + v) * C::CROW + wn * C::TN * 16 + y * 16 + i16] = acc[x][y][v];
   __syncthreads();
 }
 
@@ -378,8 +308,14 @@ __global__ __launch_bounds__(C::NT) void k_gemm_store(AOp a, BOp b, StoreParams 
     const int r = e / (C::BN / 4), c = (e % (C::BN / 4)) * 4;
     const int gr = m0 + r, gc = n0 + c;
     const bool out = gc < p.ncols;                      // ncols is a multiple of 4
-    const bool split = p.hi && gc < p.ncols_hl;
-    if (gr >= a.M || !(out || split)) continue;
+    const bool split = p.hi && gc < p.ncols_hl, s16 = p.s16 && gc < 32 * p.kb16;
+    if (gr >= a.M) {        // the two-term operand's last 16-row block is filled up with zeros
+      const float zero[4] = {0.f, 0.f, 0.f, 0.f};
+      if (s16 && p.r0_16 + gr < (p.r0_16 + a.M + kFragRows - 1) / kFragRows * kFragRows)
+        store_act4(p.s16, p.r0_16 + gr, gc, p.kb16, zero);
+      continue;
+    }
+    if (!(out || split || s16)) continue;
     float v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -394,6 +330,7 @@ __global__ __launch_bounds__(C::NT) void k_gemm_store(AOp a, BOp b, StoreParams 
       *(uint2*)(p.lo + (size_t)gr * p.ld_hl + gc) = make_uint2(t1.x, t1.y);
       *(uint2*)(p.lo2 + (size_t)gr * p.ld_hl + gc) = make_uint2(t2.x, t2.y);
     }
+    if (s16) store_act4(p.s16, p.r0_16 + gr, gc, p.kb16, v);
   }
 }
 
@@ -514,176 +451,6 @@ __global__ __launch_bounds__(C::NT) void k_gemm_lstm2(LstmPair g) {
   }
 }
 
-// Exchange with lane l ^ X (X = 1 or 2) inside each group of four lanes: a DPP quad permutation, so the
-// four threads of an epilogue row trade values without a round trip through LDS.
-template <int X>
-__device__ inline int quad_xor(int v) {
-  static_assert(X == 1 || X == 2, "quad lanes");
-  return __builtin_amdgcn_mov_dpp(v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, false);   // quad_perm [1,0,3,2] / [2,3,0,1]
-}
-template <int X>
-__device__ inline float quad_xor(float v) {
-  return __builtin_bit_cast(float, quad_xor<X>(__builtin_bit_cast(int, v)));
-}
-
-// Generator epilogue over the 64 x 128 output tile in LDS: 4 threads per row, 32 interleaved columns
-// each. Row max and sum of exponentials are combined across the row's four lanes (quad_xor); the tile's
-// top-K is taken with K rounds of a 4-lane argmax (larger logit first, smaller id on ties), each thread
-// skipping the columns it already gave away.
-// BIASED: the output tile already holds product + bias (added as the tile was written, the same single
-// fp32 addition), so the epilogue issues no bias loads of its own.
-template <class C, bool BIASED = false>
-__device__ inline void gen_epilogue(const char* smem, const GenParams& p, int M, int m0, int n0, int nt, int tid) {
-  static_assert(C::NT / C::BM == 4 && C::BN == 128, "generator tile is 64 x 128 with 256 threads");
-  const float* Ct = (const float*)smem;
-  // thread tid = (row r, part p) owns columns 4 j + p, j < 32: the 64 lanes of a wave then read 64
-  // different banks of the output tile for every j
-  const int r = tid >> 2, part = tid & 3;
-  const int row = m0 + r;
-  const float ninf = -__builtin_inff();
-  float z[32];
-  float mx = ninf;
-  if (n0 + C::BN <= p.V) {                 // uniform: every column of the tile is a vocabulary entry
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      if constexpr (BIASED)
-        z[j] = ctile<C>(Ct, r, 4 * j + part);
-      else
-        z[j] = ctile<C>(Ct, r, 4 * j + part) + p.bias[n0 + 4 * j + part];
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const int gc = n0 + 4 * j + part;
-      if constexpr (BIASED)
-        z[j] = gc < p.V ? ctile<C>(Ct, r, 4 * j + part) : ninf;
-      else
-        z[j] = gc < p.V ? ctile<C>(Ct, r, 4 * j + part) + p.bias[gc] : ninf;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 32; ++j) mx = fmaxf(mx, z[j]);
-  if (p.want && row < M) {
-    const int wc = p.want[row] - n0;      // this thread holds column 4 j + part of the tile
-    if (wc >= 0 && wc < C::BN && (wc & 3) == part) {
-#pragma unroll
-      for (int j = 0; j < 32; ++j)
-        if (4 * j + part == wc) p.want_logit[row] = z[j];
-    }
-  }
-  if (p.logits && row < M) {
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const int gc = n0 + 4 * j + part;
-      if (gc < p.V) p.logits[(size_t)row * p.ld_logits + gc] = z[j];
-    }
-  }
-  float rmx = fmaxf(mx, quad_xor<1>(mx));
-  rmx = fmaxf(rmx, quad_xor<2>(rmx));
-  float sm = 0.f;
-#pragma unroll
-  for (int j = 0; j < 32; ++j) sm += __expf(z[j] - rmx);     // exp(-inf) = 0 for columns past V
-  sm += quad_xor<1>(sm);
-  sm += quad_xor<2>(sm);
-  const size_t o = (size_t)row * p.ntiles + nt;
-  if (part == 0 && row < M) {
-    p.pmax[o] = rmx;
-    p.psum[o] = sm;
-  }
-  // filtered columns start out taken, so the top-K never picks them
-  uint32_t taken = 0;
-  if (p.banned_bits) {
-    uint32_t words[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c0 = n0 + 32 * i;
-      words[i] = c0 < p.V ? p.banned_bits[c0 >> 5] : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {            // column offset 4 j + part lies in word j / 8
-      if ((words[j >> 3] >> (4 * (j & 7) + part)) & 1u) taken |= 1u << j;
-    }
-  }
-  if (p.unk_cnt && row < M && p.max_unk >= 0 && p.unk_cnt[row] >= p.max_unk) {
-    const int c = p.unk_id - n0;
-    if (c >= 0 && c < C::BN && (c & 3) == part) taken |= 1u << (c >> 2);
-  }
-  // with no filter every column is free in the first round, whose best is then the thread's maximum at
-  // its first (smallest-id) position
-  const bool fast0 = !p.banned_bits && !p.unk_cnt;
-  for (int k = 0; k < p.K; ++k) {
-    float bv = ninf;
-    int bj = 0;
-    if (k == 0 && fast0) {
-#pragma unroll
-      for (int j = 31; j >= 0; --j) {
-        if (z[j] == mx) {
-          bv = z[j];
-          bj = j;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        const bool free = !((taken >> j) & 1u);
-        if (free && z[j] > bv) {                  // strict: the earlier (smaller id) column wins ties
-          bv = z[j];
-          bj = j;
-        }
-      }
-    }
-    int bid = bv > ninf ? n0 + 4 * bj + part : 0x7fffffff;
-    const int mine = bid;
-    {
-      const float ov = quad_xor<1>(bv);
-      const int oi = quad_xor<1>(bid);
-      if (before(ov, oi, bv, bid)) {
-        bv = ov;
-        bid = oi;
-      }
-    }
-    {
-      const float ov = quad_xor<2>(bv);
-      const int oi = quad_xor<2>(bid);
-      if (before(ov, oi, bv, bid)) {
-        bv = ov;
-        bid = oi;
-      }
-    }
-    if (bid == mine && bv > ninf) taken |= 1u << bj;
-    if (part == 0 && row < M) {
-      p.pval[o * p.K + k] = bv;
-      p.pid[o * p.K + k] = bid;
-      if (k == 0 && p.pfmax) p.pfmax[o] = bv;
-    }
-  }
-}
-
-
-// The generator bias of the columns this lane writes in the output tile (column wn * TN * 16 + 16 y + i16
-// of the tile at n0, for y < TN; 0 past V), loaded before the main loop so that its latency hides there.
-template <class C>
-__device__ inline void gen_col_bias(const GenParams& p, int n0, int wn, int i16, float (&cb)[C::TN]) {
-#pragma unroll
-  for (int y = 0; y < C::TN; ++y) {
-    const int gc = n0 + wn * C::TN * 16 + y * 16 + i16;
-    cb[y] = gc < p.V ? p.bias[gc] : 0.f;
-  }
-}
-
-template <class T, class C, int NSEG>
-__global__ __launch_bounds__(C::NT) void k_gemm_gen(AOp a, BOp b, GenParams p, int nm, int nblocks) {
-  __shared__ __attribute__((aligned(16))) char smem[C::LDS];
-  const int L = xcd_remap(blockIdx.x, nblocks);
-  const int mt = L % nm, nt = L / nm;
-  const int m0 = mt * C::BM, n0 = nt * C::BN;
-  const int wave = threadIdx.x >> 6;
-  float cb[C::TN];
-  gen_col_bias<C>(p, n0, (wave / C::WK) % C::WN, threadIdx.x & 15, cb);
-  gemm_tile<T, C, NSEG, true>(a, b, m0, n0, smem, cb);
-  gen_epilogue<C, true>(smem, p, a.M, m0, n0, nt, threadIdx.x);
-}
-
 // ---------------------------------------------------------------- launchers
 
 using TileWide32 = Tile<float, 2, 2, 1, 2, 4, 32>;
@@ -703,207 +470,6 @@ using TileThin16 = Tile<__bf16, 1, 1, 4, 1, 4, 32>;
 // the weights are re-read by half as many row tiles, which matters more than the halved workgroup count
 // once the bf16 products are cheap (decoder layers at 320-512 rows: 16-32% faster).
 using TileMid16 = Tile<__bf16, 1, 2, 2, 2, 2, 32>;
-// fp32 generator (fp32 MFMA): the 64 x 128 tile of the wide shapes with a 16-element K stage, which
-// halves the LDS stage buffers so that four workgroups fit on a CU.
-using TileGen32 = Tile<float, 2, 2, 1, 2, 4, 16>;
-// 32 x 128 fp32 generator tiles (two waves) where the last 64-row tile would be at most half full and the
-// rows are few: at 160 rows 91 us instead of 108 us (64-row tiles compute 192 rows), at 96 rows 64 instead
-// of 78 us; at multiples of 64 rows, and at 480, the 64-row tile is faster. Same partials, bitwise.
-using TileGen32h = Tile<float, 1, 2, 1, 2, 4, 16>;
-static inline bool gen_rows32(int M) {
-  const int r = M % 64;
-  return M <= 256 && r > 0 && r <= 32;
-}
-static_assert(TileGen32h::BN == TileGen32::BN && TileGen32::BN == 128,
-              "all generator tiles give the same 128-column partial tiles");
-// Pre-split bf16 generator: 64 x 256 tiles (8 waves of 32 x 64; the activations are re-read by half as
-// many column tiles as with 64 x 128) and two LDS stages of 24 KB; at 320 and 512 rows this measured
-// 10-15% faster than 64 x 128 tiles with three 16 KB stages, and three or four stages of 64 x 256 slower.
-constexpr int kGenStages = 2;
-constexpr int kGenWN = 4;
-// The pre-split generator multiplies the first two of the operand's bf16 term planes (~17 significant bits
-// of each activation, a relative error under 2^-16): its output leaves the recurrence, so the error stays
-// per step, ~1e-5 on a logit over 1000-wide rows, instead of compounding over the steps the way an error
-// of the decoder layers' operands does. The third plane serves those layers.
-constexpr int kGenPlanes = 2;
-// Three weight planes (fp32 weights): 64 x 128 tiles (four waves, two 36 KB stages, two workgroups per
-// CU). At 320 rows the generator took 108 us against 121 us with 64 x 256 tiles (one workgroup per CU)
-// and 140 us with the fp32 MFMA kernel. Where the last 64-row tile would be at most half full, the fp32
-// kernel's 32-row tiles win instead (160 rows: 84 us against 88 us; 32-row tiles of the three-plane
-// kernel, two waves per workgroup and one wave per SIMD, took 140 us), so those row counts stay on it.
-constexpr int kGen3WN = 2;
-bool gemm_gen_split_rows(int M) { return !gen_rows32(M); }
-
-// One 16-byte-per-lane buffer load into LDS (lane l writes 16 bytes at lds + 16 l). (A function of its
-// own: called directly under control flow inside a kernel template, the builtin stops the host-side
-// launch stub from being emitted.)
-__device__ inline void dma16(__amdgpu_buffer_rsrc_t r, char* lds, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 16, off, 0, 0, 0);
-}
-
-// Vector-memory wait until at most n loads of this wave are outstanding (expcnt and lgkmcnt left alone).
-constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | (((n >> 4) & 3) << 14); }
-
-// bf16 generator on a pre-split operand with its operands moved straight into LDS: buffer loads with an
-// LDS destination write one 1 KB slice per wave instruction (16 tile rows of 64 bytes, lane l at byte
-// 16 l), so a stage needs no staging registers and NSTG stages can be in flight at once. Each wave's loads
-// complete in issue order, so waiting until at most SPW (NSTG - 2) of its loads are outstanding (SPW per
-// stage) means its share of the oldest stage has landed; a barrier then makes the whole stage visible.
-// The barrier is the bare instruction: the fences of __syncthreads would also wait for the stages still
-// in flight. Fragment reads, products and the epilogue are those of the register-staged kernel.
-template <int WM, int WN, int NSTG, int NPA, int NPB>
-__global__ __launch_bounds__(64 * WM * WN) void k_gemm_gen_lds(GenSplitA a, BOp b, GenParams p, int nm,
-                                                              int nblocks) {
-  using C = Tile<__bf16, WM, WN, 1, 2, 4, 32>;         // (32 WM) x (64 WN) tile, waves of 32 x 64
-  using CE = Tile<__bf16, WM, 2, 1, 2, 4, 32>;          // the (32 WM) x 128 sub-tiles the epilogue works on
-  static_assert(C::BM % 16 == 0 && C::BK == 32 && C::CPR == 4 && C::WK == 1 && CE::BN == 128 &&
-                    C::BN % 128 == 0 && CE::BM == C::BM,
-                "the slice layout below is written for bf16 generator tiles of 16-row slices with 64-byte rows");
-  static_assert(C::BK == kGenKBlock, "a K stage is one block of the K-blocked weights");
-  constexpr int NW = C::NT / 64;
-  constexpr int ROWB = C::BK * 2;                       // bytes per tile row
-  constexpr int RPS = 16;                               // tile rows per 1 KB slice
-  constexpr int SA = C::BM / RPS, SB = C::BN / RPS;     // slices per plane of A, and of B
-  constexpr int NSL = NPA * SA + NPB * SB;              // slices per stage
-  constexpr int SPW = (NSL + NW - 1) / NW;              // slices (loads) per wave per stage, at most
-  constexpr int STG = (NPA * C::BM + NPB * C::BN) * ROWB;   // one stage: the A planes' rows, then B's
-  // term products kept: plane pair (pa, pb) with pa + pb < NPROD_MAX (two A planes against exact bf16
-  // weights; the six leading pairs of three planes each)
-  constexpr int NPROD_MAX = NPA > NPB ? NPA : NPB;
-  constexpr int NSUB = C::BN / 128;
-  constexpr int LDSB = NSTG * STG > NSUB * CE::CT ? NSTG * STG : NSUB * CE::CT;
-  // waves may move different numbers of slices only when every wait is for all loads (two stages)
-  static_assert((NSL % NW == 0 || NSTG == 2) && NSTG >= 2 && SPW * (NSTG - 2) < 64, "slice layout / wait count");
-  __shared__ __attribute__((aligned(16))) char smem[LDSB];
-  const int L = xcd_remap(blockIdx.x, nblocks);
-  const int mt = L % nm, nt = L / nm;
-  const int m0 = mt * C::BM, n0 = nt * C::BN;
-  // the wave index read into a scalar register: slice kinds derived from it are then known to be uniform,
-  // so the descriptor each load uses is picked by scalar branches rather than a per-lane loop
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i16 = lane & 15, g = lane >> 4;
-  const int wn = wave % C::WN, wm = wave / C::WN;
-  float cb[C::TN];
-  gen_col_bias<C>(p, n0, wn, i16, cb);
-
-  // slice q of a stage: rows 16 q.. of A plane q / SA (q < NPA SA), then of the B planes; wave w moves slices
-  // w, w + NW, ... (below NSL); lane's place in a slice: tile row lane / 4, 16-byte slot lane % 4 (chunk
-  // slot ^ swz)
-  const int srow = lane >> 2, sslot = lane & 3;
-  static_assert(NPA >= 1 && NPA <= kPlanes && (NPB == 1 || NPB == 3), "term planes of the operands");
-  const __amdgpu_buffer_rsrc_t rpl[kPlanes] = {make_rsrc(a.hi, (uint32_t)a.M * a.ld * 2),
-                                               make_rsrc(a.lo, (uint32_t)a.M * a.ld * 2),
-                                               make_rsrc(a.lo2, (uint32_t)a.M * a.ld * 2)};
-  const uint32_t wplane = (uint32_t)b.Np * b.Kp * 2;    // bytes per weight plane
-  __amdgpu_buffer_rsrc_t rw[NPB];
-#pragma unroll
-  for (int pb = 0; pb < NPB; ++pb) rw[pb] = make_rsrc((const char*)b.W + (size_t)pb * wplane, wplane);
-  int sl_kind[SPW], sl_lds[SPW];                        // A plane pa (pa), B plane pb (NPA + pb), -1 none
-  uint32_t sl_off[SPW];                                 // lane's byte offset in its operand at K = 0
-#pragma unroll
-  for (int i = 0; i < SPW; ++i) {
-    const int q = wave + NW * i;
-    const int kind = q >= NSL ? -1 : (q < NPA * SA ? q / SA : NPA + (q - NPA * SA) / SB);
-    const int trow = (kind >= NPA ? (q - NPA * SA) % SB : q % SA) * RPS + srow;   // row in its plane
-    const int chunk = sslot ^ C::swz(trow);
-    sl_kind[i] = kind;
-    sl_lds[i] = ((kind >= NPA ? NPA * C::BM + (kind - NPA) * C::BN : kind * C::BM) + trow - srow) * ROWB;
-    if (kind < 0) {
-      sl_off[i] = 0;
-    } else if (kind >= NPA) {                           // B rows past the packed matrix re-read its last row
-      const int br = min(n0 + trow, b.Np - 1);
-      sl_off[i] = ((uint32_t)br * C::BK + chunk * C::CH) * 2;   // in K block 0 (the stage adds its block)
-    } else {                                            // A rows past M re-read row M - 1 (never stored)
-      const int ar = min(m0 + trow, a.M - 1);
-      sl_off[i] = ((uint32_t)ar * a.ld + chunk * C::CH) * 2;
-    }
-  }
-  const int nst = a.kpad / C::BK;
-
-  f32x4 acc[C::TM][C::TN];
-#pragma unroll
-  for (int x = 0; x < C::TM; ++x)
-#pragma unroll
-    for (int y = 0; y < C::TN; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int col = (g ^ C::swz(i16)) * C::CH;           // this lane's 16-byte chunk of a fragment row
-  // stages past the last re-load the last one into a buffer that is never multiplied, which keeps every
-  // wave's count of loads in flight the same on every iteration; stage st of A is ROWB bytes into each
-  // row, of B the st-th K block of the weights
-#define ONMT_GEN_ISSUE(ST)                                                                              \
-  do {                                                                                                  \
-    char* sb_ = smem + ((ST) % NSTG) * STG;                                                             \
-    const uint32_t ks_ = (uint32_t)((ST) < nst ? (ST) : nst - 1);                                       \
-    const uint32_t ko_ = ks_ * ROWB, kb_ = ks_ * (uint32_t)b.Np * ROWB;                                 \
-    _Pragma("unroll") for (int i = 0; i < SPW; ++i) {                                                   \
-      if (sl_kind[i] == NPA)                                                                            \
-        dma16(rw[0], sb_ + sl_lds[i], sl_off[i] + kb_);                                                 \
-      else if (NPB > 1 && sl_kind[i] == NPA + 1)                                                        \
-        dma16(rw[NPB > 1 ? 1 : 0], sb_ + sl_lds[i], sl_off[i] + kb_);                                   \
-      else if (NPB > 2 && sl_kind[i] == NPA + 2)                                                        \
-        dma16(rw[NPB > 2 ? 2 : 0], sb_ + sl_lds[i], sl_off[i] + kb_);                                   \
-      else if (sl_kind[i] == 0)                                                                         \
-        dma16(rpl[0], sb_ + sl_lds[i], sl_off[i] + ko_);                                               \
-      else if (sl_kind[i] == 1)                                                                         \
-        dma16(rpl[1], sb_ + sl_lds[i], sl_off[i] + ko_);                                               \
-      else if (NPA > 2 && sl_kind[i] == 2)                                                              \
-        dma16(rpl[2], sb_ + sl_lds[i], sl_off[i] + ko_);                                               \
-    }                                                                                                   \
-  } while (0)
-#pragma unroll
-  for (int st = 0; st < NSTG - 1; ++st) ONMT_GEN_ISSUE(st);
-  for (int st = 0; st < nst; ++st) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(SPW * (NSTG - 2)));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    ONMT_GEN_ISSUE(st + NSTG - 1);                      // refills the buffer multiplied at st - 1
-    const char* base = smem + (st % NSTG) * STG;
-    const __bf16* Ah = (const __bf16*)base + (wm * C::TM * 16 + i16) * C::ROW;
-    const __bf16* Bb = (const __bf16*)base + (NPA * C::BM + wn * C::TN * 16 + i16) * C::ROW;
-    bf16x8 av[C::TM], bv[NPB][C::TN];
-#pragma unroll
-    for (int pb = 0; pb < NPB; ++pb)
-#pragma unroll
-      for (int y = 0; y < C::TN; ++y) bv[pb][y] = *(const bf16x8*)(Bb + (pb * C::BN + y * 16) * C::ROW + col);
-#pragma unroll
-    for (int pa = 0; pa < NPA; ++pa) {
-#pragma unroll
-      for (int x = 0; x < C::TM; ++x) av[x] = *(const bf16x8*)(Ah + (pa * C::BM + x * 16) * C::ROW + col);
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb) {
-        if (pa + pb >= NPROD_MAX) continue;
-#pragma unroll
-        for (int x = 0; x < C::TM; ++x)
-#pragma unroll
-          for (int y = 0; y < C::TN; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x], bv[pb][y], acc[x][y], 0, 0, 0);
-      }
-    }
-  }
-#undef ONMT_GEN_ISSUE
-  // every load (including the re-loads past the end) has landed before the output tiles reuse the buffers
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  __syncthreads();
-  // the BM x BN output as BN / 128 sub-tiles of BM x 128, each in the epilogue's layout, reduced at once
-  // (threads CE::NT s .. take sub-tile s, one partials tile of 128 columns); staging the
-  // sub-tiles one after the other through one buffer measured far slower
-  {
-    const int sub = (wn * C::TN * 16) / 128, c0 = (wn * C::TN * 16) % 128;
-    float* Ct = (float*)(smem + sub * CE::CT);
-#pragma unroll
-    for (int x = 0; x < C::TM; ++x)
-#pragma unroll
-      for (int y = 0; y < C::TN; ++y)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          Ct[(wm * C::TM * 16 + x * 16 + 4 * g + v) * CE::CROW + c0 + y * 16 + i16] = acc[x][y][v] + cb[y];
-  }
-  __syncthreads();
-  const int sub = tid / CE::NT, n0s = n0 + 128 * sub;
-  if (n0s < b.Np) gen_epilogue<CE, true>(smem + sub * CE::CT, p, a.M, m0, n0s, n0s / 128, tid % CE::NT);
-}
-
-
 // Vector-memory "no wait", LDS wait until nothing is outstanding (for LDS stores before a bare barrier).
 constexpr int kWaitLgkm0 = 15 | (7 << 4) | (0 << 8) | (3 << 14);
 
@@ -911,7 +477,7 @@ constexpr int kWaitLgkm0 = 15 | (7 << 4) | (0 << 8) | (3 << 14);
 // planes, with the operands moved straight into LDS: a stage of the A rows of every plane (fp32: one) and
 // the B rows is sliced into 1 KB pieces
 // (RPS tile rows each; lane l writes row l / (ROWB / 16), 16-byte slot l % (ROWB / 16)), kLstmStages stages
-// in flight, waits and bare barriers as in k_gemm_gen_lds. A rows come through the segment's row map
+// in flight, waits and bare barriers as in k_gen (gen.hip). A rows come through the segment's row map
 // (beam parents) and rows past M re-read row M - 1. The planes' columns past a segment's width are not
 // assumed to be zero: on a segment's last stage they are cleared in LDS before the products. Products,
 // their order and the output tile (WK partial planes) are those of gemm_tile, so the results are equal.
@@ -982,13 +548,13 @@ __device__ inline void gemm_tile_dma(const AOp& a, const BOp& b, int m0, int n0,
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
       if (sl_kind[i] == NPA)
-        dma16(rw, sb + sl_lds[i], boff[i] + kb);
+        dma16(rw, sb + sl_lds[i], boff[i] + kb, 0);
       else if (NPA == 1 || sl_kind[i] == 0)
-        dma16(rp[S][0], sb + sl_lds[i], aoff[S][i] + ka);
+        dma16(rp[S][0], sb + sl_lds[i], aoff[S][i] + ka, 0);
       else if (sl_kind[i] == 1)
-        dma16(rp[S][1], sb + sl_lds[i], aoff[S][i] + ka);
+        dma16(rp[S][1], sb + sl_lds[i], aoff[S][i] + ka, 0);
       else
-        dma16(rp[S][2], sb + sl_lds[i], aoff[S][i] + ka);
+        dma16(rp[S][2], sb + sl_lds[i], aoff[S][i] + ka, 0);
     }
   };
   auto issue = [&](int G) {
@@ -1092,8 +658,6 @@ static inline bool operands_fit(const AOp& a, const BOp& b) {
   return true;
 }
 
-int gen_tile_cols() { return TileGen32::BN; }
-
 // Kernels are specialised on the number of A segments, so that a stage's segment is known at compile
 // time wherever there is only one.
 template <class T, class C>
@@ -1171,17 +735,6 @@ static hipError_t launch_lstm2(LstmPair g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The generator's A operand is the attentional vector alone (one segment).
-template <class T, class C>
-static hipError_t launch_gen(const AOp& a, const BOp& b, const GenParams& p, hipStream_t st) {
-  int nm, nb;
-  grid_of<C>(a, b, nm, nb);
-  if (!operands_fit<T>(a, b) || a.nseg != 1) return hipErrorInvalidValue;
-  if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_gemm_gen<T, C, 1>), dim3(nb), dim3(C::NT), 0, st, a, b, p, nm, nb);
-  return hipGetLastError();
-}
-
 hipError_t gemm_store(int bf16, int shape, const AOp& a, const BOp& b, const StoreParams& p, hipStream_t st) {
   if (bf16) {
     if (shape == kShapeWide) return launch_store<__bf16, TileWide16>(a, b, p, st);
@@ -1241,29 +794,6 @@ hipError_t split_rows(const float* src, int ld_src, int rows, int cols, uint16_t
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(256), 0, st, src, ld_src, rows, cols, hi, lo, lo2,
                      ld_dst);
-  return hipGetLastError();
-}
-
-hipError_t gemm_gen(const AOp& a, const BOp& b, const GenParams& p, hipStream_t st) {
-  return gen_rows32(a.M) ? launch_gen<float, TileGen32h>(a, b, p, st) : launch_gen<float, TileGen32>(a, b, p, st);
-}
-
-hipError_t gemm_gen_split(const GenSplitA& a, const BOp& b, int b_planes, const GenParams& p, hipStream_t st) {
-  if (b_planes != 1 && b_planes != 3) return hipErrorInvalidValue;
-  const uint64_t lim = 1ull << 31;
-  // the K-blocked weights are read up to the operand's padded width: a.kpad == b.Kp
-  if (a.M < 1 || a.kpad % kSegK || a.kpad != b.Kp || a.ld < a.kpad || b.Np % 128 ||
-      (uint64_t)a.M * a.ld * 2 >= lim || (uint64_t)b.Np * b.Kp * 2 >= lim)
-    return hipErrorInvalidValue;
-  auto launch = [&](auto kernel, int BM, int BN, int threads) {
-    const int nm = (a.M + BM - 1) / BM;
-    const int nblocks = nm * ((b.Np + BN - 1) / BN);
-    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(threads), 0, st, a, b, p, nm, nblocks);
-  };
-  if (b_planes == 1)
-    launch(k_gemm_gen_lds<2, kGenWN, kGenStages, kGenPlanes, 1>, 64, 64 * kGenWN, 128 * kGenWN);
-  else
-    launch(k_gemm_gen_lds<2, kGen3WN, kGenStages, kPlanes, 3>, 64, 64 * kGen3WN, 128 * kGen3WN);
   return hipGetLastError();
 }
 

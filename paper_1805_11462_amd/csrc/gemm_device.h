@@ -1,0 +1,106 @@
+// Device-side pieces shared by the GEMM kernels (gemm.hip, thin.hip): tile numbering, bf16 term splits and
+// buffer-descriptor loads.
+#pragma once
+
+#include "common.h"
+#include "kernels.h"
+#include "split16.h"
+
+namespace onmt {
+
+// XCD-aware tile order: blocks are dealt round-robin to the 8 XCDs, so renumber them so that each
+// XCD receives a contiguous range of logical tiles; M varies fastest, so the M tiles that share a
+// weight tile run on the same XCD and share its L2.
+__device__ inline int xcd_remap(int bid, int nblocks) {
+  const int xcd = bid & 7, local = bid >> 3;
+  const int full = nblocks >> 3, rem = nblocks & 7;
+  return xcd * full + (xcd < rem ? xcd : rem) + local;
+}
+
+__device__ inline uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
+
+// Split 8 fp32 values into three bf16 terms p0 = RNE(x), p1 = RNE(x - p0), p2 = RNE(x - p0 - p1). Each
+// remainder is exact in fp32 (it drops leading bits of x), so p0 + p1 + p2 keeps about 24 significant
+// bits of x: the fp32 value itself, as the bf16 products see it. (Two terms keep ~16 bits, which over the
+// 120 steps of the 4 x 1000 decoder recurrence let a hypothesis's log-prob drift to the bf16 tolerance.)
+// The conversions are gfx950's packed fp32 -> bf16 (round to nearest even), two values per instruction.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ inline void split_bf16x8(const float4& a, const float4& b, uint4& p0, uint4& p1, uint4& p2) {
+  const f32x2_t x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
+  uint32_t t0[4], t1[4], t2[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bf16x2_t v0 = __builtin_convertvector(x[i], bf16x2_t);
+    const f32x2_t r1 = x[i] - __builtin_convertvector(v0, f32x2_t);
+    const bf16x2_t v1 = __builtin_convertvector(r1, bf16x2_t);
+    const f32x2_t r2 = r1 - __builtin_convertvector(v1, f32x2_t);
+    const bf16x2_t v2 = __builtin_convertvector(r2, bf16x2_t);
+    t0[i] = __builtin_bit_cast(uint32_t, v0);
+    t1[i] = __builtin_bit_cast(uint32_t, v1);
+    t2[i] = __builtin_bit_cast(uint32_t, v2);
+  }
+  p0 = make_uint4(t0[0], t0[1], t0[2], t0[3]);
+  p1 = make_uint4(t1[0], t1[1], t1[2], t1[3]);
+  p2 = make_uint4(t2[0], t2[1], t2[2], t2[3]);
+}
+
+__device__ inline void split_bf16(float x, uint16_t& p0, uint16_t& p1, uint16_t& p2) {
+  uint4 a, b, c;
+  split_bf16x8(make_float4(x, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f), a, b, c);
+  p0 = (uint16_t)(a.x & 0xffffu);
+  p1 = (uint16_t)(b.x & 0xffffu);
+  p2 = (uint16_t)(c.x & 0xffffu);
+}
+
+// Buffer resource descriptor (gfx9 family word 3). Loads through it return zeros past num_records, so
+// an invalid row is given an offset beyond every buffer instead of a branch.
+constexpr int kBufWord3 = 0x00020000;
+constexpr uint32_t kNoRow = 0x80000000u;      // byte offset past the end of any buffer (buffers < 2 GiB)
+
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, kBufWord3);
+}
+
+// The same with a wave-uniform byte offset on top, and an offset past the end of a buffer of up to 4 GiB.
+constexpr uint32_t kPastEnd = 0xfffffff0u;
+__device__ inline uint4 buf_load16s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+template <class A, class B>
+__device__ inline f32x4 mfma_f16(const A& a, const B& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+// LDS address of a byte in a __shared__ array, as the LDS-destination buffer loads take it. (Declared at
+// file scope: a local typedef of this pointer type inside a kernel template stops the host stub from
+// being emitted.)
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+__device__ inline lds_ptr_t lds_at(char* p) { return (lds_ptr_t)p; }
+
+__device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// One 16-byte-per-lane buffer load into LDS (lane l writes 16 bytes at lds + 16 l). (A function of its
+// own: called directly under control flow inside a kernel template, the builtin stops the host-side
+// launch stub from being emitted.)
+__device__ inline void dma16(__amdgpu_buffer_rsrc_t r, char* lds, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 16, voff, soff, 0, 0);
+}
+
+// Vector-memory wait until at most n loads of this wave are outstanding (expcnt and lgkmcnt left alone).
+constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | (((n >> 4) & 3) << 14); }
+
+// Four consecutive columns (k0 a multiple of 4) of row r of a two-term fp16 operand.
+__device__ inline void store_act4(uint16_t* dst, int r, int k0, int kblocks, const float (&v)[4]) {
+  uint16_t h[4], l[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split_act(v[j], h[j], l[j]);
+  uint16_t* d = dst + split16_at(r, k0, kblocks, 2);
+  *(uint2*)d = make_uint2(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16);
+  *(uint2*)(d + kFragElems) = make_uint2(l[0] | (uint32_t)l[1] << 16, l[2] | (uint32_t)l[3] << 16);
+}
+
+}  // namespace onmt

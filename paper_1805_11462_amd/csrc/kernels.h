@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "split16.h"
+
 namespace onmt {
 
 // K segments of GEMM operands are padded to multiples of this many elements; every tile's K stage
@@ -43,7 +45,8 @@ struct BOp {
 
 // Plain store epilogue: out[r, n] = act(acc + bias[n]) for n < ncols. act: 0 none, 1 tanh.
 // Optionally (hi != nullptr) the same values split into the bf16 term planes hi, lo, lo2 [rows, ld_hl]
-// for columns n < ncols_hl (columns past ncols hold act(0), zero for the tanh stores).
+// for columns n < ncols_hl (columns past ncols hold act(0), zero for the tanh stores), and (s16 != nullptr)
+// as a two-term fp16 operand whose row r0_16 + r holds columns n < 32 kb16.
 struct StoreParams {
   const float* bias;
   float* out;
@@ -55,6 +58,8 @@ struct StoreParams {
   int ld_hl;
   int ncols_hl;
   uint16_t* lo2;
+  uint16_t* s16;
+  int kb16, r0_16;
 };
 
 // LSTM cell epilogue over gate-blocked columns (groups of 32 = 4 gates x kUnitGroup = 8 units).
@@ -92,23 +97,24 @@ struct LstmPair {
   int nb[2];     // blocks (problem 0's rounded up to a multiple of 8)
 };
 
-// Generator epilogue: per (row, column tile) max, sum of exp and top-K; optional raw logits.
+// Generator epilogue: per (row, column tile) max and sum of exp, and the raw logits or per-tile top-K lists.
 struct GenParams {
-  const float* bias;
+  const float* bias;            // [ceil128(V)]
+  const int32_t* wexp;          // [ceil128(V)]: power of two that undoes a column's operand scales
   int V;
   int K;
   int ntiles;
   float* pmax;                  // [M, ntiles]
   float* psum;                  // [M, ntiles]
-  float* pval;                  // [M, ntiles, K]
-  int32_t* pid;                 // [M, ntiles, K]
+  float* pval;                  // optional [M, ntiles, K] top-K lists instead of logits: K = 1, or callers without
+  int32_t* pid;                 // room for logits (no filters then)
   float* logits;                // optional [M, ld_logits]
   int ld_logits;
   const int32_t* want;          // optional [M]: column whose logit is copied to want_logit[row]
   float* want_logit;
-  // hypothesis filters (optional): columns never entered into the top-K lists (max and sum of exp
-  // still cover every column): banned_bits[c >> 5] bit c & 31, and unk_id on rows whose UNK count has
-  // reached max_unk (max_unk < 0: no limit). pfmax (set when filtering) = each tile's largest allowed logit.
+  // hypothesis filters (with pfmax): columns that are no candidates: banned_bits[c >> 5] bit c & 31, and unk_id
+  // on rows whose UNK count has reached max_unk (max_unk < 0: no limit). pfmax = each tile's largest allowed
+  // logit; max and sum of exp still cover every column.
   const uint32_t* banned_bits;
   const int32_t* unk_cnt;       // [M]
   int unk_id, max_unk;
@@ -123,35 +129,9 @@ hipError_t gemm_store(int bf16, int shape, const AOp& a, const BOp& b, const Sto
 hipError_t gemm_lstm(int bf16, int shape, const AOp& a, const BOp& b, const LstmParams& p, hipStream_t st);
 // Two independent thin-shape LSTM GEMMs in one launch (segment counts 1+1, 1+2 or 2+2).
 hipError_t gemm_lstm2(int bf16, int shape, const LstmPair& g, hipStream_t st);
-// The generator with fp32 operands and the fp32 MFMA (fp32 models at the row counts gemm_gen_split_rows
-// leaves to it).
-hipError_t gemm_gen(const AOp& a, const BOp& b, const GenParams& p, hipStream_t st);
-
-
-// bf16 generator operand already split into its bf16 term planes (A = hi + lo + lo2), row-major [M, ld]
-// each with zeros in the K padding (columns width .. kpad - 1).
-struct GenSplitA {
-  const uint16_t* hi;
-  const uint16_t* lo;
-  int M;
-  int ld;      // elements per row, >= kpad
-  int kpad;    // multiple of kSegK
-  const uint16_t* lo2;
-};
-// The generator on a pre-split operand, operands moved straight into LDS, the weights given as b_planes
-// bf16 term planes (plane p of the K-blocked [Np, Kp] matrix at element offset p * Np * Kp).
-// b_planes = 1 (bf16 weights): the first two term planes of A are multiplied (A ~ hi + lo; lo2 is not
-// read), since the logits do not feed back into the decoder. b_planes = 3 (fp32 weights as three bf16
-// terms): the six term products whose order of magnitude is at least 2^-16 of the leading one
-// (hi.hi, hi.lo, lo.hi, lo.lo, hi.lo2, lo2.hi), accumulated in fp32: the six-product bf16 scheme of
-// Henry, Tang and Heinecke (ARITH 2019), whose dropped products lie below one fp32 rounding.
-// Its weights are K-blocked: element (n, k) of the [Np, Kp] matrix sits at (k / kGenKBlock) * Np *
-// kGenKBlock + n * kGenKBlock + k % kGenKBlock, so that one K stage of a column tile is one contiguous block
-// (with row-major weights each load instruction touched 16 rows 2 KB apart for 64 bytes each).
-constexpr int kGenKBlock = 32;
-hipError_t gemm_gen_split(const GenSplitA& a, const BOp& b, int b_planes, const GenParams& p, hipStream_t st);
-// fp32 models: whether M rows take the three-plane generator (else the fp32 MFMA kernel, gemm_gen).
-bool gemm_gen_split_rows(int M);
+// The generator: a two-term operand of M = a.rows rows against the vocabulary's weights (w.rows = ceil128(V)
+// rows of w_terms terms).
+hipError_t gemm_gen(const Split16& a, const Split16& w, int w_terms, const GenParams& p, hipStream_t st);
 int gen_tile_cols();
 
 // Attention coverage of the hypotheses (optional): out[r, s] = in[parent[r], s] + a[r, s] for the real
@@ -176,8 +156,26 @@ hipError_t attention(const float* q, int ld_q, const float* keys, const float* v
                      float* attn, const AttnExtra& ex, hipStream_t st);
 size_t attention_lds_bytes(int S_max, int H, int K);
 
-hipError_t lse_topk_merge(const float* pmax, const float* psum, const float* pval, const int32_t* pid, int M,
-                          int ntiles, int K, float* out_val, int32_t* out_id, float* out_lse, hipStream_t st);
+// Generator partials of one decoder step (per row and column tile), as written by gemm_gen: the top-K comes from
+// the lists (pval, pid) or, where those are null, from the logits.
+struct GenPartials {
+  const float* pmax;
+  const float* psum;
+  const float* pval;
+  const int32_t* pid;
+  int ntiles;
+  const float* logits;
+  int ld_logits, V;
+  // filters (logits only), as in GenParams
+  const float* pfmax;
+  const uint32_t* banned_bits;
+  const int32_t* unk_cnt;
+  int unk_id, max_unk;
+};
+
+// K = 0: the logsumexp alone.
+hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, int32_t* out_id, float* out_lse,
+                          hipStream_t st);
 // Teacher-forced scoring of all steps: rows r = t * B + b of the generator partials; logp[b * ld + t] =
 // want_logit[r] - logsumexp(r) for t < len[b] (0 otherwise, t < steps); nll[b] = -sum_t logp[b, t] in fp64.
 hipError_t score_rows(const float* pmax, const float* psum, int ntiles, const float* want_logit, const int32_t* len,
@@ -211,16 +209,6 @@ struct BeamParams {
   int32_t* tr_slot;             // optional trace [T_max, B, K]
   int32_t* tr_tok;
   double* tr_cand;
-};
-
-// Generator partials of one decoder step (per row and column tile), as written by gemm_gen.
-struct GenPartials {
-  const float* pmax;
-  const float* psum;
-  const float* pval;
-  const int32_t* pid;
-  int ntiles;
-  const float* pfmax;           // optional: per-tile largest allowed logit (filters active)
 };
 
 hipError_t beam_init(const BeamParams& p, int bos, hipStream_t st);

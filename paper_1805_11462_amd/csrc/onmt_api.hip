@@ -88,14 +88,12 @@ struct Dims {
   bool bf16;
   int esz;             // operand element size
   int attn;            // ONMT_ATTN_GENERAL / _DOT / _CONCAT
-  // The generator's weights packed K-blocked as gwp bf16 term planes (bf16 models: 1, their exact values;
-  // fp32 models: 3, each fp32 value as the sum of three bf16 terms, multiplied in six term products),
-  // read with the attentional vector's term planes (split by the W_c epilogue). fp32 models also keep
-  // the fp32 matrix for the row counts where the fp32 MFMA kernel is faster (gemm_gen_split_rows).
-  int gwp;
+  // fp16 terms per weight of the two-term products (split16.h): bf16 weights fit one, fp32 weights take two
+  int wterms;
   // Every K segment of a GEMM operand is padded to a multiple of kSegK so that no K stage of any tile
   // shape straddles two segments.
   int pad(int w) const { return ceil_to(w, kSegK); }
+  int kb(int w) const { return ceil_to(w, kFragK) / kFragK; }     // 32-column blocks of a two-term operand
 };
 
 bool dims_of(const onmt_config* c, Dims* d) {
@@ -113,7 +111,7 @@ bool dims_of(const onmt_config* c, Dims* d) {
   d->bf16 = c->wdtype == 1;
   d->esz = d->bf16 ? 2 : 4;
   d->attn = c->attn_type;
-  d->gwp = d->bf16 ? 1 : 3;
+  d->wterms = d->bf16 ? 1 : 2;
   return true;
 }
 
@@ -215,8 +213,10 @@ struct onmt_model {
   Packed W_a;                              // memory side of the score: general W_a, concat's memory columns
   Packed W_q;                              // concat: the query columns of W_a
   const float* v_a = nullptr;              // concat [H]
-  Packed W_c, W_s;
-  Packed W_s32;        // fp32 models: the generator's fp32 weights, row-major
+  Packed W_c;
+  size_t W_s_off = 0;
+  Split16 W_s{};                           // the generator's weights: ceil128(Vt) rows of wterms fp16 terms
+  const int32_t* W_s_exp = nullptr;        // power of two that undoes a vocabulary column's operand scales
   const float* b_s = nullptr;
   // decoder layer 0's input-projection rows for every target token, E_tgt[v] W_e^T in the packed (gate-
   // blocked) column order, fp32 [Vt, 4 H_pad]; computed on the device when the model is created
@@ -292,15 +292,13 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
   Packed wq = d.attn == ONMT_ATTN_CONCAT ? mat(ceil_to(d.H, 128), d.pad(d.H)) : Packed{};
   const size_t va = d.attn == ONMT_ATTN_CONCAT ? vec(d.H) : 0;
   Packed wc = mat(ceil_to(d.H, 128), d.pad(d.Hm) + d.pad(d.H));
-  Packed ws;         // K-blocked bf16 planes, each read through its own descriptor
   cv.off = align_up(cv.off);
-  ws.off = cv.off;
-  ws.Np = ceil_to(d.Vt, 128);
-  ws.Kp = d.pad(d.H);
-  const uint64_t plane = (uint64_t)ws.Np * ws.Kp * 2;
-  cv.off += plane * d.gwp;
-  if (mats) mats->push_back(plane);
-  Packed ws32 = d.bf16 ? Packed{} : mat(ceil_to(d.Vt, 128), d.pad(d.H));
+  const size_t ws_off = cv.off;
+  const Split16 ws{nullptr, ceil_to(d.Vt, 128), d.kb(d.H)};
+  const uint64_t ws_bytes = split16_bytes(ws.rows, ws.kblocks, d.wterms);
+  cv.off += ws_bytes;
+  if (mats) mats->push_back((uint64_t)ws.rows * d.pad(d.H) * d.esz);   // the limit is set on 128-column padding
+  const size_t wse = vec(ws.rows);
   size_t bs = vec(ceil_to(d.Vt, 128));
   const size_t image = align_up(cv.off);
   const size_t eg = vec((size_t)d.Vt * 4 * d.H_pad);
@@ -325,8 +323,10 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
       m->v_a = (const float*)(base + va);
     }
     m->W_c = fix(wc);
-    m->W_s = fix(ws);
-    if (!d.bf16) m->W_s32 = fix(ws32);
+    m->W_s_off = ws_off;
+    m->W_s = ws;
+    m->W_s.base = base + ws_off;
+    m->W_s_exp = (const int32_t*)(base + wse);
     m->b_s = (const float*)(base + bs);
     m->emb_gates = (float*)(base + eg);
     m->image_bytes = image;
@@ -516,22 +516,18 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
       pack_row(img, m->W_c, r, d.pad(d.Hm), Wc + (size_t)r * (d.Hm + d.H), d.Hm, d.H);
     }
     const float* Ws = host_weights[wi++];
-    {   // K-blocked bf16 term planes for the pre-split generator (see gemm_gen_split)
-      const size_t Np = (size_t)m->W_s.Np, plane = Np * m->W_s.Kp;
-      uint16_t* o = (uint16_t*)(img.buf.data() + m->W_s.off);
-      for (int r = 0; r < d.Vt; ++r)
-        for (int k = 0; k < d.H; ++k) {
-          const size_t at = (size_t)(k / kGenKBlock) * Np * kGenKBlock + (size_t)r * kGenKBlock + k % kGenKBlock;
-          float x = Ws[(size_t)r * d.H + k];
-          for (int p = 0; p < d.gwp; ++p) {   // RNE of the value, then of each remainder
-            const uint16_t t = f32_to_bf16_bits(x);
-            o[p * plane + at] = t;
-            x -= host_bf16_to_f32(t);
-          }
-        }
+    {
+      uint16_t* o = (uint16_t*)(img.buf.data() + m->W_s_off);
+      int32_t* ex = (int32_t*)(img.buf.data() + off_of(m->W_s_exp));
+      std::vector<float> row(d.H);
+      for (int r = 0; r < d.Vt; ++r) {
+        const float* src = Ws + (size_t)r * d.H;
+        for (int k = 0; k < d.H; ++k) row[k] = d.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(src[k])) : src[k];
+        const int e = host_row_exp(row.data(), d.H);
+        ex[r] = -(kActExp + e);
+        host_pack_row(o, r, 0, m->W_s.kblocks, d.wterms, row.data(), d.H, e);
+      }
     }
-    if (!d.bf16)
-      for (int r = 0; r < d.Vt; ++r) pack_row(img, m->W_s32, r, 0, Ws + (size_t)r * d.H, 0, d.H);
     const float* bs = host_weights[wi++];
     const size_t bo = off_of(m->b_s);
     for (int r = 0; r < d.Vt; ++r) img.putf(bo, r, bs[r]);
@@ -624,6 +620,7 @@ struct State {
   float* h;      // [L, N, H]
   float* c;
   float* feed;   // [N, H]
+  uint16_t* feed16;   // feed as a two-term fp16 operand (the generator's)
   // bf16 models: h and feed as their kPlanes bf16 term planes, [L, N, pad(H)] and [N, pad(H)] each (the
   // operands of the decoder's products, split once by their producers)
   uint16_t* h_hi;
@@ -645,9 +642,10 @@ size_t state_layout(const Dims& d, int N, char* base, State* s) {
   t.h_hi = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
   t.h_lo = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
   t.h_lo2 = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
-  t.feed_hi = c.take<uint16_t>(pl);
-  t.feed_lo = c.take<uint16_t>(pl);
-  t.feed_lo2 = c.take<uint16_t>(pl);
+  t.feed_hi = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
+  t.feed_lo = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
+  t.feed_lo2 = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
+  t.feed16 = c.take<uint16_t>(split16_bytes(N, d.kb(d.H), 2) / 2);
   if (s) *s = t;
   return align_up(c.off);
 }
@@ -658,19 +656,19 @@ struct StepWs {
   float* qproj;    // [N, H] concat: query columns of W_a times the decoder output
   float* pmax;     // [N, ntiles]
   float* psum;
-  float* pval;     // [N, ntiles, K]
+  float* logits;   // [N, ld_logits] (null: lists instead)
+  float* pval;     // [N, ntiles, K] top-K lists: K = 1, and the allocation-free step, whose scratch cannot hold logits
   int32_t* pid;
-  float* tk_val;   // [N, K]
-  int32_t* tk_id;
   float* lse;      // [N]
   int32_t* align;  // [N] attention argmax
   float* pfmax;    // [N, ntiles] largest allowed logit per tile (hypothesis filters)
   int32_t* tok_s;  // [N] previous tokens and parents checked on the device (device validation)
   int32_t* par_s;
   int ntiles;
+  int ld_logits;
 };
 
-size_t step_layout(const Dims& d, int B, int S, int K, char* base, StepWs* w) {
+size_t step_layout(const Dims& d, int B, int S, int K, char* base, StepWs* w, bool lists = false) {
   Carver c;
   c.base = base;
   StepWs t;
@@ -681,10 +679,11 @@ size_t step_layout(const Dims& d, int B, int S, int K, char* base, StepWs* w) {
   t.qproj = d.attn == ONMT_ATTN_CONCAT ? c.take<float>(N * d.H) : nullptr;
   t.pmax = c.take<float>(N * t.ntiles);
   t.psum = c.take<float>(N * t.ntiles);
-  t.pval = c.take<float>(N * t.ntiles * K);
-  t.pid = c.take<int32_t>(N * t.ntiles * K);
-  t.tk_val = c.take<float>(N * K);
-  t.tk_id = c.take<int32_t>(N * K);
+  lists = lists || K == 1;
+  t.ld_logits = t.ntiles * gen_tile_cols();
+  t.logits = lists ? nullptr : c.take<float>(N * t.ld_logits);
+  t.pval = lists ? c.take<float>(N * t.ntiles * K) : nullptr;
+  t.pid = lists ? c.take<int32_t>(N * t.ntiles * K) : nullptr;
   t.lse = c.take<float>(N);
   t.align = c.take<int32_t>(N);
   t.pfmax = c.take<float>(N * t.ntiles);
@@ -757,6 +756,7 @@ struct ScoreWs {
   uint16_t* feeds_hi;  // bf16 models: [T, B, pad(H)] each, the same as bf16 term planes
   uint16_t* feeds_lo;
   uint16_t* feeds_lo2;
+  uint16_t* feeds16;   // the same as a two-term fp16 operand of T * B rows
   float* gpmax;        // [T * B, ntiles] generator partials of all steps
   float* gpsum;
   float* want_logit;   // [T, B]
@@ -775,16 +775,17 @@ size_t score_layout(const Dims& d, int B, int S, int T, char* base, ScoreWs* w) 
     char* p = c.take<char>(sb);
     state_layout(d, B, p, &t.st[i]);
   }
-  const size_t pb = step_layout(d, B, S, 1, nullptr, nullptr);
+  const size_t pb = step_layout(d, B, S, 1, nullptr, nullptr, true);   // no per-step logits in scoring
   char* p = c.take<char>(pb);
-  step_layout(d, B, S, 1, p, &t.step);
+  step_layout(d, B, S, 1, p, &t.step, true);
   t.in_tok = c.take<int32_t>((size_t)T * B);
   t.want = c.take<int32_t>((size_t)T * B);
   t.tlen = c.take<int32_t>(B);
   t.feeds = c.take<float>((size_t)T * B * d.H);
-  t.feeds_hi = c.take<uint16_t>((size_t)T * B * d.pad(d.H));
-  t.feeds_lo = c.take<uint16_t>((size_t)T * B * d.pad(d.H));
-  t.feeds_lo2 = c.take<uint16_t>((size_t)T * B * d.pad(d.H));
+  t.feeds_hi = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
+  t.feeds_lo = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
+  t.feeds_lo2 = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
+  t.feeds16 = c.take<uint16_t>(split16_bytes((size_t)T * B, d.kb(d.H), 2) / 2);
   t.gpmax = c.take<float>((size_t)T * B * t.step.ntiles);
   t.gpsum = c.take<float>((size_t)T * B * t.step.ntiles);
   t.want_logit = c.take<float>((size_t)T * B);
@@ -1084,6 +1085,25 @@ void time_collect(onmt_model* m) {
   m->ev_used = 0;
 }
 
+// What the merge of a step's generator launch reads.
+GenPartials gen_partials(const GenParams& gp) {
+  GenPartials q{};
+  q.pmax = gp.pmax;
+  q.psum = gp.psum;
+  q.pval = gp.pval;
+  q.pid = gp.pid;
+  q.ntiles = gp.ntiles;
+  q.logits = gp.logits;
+  q.ld_logits = gp.ld_logits;
+  q.V = gp.V;
+  q.pfmax = gp.pfmax;
+  q.banned_bits = gp.banned_bits;
+  q.unk_cnt = gp.unk_cnt;
+  q.unk_id = gp.unk_id;
+  q.max_unk = gp.max_unk;
+  return q;
+}
+
 // One decoder step on validated inputs (Section 2; Figure 1(a); items (a)-(c); Section 4.2 attention).
 // mode 0: logp [N, V] full log-softmax; mode 1: top-K (logp [N, K], ids [N, K]); mode 2 (beam search):
 // stop after the generator, leaving its per-tile partials in the step workspace for the beam step;
@@ -1091,7 +1111,10 @@ void time_collect(onmt_model* m) {
 // all steps at once.
 // Optional work of a decoder step beyond the log-distribution.
 struct StepExtras {
-  // bf16 models: where the attentional vector's term planes go (default: the output state's)
+  // where the attentional vector's two-term operand goes, from which row on (default: the output state's)
+  uint16_t* feed16 = nullptr;
+  int feed16_r0 = 0;
+  // bf16 models: where its term planes go (default: the output state's)
   uint16_t* feed_hi = nullptr;
   uint16_t* feed_lo = nullptr;
   uint16_t* feed_lo2 = nullptr;
@@ -1186,7 +1209,10 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
     a.seg[0] = seg(sw.ctx, nullptr, N, d.Hm, d.Hm, d.pad(d.Hm), 0);
     a.seg[1] = seg(q, nullptr, N, d.H, d.H, d.pad(d.H), 0);
     StoreParams sp{nullptr, out.feed, d.H, d.H, 1};
-    {                        // the generator's operand, split once here instead of in every column tile
+    sp.s16 = ex.feed16 ? ex.feed16 : out.feed16;   // the generator's operand, split once here
+    sp.r0_16 = ex.feed16_r0;
+    sp.kb16 = d.kb(d.H);
+    if (d.bf16) {
       sp.hi = ex.feed_hi ? ex.feed_hi : out.feed_hi;
       sp.lo = ex.feed_lo ? ex.feed_lo : out.feed_lo;
       sp.lo2 = ex.feed_lo2 ? ex.feed_lo2 : out.feed_lo2;
@@ -1197,22 +1223,20 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
     if (timing) time_end(m, st, ONMT_KERNEL_OUTPUT);
   }
   if (mode == 3) return ONMT_OK;
+  GenPartials part{};
   {
-    AOp a{};
-    a.M = N;
-    a.nseg = 1;
-    a.seg[0] = seg(out.feed, nullptr, N, d.H, d.H, d.pad(d.H), 0);
     GenParams gp{};
     gp.bias = m->b_s;
+    gp.wexp = m->W_s_exp;
     gp.V = d.Vt;
     gp.K = K;
     gp.ntiles = sw.ntiles;
     gp.pmax = sw.pmax;
     gp.psum = sw.psum;
-    gp.pval = sw.pval;
+    gp.logits = mode == 0 ? logp : sw.logits;
+    gp.ld_logits = mode == 0 ? d.Vt : sw.ld_logits;
+    gp.pval = mode == 0 ? nullptr : sw.pval;
     gp.pid = sw.pid;
-    gp.logits = mode == 0 ? logp : nullptr;
-    gp.ld_logits = d.Vt;
     gp.want = ex.want;
     gp.want_logit = ex.want_logit;
     gp.banned_bits = ex.banned_bits;
@@ -1220,21 +1244,18 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
     gp.unk_id = ex.unk_id;
     gp.max_unk = ex.max_unk;
     gp.pfmax = ex.pfmax;
+    part = gen_partials(gp);
     if (timing) time_begin(m, st);
-    if (d.bf16 || gemm_gen_split_rows(N))
-      HIP_TRY(gemm_gen_split(GenSplitA{out.feed_hi, out.feed_lo, N, d.pad(d.H), d.pad(d.H), out.feed_lo2},
-                             bop(m->W_s), d.gwp, gp, st));
-    else
-      HIP_TRY(gemm_gen(a, bop(m->W_s32), gp, st));
+    HIP_TRY(gemm_gen(Split16{out.feed16, N, d.kb(d.H)}, m->W_s, d.wterms, gp, st));
     if (timing) time_end(m, st);
   }
   if (mode == 2) return ONMT_OK;
   float* lse_out = lse ? lse : sw.lse;
   if (mode == 0) {
-    HIP_TRY(lse_topk_merge(sw.pmax, sw.psum, sw.pval, sw.pid, N, sw.ntiles, K, sw.tk_val, sw.tk_id, lse_out, st));
+    HIP_TRY(lse_topk_merge(part, N, 0, nullptr, nullptr, lse_out, st));
     HIP_TRY(subtract_rows(logp, d.Vt, lse_out, N, d.Vt, st));
   } else {
-    HIP_TRY(lse_topk_merge(sw.pmax, sw.psum, sw.pval, sw.pid, N, sw.ntiles, K, logp, ids, lse_out, st));
+    HIP_TRY(lse_topk_merge(part, N, K, logp, ids, lse_out, st));
   }
   return ONMT_OK;
 }
@@ -1359,7 +1380,7 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
   if ((rc = check_ws_limits(m->d, B, S, K, 0))) return rc;
   if (mode != 0 && mode != 1) return fail(ONMT_EINVAL, "mode must be 0 (full) or 1 (top-K)");
   if (mode == 1 && !ids) return fail(ONMT_EINVAL, "ids is NULL in top-K mode");
-  const size_t need = step_layout(m->d, B, S, K, nullptr, nullptr);
+  const size_t need = step_layout(m->d, B, S, K, nullptr, nullptr, true);
   if (need > ONMT_NOALLOC_SCRATCH_BYTES)
     return fail(ONMT_EUNSUPPORTED, "this step needs %zu bytes of scratch, more than the %u of the allocation-free call",
                 need, (unsigned)ONMT_NOALLOC_SCRATCH_BYTES);
@@ -1368,7 +1389,7 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
   hipStream_t st = (hipStream_t)stream;
   const int N = B * K;
   StepWs sw;
-  step_layout(m->d, B, S, K, (char*)sp, &sw);
+  step_layout(m->d, B, S, K, (char*)sp, &sw, true);
   HIP_TRY(sanitize_step(prev_tok, parent, N, m->cfg.tgt_vocab, sw.tok_s, sw.par_s, m->err_host, st));
   EncWs w;
   enc_layout(m->d, B, S, (char*)enc_ws, &w);
@@ -1440,7 +1461,15 @@ int onmt_beam_search(onmt_model* m, const int32_t* src, const int32_t* len, int 
   bp.tr_tok = trace ? trace->tok : nullptr;
   bp.tr_cand = trace ? trace->cand : nullptr;
 
-  GenPartials gp{w.step.pmax, w.step.psum, w.step.pval, w.step.pid, w.step.ntiles};
+  GenPartials gp{};
+  gp.pmax = w.step.pmax;
+  gp.psum = w.step.psum;
+  gp.ntiles = w.step.ntiles;
+  gp.logits = w.step.logits;
+  gp.pval = w.step.pval;
+  gp.pid = w.step.pid;
+  gp.ld_logits = w.step.ld_logits;
+  gp.V = m->cfg.tgt_vocab;
   rc = encode_compute(m, src, lsrc, B, S, mx, w.enc, st);
   if (rc) return rc;
   rc = decode_init_compute(m, w.enc, B, K, w.st[0], st);
@@ -1466,6 +1495,10 @@ int onmt_beam_search(onmt_model* m, const int32_t* src, const int32_t* len, int 
     ex.max_unk = prm->max_unk;
     ex.pfmax = w.step.pfmax;
     gp.pfmax = w.step.pfmax;
+    gp.banned_bits = ex.banned_bits;
+    gp.unk_cnt = ex.unk_cnt;
+    gp.unk_id = ex.unk_id;
+    gp.max_unk = ex.max_unk;
   }
   HIP_TRY(beam_init(bp, m->cfg.bos_id, st));
   if (coverage) HIP_TRY(fill_f32(w.cov[0], (size_t)B * K * S, 0.f, st));
@@ -1588,7 +1621,9 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
     }
     out.feed = w.feeds + (size_t)t * B * d.H;
     StepExtras ex;
-    {
+    ex.feed16 = w.feeds16;
+    ex.feed16_r0 = t * B;
+    if (d.bf16) {
       ex.feed_hi = w.feeds_hi + (size_t)t * B * d.pad(d.H);
       ex.feed_lo = w.feeds_lo + (size_t)t * B * d.pad(d.H);
       ex.feed_lo2 = w.feeds_lo2 + (size_t)t * B * d.pad(d.H);
@@ -1601,12 +1636,9 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
   // one generator pass over the steps * B rows: per-tile max and sum of exponentials, and the target's logit
   {
     const int M = steps * B;
-    AOp a{};
-    a.M = M;
-    a.nseg = 1;
-    a.seg[0] = seg(w.feeds, nullptr, M, d.H, d.H, d.pad(d.H), 0);
     GenParams gp{};
     gp.bias = m->b_s;
+    gp.wexp = m->W_s_exp;
     gp.V = d.Vt;
     gp.K = 0;
     gp.ntiles = w.step.ntiles;
@@ -1615,11 +1647,7 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
     gp.want = w.want;
     gp.want_logit = w.want_logit;
     time_begin(m, st);
-    if (d.bf16 || gemm_gen_split_rows(M))
-      HIP_TRY(gemm_gen_split(GenSplitA{w.feeds_hi, w.feeds_lo, M, d.pad(d.H), d.pad(d.H), w.feeds_lo2}, bop(m->W_s),
-                             d.gwp, gp, st));
-    else
-      HIP_TRY(gemm_gen(a, bop(m->W_s32), gp, st));
+    HIP_TRY(gemm_gen(Split16{w.feeds16, M, d.kb(d.H)}, m->W_s, d.wterms, gp, st));
     time_end(m, st);
     HIP_TRY(score_rows(w.gpmax, w.gpsum, w.step.ntiles, w.want_logit, w.tlen, B, steps, out_logp, T, w.nll, st));
   }
