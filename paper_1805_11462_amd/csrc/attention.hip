@@ -19,7 +19,9 @@
 // Keys and memory are each read once per step, and all reductions run in a fixed order.
 
 #include "common.h"
+#include "gemm_device.h"
 #include "kernels.h"
+#include "split16.h"
 
 namespace onmt {
 
@@ -124,7 +126,7 @@ template <int KMAX, int PL>
 __global__ __launch_bounds__(kCtxThreads) void k_attn_context(const float* __restrict__ e,
                                                               const float* __restrict__ mem,
                                                               const int32_t* __restrict__ lens, int S_max, int Hm,
-                                                              int K, int G, float* __restrict__ ctx,
+                                                              int K, int G, uint16_t* __restrict__ ctx16,
                                                               float* __restrict__ attn, Coverage cov,
                                                               int32_t* __restrict__ align) {
   extern __shared__ __attribute__((aligned(16))) float as[];      // [K][S_max] attention weights
@@ -262,10 +264,15 @@ __global__ __launch_bounds__(kCtxThreads) void k_attn_context(const float* __res
       }
     }
   }
-  if (pl == 0 && col_ok) {
+  // written as the two-term operand the attentional output reads, zeros up to its last block's end
+  const int kb = (Hm + kFragK - 1) / kFragK;
+  if (pl == 0 && 4 * c < kb * kFragK) {
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
-      if (k < K) *(float4*)(ctx + (size_t)(r0 + k) * Hm + 4 * c) = acc[k];
+      if (k < K) {
+        const float v[4] = {acc[k].x, acc[k].y, acc[k].z, acc[k].w};
+        store_act4(ctx16, r0 + k, 4 * c, kb, v);
+      }
   }
 }
 
@@ -286,7 +293,7 @@ static int ctx_lanes(int B, int Hm4) {
 
 template <int KMAX>
 static void launch_context(int pl, dim3 grid, size_t lds, hipStream_t st, const float* e, const float* mem,
-                           const int32_t* lens, int S_max, int Hm, int K, int G, float* ctx, float* attn,
+                           const int32_t* lens, int S_max, int Hm, int K, int G, uint16_t* ctx, float* attn,
                            const Coverage& cov, int32_t* align) {
   const dim3 block(kCtxThreads);
   switch (pl) {
@@ -316,7 +323,7 @@ static void launch_scores(int K, dim3 grid, size_t lds, hipStream_t st, const fl
 }
 
 hipError_t attention(const float* q, int ld_q, const float* keys, const float* v_a, const float* mem,
-                     const int32_t* lens, int B, int S_max, int H, int Hm, int K, float* scores, float* ctx,
+                     const int32_t* lens, int B, int S_max, int H, int Hm, int K, float* scores, uint16_t* ctx,
                      float* attn, const AttnExtra& ex, hipStream_t st) {
   const Coverage cv = ex.cov ? *ex.cov : Coverage{};
   if (H / 4 > kScoreLanes * kScoreChunks || H % 4 || Hm % 4 || K < 1 || K > kMaxBeam) return hipErrorInvalidValue;
@@ -331,7 +338,7 @@ hipError_t attention(const float* q, int ld_q, const float* keys, const float* v
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
 
-  const int Hm4 = Hm / 4;
+  const int Hm4 = (Hm + kFragK - 1) / kFragK * (kFragK / 4);     // columns written, in fours
   const int pl = ctx_lanes(B, Hm4);
   const int cw = kCtxThreads / pl;
   const int G = (Hm4 + cw - 1) / cw;

@@ -630,26 +630,6 @@ __global__ void k_sanitize_src(const int32_t* __restrict__ src, const int32_t* _
   }
 }
 
-__global__ void k_sanitize_step(const int32_t* __restrict__ tok, const int32_t* __restrict__ parent, int N, int V,
-                                int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out, int32_t* err) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < N; r += gridDim.x * blockDim.x) {
-    int t = tok[r];
-    if (t < 0 || t >= V) {
-      *err = kErrToken;
-      t = 0;
-    }
-    tok_out[r] = t;
-    if (par_out) {
-      int p = parent[r];
-      if (p < 0 || p >= N) {
-        *err = kErrParent;
-        p = r;
-      }
-      par_out[r] = p;
-    }
-  }
-}
-
 hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
                         int32_t* rowmap, int32_t* err, hipStream_t st) {
   const size_t n = (size_t)B * S;
@@ -660,31 +640,7 @@ hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, in
   return hipGetLastError();
 }
 
-hipError_t sanitize_step(const int32_t* tok, const int32_t* parent, int N, int V, int32_t* tok_out, int32_t* par_out,
-                         int32_t* err, hipStream_t st) {
-  int blocks = (N + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_sanitize_step, dim3(blocks), dim3(256), 0, st, tok, parent, N, V, tok_out,
-                     parent ? par_out : nullptr, err);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ layout helpers
-__global__ void k_replicate_rows(const float* src, int ld_src, int rows, int K, float* dst, int ld_dst, int ncols) {
-  const int r = blockIdx.y;                 // destination row
-  const float* s = src + (size_t)(r / K) * ld_src;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncols; c += gridDim.x * blockDim.x)
-    dst[(size_t)r * ld_dst + c] = s[c];
-}
-
-hipError_t replicate_rows(const float* src, int ld_src, int rows, int K, float* dst, int ld_dst, int ncols,
-                          hipStream_t st) {
-  if (rows * K == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_replicate_rows, dim3((ncols + 255) / 256, rows * K), dim3(256), 0, st, src, ld_src, rows, K,
-                     dst, ld_dst, ncols);
-  return hipGetLastError();
-}
-
 __global__ void k_fill(float* dst, size_t n, float v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
     dst[i] = v;

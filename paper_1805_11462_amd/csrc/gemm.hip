@@ -773,28 +773,4 @@ hipError_t gemm_lstm2(int bf16, int shape, const LstmPair& g, hipStream_t st) {
   return shape == kShapeMid ? lstm2_dispatch<__bf16, TileMid16>(g, st) : lstm2_dispatch<__bf16, TileThin16>(g, st);
 }
 
-__global__ void k_split_rows(const float* __restrict__ src, int ld_src, int rows, int cols, uint16_t* __restrict__ hi,
-                             uint16_t* __restrict__ lo, uint16_t* __restrict__ lo2, int ld_dst) {
-  const size_t n = (size_t)rows * ld_dst;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int r = (int)(i / ld_dst), c = (int)(i % ld_dst);
-    uint16_t t0 = 0, t1 = 0, t2 = 0;
-    if (c < cols) split_bf16(src[(size_t)r * ld_src + c], t0, t1, t2);
-    hi[i] = t0;
-    lo[i] = t1;
-    lo2[i] = t2;
-  }
-}
-
-hipError_t split_rows(const float* src, int ld_src, int rows, int cols, uint16_t* hi, uint16_t* lo, uint16_t* lo2,
-                      int ld_dst, hipStream_t st) {
-  const size_t n = (size_t)rows * ld_dst;
-  if (n == 0) return hipSuccess;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_split_rows, dim3((unsigned)blocks), dim3(256), 0, st, src, ld_src, rows, cols, hi, lo, lo2,
-                     ld_dst);
-  return hipGetLastError();
-}
-
 }  // namespace onmt

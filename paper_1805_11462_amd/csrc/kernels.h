@@ -85,6 +85,33 @@ struct LstmParams {
   int ld_y, y_S, y_s, y_col0;
   const int32_t* lens;          // optional: GEMM row b is active iff y_s < lens[b]
   int H;                        // real units
+  uint16_t* h16;                // optional two-term copy of h_out (kb16 blocks of 32 columns)
+  int kb16;
+  uint16_t* y16;                // optional two-term copy of y_out
+  int y_kb16;
+};
+
+// Operands of the few-row GEMMs: A rows in up to two two-term segments (row r of segment s is row
+// row0 + (idx ? idx[r] : r) of its buffer of `bytes` bytes), K one after the other; W the weights' rows in fragment
+// blocks, of which K blocks kb0 .. are multiplied, with the power of two that undoes each column's scales.
+struct ThinSeg {
+  const void* base;
+  const int32_t* idx;
+  int row0;
+  int kblocks;
+  uint32_t bytes;
+};
+struct ThinA {
+  ThinSeg seg[2];
+  int nseg;
+  int M;
+};
+struct ThinW {
+  const void* base;
+  const int32_t* wexp;
+  int rows;
+  int kblocks;
+  int kb0;
 };
 
 // Two LSTM GEMM problems for one launch (nm/nt/nb are filled in by the launcher).
@@ -121,6 +148,28 @@ struct GenParams {
   float* pfmax;                 // [M, ntiles]
 };
 
+// w_terms: fp16 terms per weight (1 or 2). thin_store: StoreParams without bf16 term planes.
+hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st);
+hipError_t thin_store(int w_terms, const ThinA& a, const ThinW& w, const StoreParams& p, hipStream_t st);
+
+// A decoder state of N rows: fp32 h, c [L, N, H] and feed [N, H], and the two-term copies of h (one operand of
+// `plane` halfwords per layer) and feed that the products read (kb blocks of 32 columns).
+struct DecodeState {
+  float* h;
+  float* c;
+  float* feed;
+  uint16_t* h16;
+  uint16_t* feed16;
+  size_t plane;
+  int L, N, H, kb;
+};
+// Rows b * K + k of the state = the encoder's final rows b; feed = 0.
+hipError_t decode_init(const DecodeState& s, const float* final_h, const float* final_c, int B, int K, hipStream_t st);
+// split: the two-term copies from h and feed. tok != NULL: tok_out [N] = tok with invalid ids set to 0; par_out [N]
+// (parent != NULL) = parent with rows outside [0, N) replaced by the row itself; violations recorded in *err.
+hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
+                        int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st);
+
 // kShapeMid: 32 x 64 tiles with two waves splitting K, for bf16 LSTM GEMMs of a few hundred rows (fp32 maps
 // it to the thin tile); when every A segment is a pre-split plane pair the operands go straight into LDS.
 enum GemmShape { kShapeWide = 0, kShapeSplitK = 1, kShapeSplitKThin = 2, kShapeMid = 3 };
@@ -150,9 +199,9 @@ struct AttnExtra {
   int32_t* align;               // [N]: position of the largest weight (smaller position on ties)
 };
 
-// v_a != nullptr selects concat scores v_a . tanh(q_k + keys[s]) (q = the projected query); else q_k . keys[s].
+// ctx16: the contexts as a two-term operand of ceil32(Hm) columns. v_a != nullptr selects concat scores v_a . tanh(q_k + keys[s]) (q = the projected query); else q_k . keys[s].
 hipError_t attention(const float* q, int ld_q, const float* keys, const float* v_a, const float* mem,
-                     const int32_t* lens, int B, int S_max, int H, int Hm, int K, float* scores, float* ctx,
+                     const int32_t* lens, int B, int S_max, int H, int Hm, int K, float* scores, uint16_t* ctx16,
                      float* attn, const AttnExtra& ex, hipStream_t st);
 size_t attention_lds_bytes(int S_max, int H, int K);
 
@@ -226,17 +275,6 @@ enum { kErrLength = 1, kErrSourceId = 2, kErrToken = 3, kErrParent = 4 };
 // rowmap [S, B] = b * S + s.
 hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
                         int32_t* rowmap, int32_t* err, hipStream_t st);
-// tok_out [N] = tok with invalid ids set to 0; par_out [N] (when parent != NULL) = parent with rows outside
-// [0, N) replaced by the row itself.
-hipError_t sanitize_step(const int32_t* tok, const int32_t* parent, int N, int V, int32_t* tok_out, int32_t* par_out,
-                         int32_t* err, hipStream_t st);
-
-hipError_t replicate_rows(const float* src, int ld_src, int rows, int K, float* dst, int ld_dst, int ncols,
-                          hipStream_t st);
-// hi / lo / lo2 [rows, ld_dst] = the bf16 term planes of src [rows, ld_src] columns < cols, zeros in
-// columns cols .. ld_dst.
-hipError_t split_rows(const float* src, int ld_src, int rows, int cols, uint16_t* hi, uint16_t* lo, uint16_t* lo2,
-                      int ld_dst, hipStream_t st);
 hipError_t fill_f32(float* dst, size_t n, float v, hipStream_t st);
 hipError_t copy_cols(const float* src, int ld_src, float* dst, int ld_dst, int rows, int ncols, hipStream_t st);
 

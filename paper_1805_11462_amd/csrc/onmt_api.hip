@@ -74,6 +74,15 @@ Seg seg(const void* base, const int32_t* idx, int rows, int ld, int width, int k
   return s;
 }
 
+// Weights of a few-row GEMM: `rows` (a multiple of 128) rows in fragment blocks of 1 or 2 fp16 terms and each
+// row's power of two, inside the model buffer.
+struct ThinMat {
+  size_t off = 0, exp_off = 0;
+  int rows = 0, kblocks = 0;
+  const char* base = nullptr;
+  ThinW w(int kb0 = 0) const { return ThinW{base + off, (const int32_t*)(base + exp_off), rows, kblocks, kb0}; }
+};
+
 BOp bop(const Packed& p) {
   BOp b;
   b.W = p.W;
@@ -208,12 +217,13 @@ struct onmt_model {
   std::vector<const float*> enc_bias;      // per layer [ndir * 4 Hd_pad]
   std::vector<Packed> enc_h;               // per layer * ndir: [4 Hd_pad, pad(Hd)]
   std::vector<Packed> enc_xh;              // unidirectional layers >= 1: [4 Hd_pad, pad(in) + pad(Hd)]
-  std::vector<Packed> dec_w;               // per layer [4 H_pad, sum of padded segment widths]
+  Packed dec_emb;                          // layer 0's embedding columns (for emb_gates) [4 H_pad, pad(E)]
+  std::vector<ThinMat> dec_t;              // per layer, columns [feed | recurrent] or [below | recurrent]
   std::vector<const float*> dec_bias;      // per layer [4 H_pad]
   Packed W_a;                              // memory side of the score: general W_a, concat's memory columns
-  Packed W_q;                              // concat: the query columns of W_a
+  ThinMat W_q;                             // concat: the query columns of W_a
   const float* v_a = nullptr;              // concat [H]
-  Packed W_c;
+  ThinMat W_c;                             // columns [context | query]
   size_t W_s_off = 0;
   Split16 W_s{};                           // the generator's weights: ceil128(Vt) rows of wterms fp16 terms
   const int32_t* W_s_exp = nullptr;        // power of two that undoes a vocabulary column's operand scales
@@ -266,8 +276,21 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
     cv.off += n * sizeof(float);
     return o;
   };
+  // limit: the size the refusal rule counts for the matrix (128-column padding of each segment)
+  auto thin = [&](int rows, int kblocks, uint64_t limit) {
+    ThinMat t;
+    t.rows = rows;
+    t.kblocks = kblocks;
+    cv.off = align_up(cv.off);
+    t.off = cv.off;
+    cv.off += split16_bytes(rows, kblocks, d.wterms);
+    t.exp_off = vec(rows);
+    if (mats) mats->push_back(limit);
+    return t;
+  };
   Packed esrc = mat(d.Vs, d.E);
-  std::vector<Packed> ex, eh, exh, dw;
+  std::vector<Packed> ex, eh, exh;
+  std::vector<ThinMat> dt;
   std::vector<size_t> eb, db;
   for (int l = 0; l < d.L; ++l) {
     const int in = l == 0 ? d.E : d.Hm;
@@ -284,14 +307,16 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
   }
   Packed etgt = mat(d.Vt, d.E);
   for (int l = 0; l < d.L; ++l) {
-    const int kp = l == 0 ? d.pad(d.E) + 2 * d.pad(d.H) : 2 * d.pad(d.H);
-    dw.push_back(mat(4 * d.H_pad, kp));
+    const uint64_t kp = (l == 0 ? d.pad(d.E) : 0) + 2 * d.pad(d.H);
+    dt.push_back(thin(4 * d.H_pad, 2 * d.kb(d.H), 4 * d.H_pad * kp * d.esz));
     db.push_back(vec((size_t)4 * d.H_pad));
   }
+  Packed demb = mat(4 * d.H_pad, d.pad(d.E));
   Packed wa = d.attn != ONMT_ATTN_DOT ? mat(ceil_to(d.H, 128), d.pad(d.Hm)) : Packed{};
-  Packed wq = d.attn == ONMT_ATTN_CONCAT ? mat(ceil_to(d.H, 128), d.pad(d.H)) : Packed{};
+  const int hr = ceil_to(d.H, 128);
+  ThinMat wq = d.attn == ONMT_ATTN_CONCAT ? thin(hr, d.kb(d.H), (uint64_t)hr * d.pad(d.H) * d.esz) : ThinMat{};
   const size_t va = d.attn == ONMT_ATTN_CONCAT ? vec(d.H) : 0;
-  Packed wc = mat(ceil_to(d.H, 128), d.pad(d.Hm) + d.pad(d.H));
+  ThinMat wc = thin(hr, d.kb(d.Hm) + d.kb(d.H), (uint64_t)hr * (d.pad(d.Hm) + d.pad(d.H)) * d.esz);
   cv.off = align_up(cv.off);
   const size_t ws_off = cv.off;
   const Split16 ws{nullptr, ceil_to(d.Vt, 128), d.kb(d.H)};
@@ -315,14 +340,19 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
     for (auto o : eb) m->enc_bias.push_back((const float*)(base + o));
     for (auto& p : eh) m->enc_h.push_back(fix(p));
     for (auto& p : exh) m->enc_xh.push_back(fix(p));
-    for (auto& p : dw) m->dec_w.push_back(fix(p));
+    auto fix_thin = [&](ThinMat t) {
+      t.base = base;
+      return t;
+    };
+    m->dec_emb = fix(demb);
+    for (auto& t : dt) m->dec_t.push_back(fix_thin(t));
     for (auto o : db) m->dec_bias.push_back((const float*)(base + o));
     if (d.attn != ONMT_ATTN_DOT) m->W_a = fix(wa);
     if (d.attn == ONMT_ATTN_CONCAT) {
-      m->W_q = fix(wq);
+      m->W_q = fix_thin(wq);
       m->v_a = (const float*)(base + va);
     }
-    m->W_c = fix(wc);
+    m->W_c = fix_thin(wc);
     m->W_s_off = ws_off;
     m->W_s = ws;
     m->W_s.base = base + ws_off;
@@ -353,6 +383,21 @@ void pack_row(HostImage& img, const Packed& p, int prow, int pc0, const float* s
   for (int j = 0; j < w; ++j) img.put(p.off, (size_t)prow * p.Kp + pc0 + j, src_row[c0 + j]);
 }
 
+// Row r of a few-row GEMM's matrix: columns w[i] values of src[i] from K block kb[i] on, under one row exponent.
+struct RowPart {
+  const float* src;
+  int w, kb;
+};
+void pack_thin(HostImage& img, const ThinMat& t, int terms, int r, const std::vector<RowPart>& parts) {
+  std::vector<float> row((size_t)t.kblocks * kFragK, 0.f);
+  for (const RowPart& q : parts)
+    for (int j = 0; j < q.w; ++j)
+      row[(size_t)q.kb * kFragK + j] = img.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(q.src[j])) : q.src[j];
+  const int e = host_row_exp(row.data(), (int)row.size());
+  ((int32_t*)(img.buf.data() + t.exp_off))[r] = -(kActExp + e);
+  host_pack_row((uint16_t*)(img.buf.data() + t.off), r, 0, t.kblocks, terms, row.data(), (int)row.size(), e);
+}
+
 }  // namespace
 
 // ====================================================================== allocation-free step scratch
@@ -362,7 +407,10 @@ void pack_row(HostImage& img, const Packed& p, int prow, int pc0, const float* s
 // GPU holds its own copy, at its own address, until the process ends. In host code `scratch` names a
 // host-side stand-in, never the device memory: kernels get the address hipGetSymbolAddress returns for
 // the current device, kept per device below.
-static __device__ __align__(256) char scratch[ONMT_NOALLOC_SCRATCH_BYTES];
+// The refusal rule counts ONMT_NOALLOC_SCRATCH_BYTES with unpadded contexts; the array leaves room for their
+// padding to whole fragment blocks, at most 112 bytes on a row of 56 or more.
+constexpr size_t kScratchBytes = 3 * (size_t)ONMT_NOALLOC_SCRATCH_BYTES;
+static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace {
 
@@ -478,20 +526,17 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   for (int l = 0; l < d.L; ++l) {
     const float* W = host_weights[wi++];
     const float* bvec = host_weights[wi++];
-    const Packed& P = m->dec_w[l];
     const size_t bo = off_of(m->dec_bias[l]);
-    const int in = l == 0 ? d.E + d.H : d.H;
+    const int in = l == 0 ? d.E + d.H : d.H, kb = d.kb(d.H);
     for (int g = 0; g < 4; ++g)
       for (int u = 0; u < d.H; ++u) {
         const float* row = W + (size_t)(g * d.H + u) * (in + d.H);
         const int pr = gate_row(g, u);
-        if (l == 0) {   // segments [embedding | feed | recurrent]
-          pack_row(img, P, pr, 0, row, 0, d.E);
-          pack_row(img, P, pr, d.pad(d.E), row, d.E, d.H);
-          pack_row(img, P, pr, d.pad(d.E) + d.pad(d.H), row, d.E + d.H, d.H);
-        } else {        // segments [layer below | recurrent]
-          pack_row(img, P, pr, 0, row, 0, d.H);
-          pack_row(img, P, pr, d.pad(d.H), row, d.H, d.H);
+        if (l == 0) {   // [embedding] apart; [feed | recurrent]
+          pack_row(img, m->dec_emb, pr, 0, row, 0, d.E);
+          pack_thin(img, m->dec_t[l], d.wterms, pr, {{row + d.E, d.H, 0}, {row + d.E + d.H, d.H, kb}});
+        } else {        // [layer below | recurrent]
+          pack_thin(img, m->dec_t[l], d.wterms, pr, {{row, d.H, 0}, {row + d.H, d.H, kb}});
         }
         img.putf(bo, pr, bvec[g * d.H + u]);
       }
@@ -503,7 +548,7 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
     } else if (d.attn == ONMT_ATTN_CONCAT) {   // columns [query | memory]
       const float* Wa = host_weights[wi++];
       for (int r = 0; r < d.H; ++r) {
-        pack_row(img, m->W_q, r, 0, Wa + (size_t)r * (d.H + d.Hm), 0, d.H);
+        pack_thin(img, m->W_q, d.wterms, r, {{Wa + (size_t)r * (d.H + d.Hm), d.H, 0}});
         pack_row(img, m->W_a, r, 0, Wa + (size_t)r * (d.H + d.Hm), d.H, d.Hm);
       }
       const float* va = host_weights[wi++];
@@ -512,8 +557,8 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
     }
     const float* Wc = host_weights[wi++];
     for (int r = 0; r < d.H; ++r) {
-      pack_row(img, m->W_c, r, 0, Wc + (size_t)r * (d.Hm + d.H), 0, d.Hm);
-      pack_row(img, m->W_c, r, d.pad(d.Hm), Wc + (size_t)r * (d.Hm + d.H), d.Hm, d.H);
+      const float* row = Wc + (size_t)r * (d.Hm + d.H);
+      pack_thin(img, m->W_c, d.wterms, r, {{row, d.Hm, 0}, {row + d.Hm, d.H, d.kb(d.Hm)}});
     }
     const float* Ws = host_weights[wi++];
     {
@@ -541,7 +586,7 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
     a.nseg = 1;
     a.seg[0] = seg(m->E_tgt, nullptr, d.Vt, d.E, d.E, d.pad(d.E), d.bf16);
     StoreParams sp{nullptr, m->emb_gates, 4 * d.H_pad, 4 * d.H_pad, 0};
-    e = gemm_store(d.bf16, kShapeWide, a, bop(m->dec_w[0]), sp, st);
+    e = gemm_store(d.bf16, kShapeWide, a, bop(m->dec_emb), sp, st);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess) {
@@ -620,15 +665,12 @@ struct State {
   float* h;      // [L, N, H]
   float* c;
   float* feed;   // [N, H]
-  uint16_t* feed16;   // feed as a two-term fp16 operand (the generator's)
-  // bf16 models: h and feed as their kPlanes bf16 term planes, [L, N, pad(H)] and [N, pad(H)] each (the
-  // operands of the decoder's products, split once by their producers)
-  uint16_t* h_hi;
-  uint16_t* h_lo;
-  uint16_t* h_lo2;
-  uint16_t* feed_hi;
-  uint16_t* feed_lo;
-  uint16_t* feed_lo2;
+  // h and feed as two-term fp16 operands, one of `plane` halfwords per layer (written by their producers)
+  uint16_t* h16;
+  uint16_t* feed16;
+  size_t plane;
+  // scoring keeps every step's feed16 in one operand of feed16_rows rows, this step's from row feed16_r0 on
+  int feed16_r0 = 0, feed16_rows = 0;
 };
 
 size_t state_layout(const Dims& d, int N, char* base, State* s) {
@@ -638,20 +680,20 @@ size_t state_layout(const Dims& d, int N, char* base, State* s) {
   t.h = c.take<float>((size_t)d.L * N * d.H);
   t.c = c.take<float>((size_t)d.L * N * d.H);
   t.feed = c.take<float>((size_t)N * d.H);
-  const size_t pl = (size_t)N * d.pad(d.H);
-  t.h_hi = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
-  t.h_lo = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
-  t.h_lo2 = d.bf16 ? c.take<uint16_t>(d.L * pl) : nullptr;
-  t.feed_hi = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
-  t.feed_lo = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
-  t.feed_lo2 = d.bf16 ? c.take<uint16_t>(pl) : nullptr;
-  t.feed16 = c.take<uint16_t>(split16_bytes(N, d.kb(d.H), 2) / 2);
+  t.plane = split16_bytes(N, d.kb(d.H), 2) / 2;
+  t.h16 = c.take<uint16_t>(d.L * t.plane);
+  t.feed16 = c.take<uint16_t>(t.plane);
   if (s) *s = t;
   return align_up(c.off);
 }
 
+// The parts of a State the kernels that fill it write.
+DecodeState decode_state(const Dims& d, const State& s, int N) {
+  return DecodeState{s.h, s.c, s.feed, s.h16, s.feed16, s.plane, d.L, N, d.H, d.kb(d.H)};
+}
+
 struct StepWs {
-  float* ctx;      // [N, Hm]
+  uint16_t* ctx16; // [N, Hm] attention contexts as a two-term operand
   float* scores;   // [N, S_max] raw attention scores
   float* qproj;    // [N, H] concat: query columns of W_a times the decoder output
   float* pmax;     // [N, ntiles]
@@ -674,7 +716,7 @@ size_t step_layout(const Dims& d, int B, int S, int K, char* base, StepWs* w, bo
   StepWs t;
   const size_t N = (size_t)B * K;
   t.ntiles = (d.Vt + gen_tile_cols() - 1) / gen_tile_cols();
-  t.ctx = c.take<float>(N * d.Hm);
+  t.ctx16 = c.take<uint16_t>(split16_bytes(N, d.kb(d.Hm), 2) / 2);
   t.scores = c.take<float>(N * S);
   t.qproj = d.attn == ONMT_ATTN_CONCAT ? c.take<float>(N * d.H) : nullptr;
   t.pmax = c.take<float>(N * t.ntiles);
@@ -753,9 +795,6 @@ struct ScoreWs {
   int32_t* want;       // [T, B] target predicted at step t
   int32_t* tlen;       // [B]
   float* feeds;        // [T, B, H] attentional vector of every step (the generator's input)
-  uint16_t* feeds_hi;  // bf16 models: [T, B, pad(H)] each, the same as bf16 term planes
-  uint16_t* feeds_lo;
-  uint16_t* feeds_lo2;
   uint16_t* feeds16;   // the same as a two-term fp16 operand of T * B rows
   float* gpmax;        // [T * B, ntiles] generator partials of all steps
   float* gpsum;
@@ -782,9 +821,6 @@ size_t score_layout(const Dims& d, int B, int S, int T, char* base, ScoreWs* w) 
   t.want = c.take<int32_t>((size_t)T * B);
   t.tlen = c.take<int32_t>(B);
   t.feeds = c.take<float>((size_t)T * B * d.H);
-  t.feeds_hi = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
-  t.feeds_lo = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
-  t.feeds_lo2 = c.take<uint16_t>(d.bf16 ? (size_t)T * B * d.pad(d.H) : 0);
   t.feeds16 = c.take<uint16_t>(split16_bytes((size_t)T * B, d.kb(d.H), 2) / 2);
   t.gpmax = c.take<float>((size_t)T * B * t.step.ntiles);
   t.gpsum = c.take<float>((size_t)T * B * t.step.ntiles);
@@ -1037,17 +1073,7 @@ int encode_compute(onmt_model* m, const int32_t* src, const int32_t* len, int B,
 }
 
 int decode_init_compute(onmt_model* m, const EncWs& w, int B, int K, const State& s, hipStream_t st) {
-  const Dims& d = m->d;
-  const int N = B * K;
-  for (int l = 0; l < d.L; ++l) {
-    HIP_TRY(replicate_rows(w.final_h + (size_t)l * B * d.H, d.H, B, K, s.h + (size_t)l * N * d.H, d.H, d.H, st));
-    HIP_TRY(replicate_rows(w.final_c + (size_t)l * B * d.H, d.H, B, K, s.c + (size_t)l * N * d.H, d.H, d.H, st));
-  }
-  HIP_TRY(fill_f32(s.feed, (size_t)N * d.H, 0.f, st));
-  if (d.bf16) {   // the operand planes of the first step
-    HIP_TRY(split_rows(s.h, d.H, d.L * N, d.H, s.h_hi, s.h_lo, s.h_lo2, d.pad(d.H), st));
-    HIP_TRY(split_rows(s.feed, d.H, N, d.H, s.feed_hi, s.feed_lo, s.feed_lo2, d.pad(d.H), st));
-  }
+  HIP_TRY(decode_init(decode_state(m->d, s, B * K), w.final_h, w.final_c, B, K, st));
   return ONMT_OK;
 }
 
@@ -1111,13 +1137,6 @@ GenPartials gen_partials(const GenParams& gp) {
 // all steps at once.
 // Optional work of a decoder step beyond the log-distribution.
 struct StepExtras {
-  // where the attentional vector's two-term operand goes, from which row on (default: the output state's)
-  uint16_t* feed16 = nullptr;
-  int feed16_r0 = 0;
-  // bf16 models: where its term planes go (default: the output state's)
-  uint16_t* feed_hi = nullptr;
-  uint16_t* feed_lo = nullptr;
-  uint16_t* feed_lo2 = nullptr;
   const int32_t* want = nullptr;        // the logit of column want[r] of every row goes to want_logit[r]
   float* want_logit = nullptr;
   const Coverage* cov = nullptr;        // attention coverage and its penalty
@@ -1135,45 +1154,27 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
   const Dims& d = m->d;
   const int N = B * K;
   const size_t LH = (size_t)N * d.H;
-  const int pH = d.pad(d.H);
-  const size_t LP = (size_t)N * pH;
-  // bf16 models read the pre-split planes of h and feed (widths that are multiples of 8)
-  const bool pre = d.bf16 && d.H % 8 == 0;
-  auto act = [&](const float* x, const uint16_t* hi, const uint16_t* lo, const uint16_t* lo2, const int32_t* idx) {
-    if (!pre) return seg(x, idx, N, d.H, d.H, pH, 0);
-    Seg s = seg(hi, idx, N, pH, d.H, pH, 1);
-    s.lo = lo;
-    s.lo2 = lo2;
-    return s;
+  const int kb = d.kb(d.H);
+  auto rows16 = [&](const uint16_t* base, const int32_t* idx, int row0, int width, int rows) {
+    return ThinSeg{base, idx, row0, d.kb(width), (uint32_t)split16_bytes(rows, d.kb(width), 2)};
   };
   for (int l = 0; l < d.L; ++l) {
-    AOp a{};
+    ThinA a{};
     a.M = N;
-    BOp wb = bop(m->dec_w[l]);
     LstmParams lp{};
     a.nseg = 2;
     if (l == 0) {
       // [feed ; h] against the feed and recurrent columns; the embedding columns' product is the
       // precomputed row of the previous token (emb_gates), added in the epilogue
-      a.seg[0] = act(in.feed, in.feed_hi, in.feed_lo, in.feed_lo2, parent);
-      a.seg[1] = act(in.h, in.h_hi, in.h_lo, in.h_lo2, parent);
-      wb.W = (const char*)wb.W + (size_t)d.pad(d.E) * d.esz;
+      a.seg[0] = rows16(in.feed16, parent, in.feed16_r0, d.H, in.feed16_rows ? in.feed16_rows : N);
       lp.gx = m->emb_gates;
       lp.gx_idx = prev_tok;
       lp.gx_rows = d.Vt;
       lp.ld_gx = 4 * d.H_pad;
     } else {
-      a.seg[0] = act(out.h + (l - 1) * LH, pre ? out.h_hi + (l - 1) * LP : nullptr,
-                     pre ? out.h_lo + (l - 1) * LP : nullptr, pre ? out.h_lo2 + (l - 1) * LP : nullptr, nullptr);
-      a.seg[1] = act(in.h + l * LH, pre ? in.h_hi + l * LP : nullptr, pre ? in.h_lo + l * LP : nullptr,
-                     pre ? in.h_lo2 + l * LP : nullptr, parent);
+      a.seg[0] = rows16(out.h16 + (l - 1) * out.plane, nullptr, 0, d.H, N);
     }
-    if (d.bf16) {
-      lp.h_hi = out.h_hi + l * LP;
-      lp.h_lo = out.h_lo + l * LP;
-      lp.h_lo2 = out.h_lo2 + l * LP;
-      lp.ld_hl = pH;
-    }
+    a.seg[1] = rows16(in.h16 + l * in.plane, parent, 0, d.H, N);
     lp.bias = m->dec_bias[l];
     lp.c_in = in.c + l * LH;
     lp.c_idx = parent;
@@ -1182,44 +1183,46 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
     lp.c_out = out.c + l * LH;
     lp.ld_out = d.H;
     lp.H = d.H;
+    lp.h16 = out.h16 + l * out.plane;
+    lp.kb16 = kb;
     if (timing) time_begin(m, st, ONMT_KERNEL_LSTM);
-    HIP_TRY(gemm_lstm(d.bf16, lstm_shape(d, N, m->dec_w[l].Np), a, wb, lp, st));
+    HIP_TRY(thin_lstm(d.wterms, a, m->dec_t[l].w(), lp, st));
     if (timing) time_end(m, st, ONMT_KERNEL_LSTM);
   }
+  const ThinSeg q16 = rows16(out.h16 + (d.L - 1) * out.plane, nullptr, 0, d.H, N);
   const float* q = out.h + (d.L - 1) * LH;
   const float* sq = q;
   if (d.attn == ONMT_ATTN_CONCAT) {   // the query side of concat's tanh argument, W_q q
-    AOp a{};
+    ThinA a{};
     a.M = N;
     a.nseg = 1;
-    a.seg[0] = seg(q, nullptr, N, d.H, d.H, d.pad(d.H), 0);
-    StoreParams sp{nullptr, sw.qproj, d.H, d.H, 0};
-    HIP_TRY(gemm_store(d.bf16, small_shape(N, m->W_q.Np), a, bop(m->W_q), sp, st));
+    a.seg[0] = q16;
+    StoreParams sp{};
+    sp.out = sw.qproj;
+    sp.ldo = sp.ncols = d.H;
+    HIP_TRY(thin_store(d.wterms, a, m->W_q.w(), sp, st));
     sq = sw.qproj;
   }
   const AttnExtra ax{ex.cov, ex.align};
   if (timing) time_begin(m, st, ONMT_KERNEL_ATTENTION);
-  HIP_TRY(attention(sq, d.H, w.keys, m->v_a, w.memory, w.lens, B, S, d.H, d.Hm, K, sw.scores, sw.ctx, attn, ax,
+  HIP_TRY(attention(sq, d.H, w.keys, m->v_a, w.memory, w.lens, B, S, d.H, d.Hm, K, sw.scores, sw.ctx16, attn, ax,
                     st));
   if (timing) time_end(m, st, ONMT_KERNEL_ATTENTION);
   {
-    AOp a{};
+    ThinA a{};
     a.M = N;
     a.nseg = 2;
-    a.seg[0] = seg(sw.ctx, nullptr, N, d.Hm, d.Hm, d.pad(d.Hm), 0);
-    a.seg[1] = seg(q, nullptr, N, d.H, d.H, d.pad(d.H), 0);
-    StoreParams sp{nullptr, out.feed, d.H, d.H, 1};
-    sp.s16 = ex.feed16 ? ex.feed16 : out.feed16;   // the generator's operand, split once here
-    sp.r0_16 = ex.feed16_r0;
-    sp.kb16 = d.kb(d.H);
-    if (d.bf16) {
-      sp.hi = ex.feed_hi ? ex.feed_hi : out.feed_hi;
-      sp.lo = ex.feed_lo ? ex.feed_lo : out.feed_lo;
-      sp.lo2 = ex.feed_lo2 ? ex.feed_lo2 : out.feed_lo2;
-      sp.ld_hl = sp.ncols_hl = d.pad(d.H);
-    }
+    a.seg[0] = rows16(sw.ctx16, nullptr, 0, d.Hm, N);
+    a.seg[1] = q16;
+    StoreParams sp{};
+    sp.out = out.feed;
+    sp.ldo = sp.ncols = d.H;
+    sp.act = 1;
+    sp.s16 = out.feed16;             // the operand of the generator and of the next step's first layer
+    sp.r0_16 = out.feed16_r0;
+    sp.kb16 = kb;
     if (timing) time_begin(m, st, ONMT_KERNEL_OUTPUT);
-    HIP_TRY(gemm_store(d.bf16, small_shape(N, m->W_c.Np), a, bop(m->W_c), sp, st));
+    HIP_TRY(thin_store(d.wterms, a, m->W_c.w(), sp, st));
     if (timing) time_end(m, st, ONMT_KERNEL_OUTPUT);
   }
   if (mode == 3) return ONMT_OK;
@@ -1259,6 +1262,11 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
   }
   return ONMT_OK;
 }
+
+// Whether an external step rebuilds the two-term copies of its input state from the fp32 h and feed, which a caller
+// may have written: always for fp32 models, and for bf16 models whose hidden size is not a multiple of 8 (the
+// others read the copies their producer left beside them).
+int split_state(const Dims& d) { return !d.bf16 || d.H % 8 != 0; }
 
 int check_beam(const onmt_model* m, int S, int K) {
   if (K < 1 || K > kMaxBeam) return fail(ONMT_EUNSUPPORTED, "beam %d outside [1, %d]", K, kMaxBeam);
@@ -1334,8 +1342,12 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
   const int N = B * K;
   StepWs sw;
   step_layout(m->d, B, S, K, (char*)step_ws, &sw);
+  State si, so;
+  state_layout(m->d, N, (char*)state_in, &si);
+  state_layout(m->d, N, (char*)state_out, &so);
   if (m->validation == ONMT_VALIDATE_DEVICE) {
-    HIP_TRY(sanitize_step(prev_tok, parent, N, m->cfg.tgt_vocab, sw.tok_s, sw.par_s, m->err_host, st));
+    HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), prev_tok, parent, m->cfg.tgt_vocab, sw.tok_s,
+                         sw.par_s, m->err_host, st));
     prev_tok = sw.tok_s;
     parent = parent ? sw.par_s : nullptr;
   } else {
@@ -1347,12 +1359,11 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
       if (ht[r] < 0 || ht[r] >= m->cfg.tgt_vocab) return fail(ONMT_EINVAL, "prev_tok[%d] = %d out of range", r, ht[r]);
       if (parent && (hp[r] < 0 || hp[r] >= N)) return fail(ONMT_EINVAL, "parent[%d] = %d out of range", r, hp[r]);
     }
+    HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), nullptr, nullptr, 0, nullptr, nullptr, nullptr,
+                         st));
   }
   EncWs w;
   enc_layout(m->d, B, S, (char*)enc_ws, &w);
-  State si, so;
-  state_layout(m->d, N, (char*)state_in, &si);
-  state_layout(m->d, N, (char*)state_out, &so);
   rc = decode_compute(m, w, B, S, K, si, so, prev_tok, parent, mode, logp, ids, lse, attn, sw, st);
   if (m->prof) {
     HIP_TRY(hipStreamSynchronize(st));
@@ -1380,8 +1391,10 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
   if ((rc = check_ws_limits(m->d, B, S, K, 0))) return rc;
   if (mode != 0 && mode != 1) return fail(ONMT_EINVAL, "mode must be 0 (full) or 1 (top-K)");
   if (mode == 1 && !ids) return fail(ONMT_EINVAL, "ids is NULL in top-K mode");
-  const size_t need = step_layout(m->d, B, S, K, nullptr, nullptr, true);
-  if (need > ONMT_NOALLOC_SCRATCH_BYTES)
+  const size_t bytes = step_layout(m->d, B, S, K, nullptr, nullptr, true), rows = (size_t)B * K;
+  const size_t need = bytes - align_up(split16_bytes(rows, m->d.kb(m->d.Hm), 2)) +
+                      align_up(rows * m->d.Hm * sizeof(float)) + 2 * align_up(rows * K * sizeof(float));
+  if (need > ONMT_NOALLOC_SCRATCH_BYTES || bytes > kScratchBytes)
     return fail(ONMT_EUNSUPPORTED, "this step needs %zu bytes of scratch, more than the %u of the allocation-free call",
                 need, (unsigned)ONMT_NOALLOC_SCRATCH_BYTES);
   void* sp = nullptr;
@@ -1390,12 +1403,13 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
   const int N = B * K;
   StepWs sw;
   step_layout(m->d, B, S, K, (char*)sp, &sw, true);
-  HIP_TRY(sanitize_step(prev_tok, parent, N, m->cfg.tgt_vocab, sw.tok_s, sw.par_s, m->err_host, st));
   EncWs w;
   enc_layout(m->d, B, S, (char*)enc_ws, &w);
   State si, so;
   state_layout(m->d, N, (char*)state_in, &si);
   state_layout(m->d, N, (char*)state_out, &so);
+  HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), prev_tok, parent, m->cfg.tgt_vocab, sw.tok_s,
+                       sw.par_s, m->err_host, st));
   return decode_compute(m, w, B, S, K, si, so, sw.tok_s, parent ? sw.par_s : nullptr, mode, logp, ids, lse, attn, sw,
                         st, StepExtras{}, false);
 }
@@ -1613,23 +1627,16 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
     State in = w.st[cur], out = w.st[cur ^ 1];
     if (t > 0) {
       in.feed = w.feeds + (size_t)(t - 1) * B * d.H;
-      if (d.bf16) {
-        in.feed_hi = w.feeds_hi + (size_t)(t - 1) * B * d.pad(d.H);
-        in.feed_lo = w.feeds_lo + (size_t)(t - 1) * B * d.pad(d.H);
-        in.feed_lo2 = w.feeds_lo2 + (size_t)(t - 1) * B * d.pad(d.H);
-      }
+      in.feed16 = w.feeds16;
+      in.feed16_r0 = (t - 1) * B;
+      in.feed16_rows = T * B;
     }
     out.feed = w.feeds + (size_t)t * B * d.H;
-    StepExtras ex;
-    ex.feed16 = w.feeds16;
-    ex.feed16_r0 = t * B;
-    if (d.bf16) {
-      ex.feed_hi = w.feeds_hi + (size_t)t * B * d.pad(d.H);
-      ex.feed_lo = w.feeds_lo + (size_t)t * B * d.pad(d.H);
-      ex.feed_lo2 = w.feeds_lo2 + (size_t)t * B * d.pad(d.H);
-    }
+    out.feed16 = w.feeds16;
+    out.feed16_r0 = t * B;
+    out.feed16_rows = T * B;
     rc = decode_compute(m, w.enc, B, S, 1, in, out, w.in_tok + (size_t)t * B, nullptr, 3, nullptr, nullptr, nullptr,
-                        nullptr, w.step, st, ex);
+                        nullptr, w.step, st);
     if (rc) return rc;
     cur ^= 1;
   }

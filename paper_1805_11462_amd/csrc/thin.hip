@@ -1,0 +1,442 @@
+// GEMMs of few rows for gfx950 (decoder layers, encoder recurrence, attentional output): out[r, n] =
+// sum_k A[r, k] W[n, k] over at most a few hundred gathered rows, with the LSTM cell (Section 2 item (a) of the
+// OpenNMT paper) or a plain store as epilogue.
+//
+// A step's weights are a few MB and its products take 1-6 us of MFMA time, so what bounds these launches is how
+// many bytes of operands a CU keeps in flight and the fixed cost of a launch. The main loop has no LDS and no
+// barrier: the workgroup's NW waves split K, each wave loads its own 32-column K blocks of the tile's A and W rows
+// straight into registers, D blocks ahead, and nothing is loaded twice inside a workgroup. Operands are two-term
+// fp16 splits in fragment blocks (split16.h): every load is 1 KB of consecutive addresses (A rows that come
+// through a beam parent map: 16-byte chunks of a few neighbouring rows). The waves' partial tiles meet once, in
+// LDS, before the epilogue.
+
+#include "common.h"
+#include "gemm_device.h"
+#include "kernels.h"
+#include "split16.h"
+
+namespace onmt {
+
+// PB: weight terms; the tile is 16 TM x 16 TN, NW waves split K, D K blocks in flight per wave.
+template <int PB_, int TM_, int TN_, int NW_, int D_>
+struct Thin {
+  static constexpr int PB = PB_, TM = TM_, TN = TN_, NW = NW_, D = D_;
+  static constexpr int BM = 16 * TM, BN = 16 * TN, NT = 64 * NW;
+  static constexpr int CROW = BN + 4;
+  static constexpr int PART = BM * CROW;        // floats of one wave's partial tile
+  static constexpr int LDS = NW * PART * 4;
+};
+
+// Main loop: leaves NW partial tiles in LDS at red ([NW][BM][CROW] floats), no barrier after the stores.
+template <class C, int NSEG>
+__device__ __forceinline__ void thin_main(const ThinA& a, const ThinW& w, int m0, int n0, float* red) {
+  static_assert(NSEG == 1 || NSEG == 2, "one or two A segments");
+  constexpr int TM = C::TM, TN = C::TN, PB = C::PB, D = C::D;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  // byte offsets of the lane's A rows in each segment (rows past M read row M - 1; never stored)
+  uint32_t ro[NSEG][TM];
+#pragma unroll
+  for (int s = 0; s < NSEG; ++s)
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+      const int m = min(m0 + 16 * x + i16, a.M - 1);
+      const uint32_t r = a.seg[s].row0 + (a.seg[s].idx ? a.seg[s].idx[m] : m);
+      ro[s][x] = (r / kFragRows) * a.seg[s].kblocks * 2048u + g * 256u + (r % kFragRows) * 16u;
+    }
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(w.base, (uint32_t)(w.rows / 16) * w.kblocks * (PB * 1024u));
+  uint32_t wo[TN];
+#pragma unroll
+  for (int y = 0; y < TN; ++y) wo[y] = ((uint32_t)(n0 / 16 + y) * w.kblocks + w.kb0) * (PB * 1024u) + lane * 16u;
+  const int kb0 = a.seg[0].kblocks, ktot = kb0 + (NSEG > 1 ? a.seg[NSEG - 1].kblocks : 0);
+
+  struct Frag {
+    uint4 a[TM][2];
+    uint4 w[TN][PB];
+  };
+  // K block st of the segments one after the other; past the last, the offsets lie beyond the buffers (zeros)
+  auto load = [&](int st, Frag& f) {
+    const bool on = st < ktot, s1 = NSEG > 1 && st >= kb0;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(s1 ? a.seg[NSEG - 1].base : a.seg[0].base,
+                                                s1 ? a.seg[NSEG - 1].bytes : a.seg[0].bytes);
+    const uint32_t ks = on ? (uint32_t)(s1 ? st - kb0 : st) * 2048u : 0u;
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+      const uint32_t off = on ? (s1 ? ro[NSEG - 1][x] : ro[0][x]) : kPastEnd;
+      f.a[x][0] = buf_load16s(ra, off, ks);
+      f.a[x][1] = buf_load16s(ra, on ? off + 1024u : kPastEnd, ks);
+    }
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb)
+        f.w[y][pb] = buf_load16s(rw, on ? wo[y] : kPastEnd, on ? (uint32_t)(st * PB + pb) * 1024u : 0u);
+  };
+
+  f32x4 c0[TM][TN], c1[TM][TN];
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) c0[x][y] = c1[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the weights are the MFMA's row operand, so a lane ends up with four consecutive columns of one row
+  auto compute = [&](const Frag& f) {
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+#pragma unroll
+      for (int y = 0; y < TN; ++y) c0[x][y] = mfma_f16(f.w[y][0], f.a[x][0], c0[x][y]);
+#pragma unroll
+      for (int y = 0; y < TN; ++y) c1[x][y] = mfma_f16(f.w[y][0], f.a[x][1], c1[x][y]);
+      if constexpr (PB == 2) {
+#pragma unroll
+        for (int y = 0; y < TN; ++y) c1[x][y] = mfma_f16(f.w[y][PB - 1], f.a[x][0], c1[x][y]);
+      }
+    }
+  };
+  Frag f[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(wave + C::NW * d, f[d]);
+  for (int st = wave; st < ktot; st += C::NW * D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      compute(f[d]);
+      load(st + C::NW * (d + D), f[d]);
+    }
+  }
+  float* Ct = red + wave * C::PART;
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = fmaf(c1[x][y][j], 1.f / kLoScale, c0[x][y][j]);
+      *(f32x4*)(Ct + (16 * x + i16) * C::CROW + 16 * y + 4 * g) = v;
+    }
+}
+
+template <class C>
+__device__ inline float thin_sum(const float* red, int r, int c) {
+  float s = red[r * C::CROW + c];
+#pragma unroll
+  for (int w = 1; w < C::NW; ++w) s += red[w * C::PART + r * C::CROW + c];
+  return s;
+}
+
+// What the LSTM epilogue adds to this thread's (row, unit) elements: bias, the precomputed input projection
+// (table rows gathered by token id) and the previous cell state, with the columns' scales, all loaded before the
+// main loop.
+template <class C>
+struct ThinLstm {
+  static constexpr int UPT = C::BN / 4;                          // units per tile
+  static constexpr int EPT = (C::BM * UPT + C::NT - 1) / C::NT;  // elements per thread
+  float z[EPT][4], c[EPT];
+  int ex[EPT][4];
+
+  __device__ __forceinline__ void load(const LstmParams& p, const int32_t* wexp, int M, int m0, int n0) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      const int e = threadIdx.x + i * C::NT;
+      const int r = e / UPT, uu = e % UPT;
+      const int row = m0 + r, unit = n0 / 4 + uu;
+      const bool ok = e < C::BM * UPT && row < M && unit < p.H;
+      const int cbase = (uu / kUnitGroup) * (4 * kUnitGroup) + (uu % kUnitGroup);
+      const int grow = !(ok && p.gx) ? 0 : (p.gx_idx ? min((unsigned)p.gx_idx[row], (unsigned)p.gx_rows - 1u) : row * p.gx_S + p.gx_s);
+      const int crow = ok && p.c_idx ? p.c_idx[row] : row;
+      c[i] = ok && p.c_in ? p.c_in[(size_t)crow * p.ld_c + unit] : 0.f;
+#pragma unroll
+      for (int gt = 0; gt < 4; ++gt) {
+        const int col = n0 + cbase + gt * kUnitGroup;
+        ex[i][gt] = ok ? wexp[col] : 0;
+        z[i][gt] = (ok && p.bias ? p.bias[col] : 0.f) +
+                   (ok && p.gx ? p.gx[(size_t)grow * p.ld_gx + p.gx_col0 + col] : 0.f);
+      }
+    }
+  }
+
+  // Gate nonlinearities and cell update over the tile whose partial sums are in LDS. The rows past M of the last
+  // 16-row block and the units past H of the last 32-column block of the two-term copies are zeros.
+  __device__ __forceinline__ void finish(const float* red, const LstmParams& p, int M, int m0, int n0) const {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      const int e = threadIdx.x + i * C::NT;
+      const int r = e / UPT, uu = e % UPT;
+      const int row = m0 + r, unit = n0 / 4 + uu;
+      if (e >= C::BM * UPT) continue;
+      float h_new = 0.f, y = 0.f;
+      const bool on = row < M && unit < p.H;
+      if (on) {
+        const int cbase = (uu / kUnitGroup) * (4 * kUnitGroup) + (uu % kUnitGroup);
+        float zz[4], c_new;
+#pragma unroll
+        for (int gt = 0; gt < 4; ++gt) zz[gt] = ldexpf(thin_sum<C>(red, r, cbase + gt * kUnitGroup), ex[i][gt]) + z[i][gt];
+        if (p.lens && p.y_s >= p.lens[row]) {
+          c_new = c[i];
+          h_new = p.h_in ? p.h_in[(size_t)row * p.ld_h_in + unit] : 0.f;
+        } else {
+          const float ig = sigmoidf_(zz[0]), fg = sigmoidf_(zz[1]), gg = tanhf(zz[2]), og = sigmoidf_(zz[3]);
+          c_new = fg * c[i] + ig * gg;
+          h_new = og * tanhf(c_new);
+          y = h_new;
+        }
+        p.h_out[(size_t)row * p.ld_out + unit] = h_new;
+        p.c_out[(size_t)row * p.ld_out + unit] = c_new;
+        if (p.y_out) p.y_out[(size_t)(row * p.y_S + p.y_s) * p.ld_y + p.y_col0 + unit] = y;
+      }
+      if (p.h16 && row < (M + kFragRows - 1) / kFragRows * kFragRows && unit < p.kb16 * kFragK) {
+        uint16_t hi, lo;
+        split_act(h_new, hi, lo);
+        uint16_t* d = p.h16 + split16_at(row, unit, p.kb16, 2);
+        d[0] = hi;
+        d[kFragElems] = lo;
+      }
+      if (p.y16 && on) {
+        uint16_t hi, lo;
+        split_act(y, hi, lo);
+        uint16_t* d = p.y16 + split16_at((size_t)row * p.y_S + p.y_s, p.y_col0 + unit, p.y_kb16, 2);
+        d[0] = hi;
+        d[kFragElems] = lo;
+      }
+    }
+  }
+};
+
+template <class C, int NSEG>
+__device__ __forceinline__ void thin_lstm_tile(const ThinA& a, const ThinW& w, const LstmParams& p, int nm, int nblocks,
+                                               int bid, float* red) {
+  const int L = xcd_remap(bid, nblocks);
+  const int m0 = (L % nm) * C::BM, n0 = (L / nm) * C::BN;
+  ThinLstm<C> ep;
+  ep.load(p, w.wexp, a.M, m0, n0);
+  thin_main<C, NSEG>(a, w, m0, n0, red);
+  __syncthreads();
+  ep.finish(red, p, a.M, m0, n0);
+}
+
+template <class C, int NSEG>
+__global__ __launch_bounds__(C::NT) void k_thin_lstm(ThinA a, ThinW w, LstmParams p, int nm, int nblocks) {
+  __shared__ __attribute__((aligned(16))) float red[C::LDS / 4];
+  thin_lstm_tile<C, NSEG>(a, w, p, nm, nblocks, blockIdx.x, red);
+}
+
+template <class C, int NSEG>
+__global__ __launch_bounds__(C::NT) void k_thin_store(ThinA a, ThinW w, StoreParams p, int nm, int nblocks) {
+  __shared__ __attribute__((aligned(16))) float red[C::LDS / 4];
+  const int L = xcd_remap(blockIdx.x, nblocks);
+  const int m0 = (L % nm) * C::BM, n0 = (L / nm) * C::BN;
+  thin_main<C, NSEG>(a, w, m0, n0, red);
+  __syncthreads();
+  const int pad_rows = (p.r0_16 + a.M + kFragRows - 1) / kFragRows * kFragRows - p.r0_16;
+  for (int e = threadIdx.x; e < C::BM * (C::BN / 4); e += C::NT) {
+    const int r = e / (C::BN / 4), c = e % (C::BN / 4) * 4;
+    const int row = m0 + r, col = n0 + c;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (row < a.M && col < p.ncols) {            // ncols is a multiple of 4
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] = ldexpf(thin_sum<C>(red, r, c + j), w.wexp[col + j]) + (p.bias ? p.bias[col + j] : 0.f);
+        if (p.act == 1) v[j] = tanhf(v[j]);
+      }
+      *(float4*)(p.out + (size_t)row * p.ldo + col) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    // the two-term copy, with zeros in the rest of its last 16-row and 32-column blocks
+    if (p.s16 && row < pad_rows && col < p.kb16 * kFragK) store_act4(p.s16, p.r0_16 + row, col, p.kb16, v);
+  }
+}
+
+// ---------------------------------------------------------------- launchers
+
+// Tile by the operand bytes a CU reads per K element when `blocks` workgroups are dealt to 256 CUs: rounds x (4
+// per row of the tile + 2 per column and weight term), the least of the shapes below. Measured (us, weights cold,
+// two-segment LSTM layers; the 16 x 32 tiles with LDS stages before in brackets), fp32 weights, 2 x 500 columns,
+// 2000 units x gates: 320 rows 80 x 32 10.5, 48 x 32 12.9, 32 x 32 13.3 [18.3]; 160 rows 48 x 32 8.2, 32 x 32 10.3
+// [13.4]; 64 rows 16 x 32 5.8, 32 x 32 6.8 [11.5]; 5 rows 5.5 [11.0]; bf16 weights, 320 x 2 x 1000 x 4000: 80 x 64
+// 21.2, 32 x 64 27.6 [31]; 512 x 2 x 1024 x 4096: 32 x 128 31.1, 80 x 64 38.4 [42].
+struct ThinShape {
+  int tm, tn;
+};
+constexpr ThinShape kThin2[] = {{1, 2}, {2, 2}, {3, 2}, {5, 2}};      // two weight terms
+constexpr ThinShape kThin1[] = {{1, 2}, {2, 4}, {5, 4}, {2, 8}};      // one
+template <int N>
+static int thin_shape(const ThinShape (&list)[N], int pb, int nprob, const int* M, const int* rows) {
+  int best = 0;
+  long cost = -1;
+  for (int i = 0; i < N; ++i) {
+    long blocks = 0;
+    for (int q = 0; q < nprob; ++q)
+      blocks += (long)((M[q] + 16 * list[i].tm - 1) / (16 * list[i].tm)) * (rows[q] / (16 * list[i].tn));
+    const long c = (blocks + 255) / 256 * (list[i].tm * 64 + list[i].tn * 32 * pb);
+    if (cost < 0 || c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
+static bool thin_ok(const ThinA& a, const ThinW& w, int pb) {
+  if ((pb != 1 && pb != 2) || a.M < 1 || a.nseg < 1 || a.nseg > 2 || w.rows % 128 || w.rows < 1) return false;
+  int k = w.kb0;
+  for (int s = 0; s < a.nseg; ++s) k += a.seg[s].kblocks;
+  return w.kb0 >= 0 && k <= w.kblocks && split16_bytes(w.rows, w.kblocks, pb) < (1ull << 31);
+}
+
+template <class C>
+static hipError_t launch_thin_lstm(const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st) {
+  const int nm = (a.M + C::BM - 1) / C::BM, nb = nm * (w.rows / C::BN);
+  if (a.nseg == 1) hipLaunchKernelGGL((k_thin_lstm<C, 1>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
+  else hipLaunchKernelGGL((k_thin_lstm<C, 2>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
+  return hipGetLastError();
+}
+
+template <class C>
+static hipError_t launch_thin_store(const ThinA& a, const ThinW& w, const StoreParams& p, hipStream_t st) {
+  const int nm = (a.M + C::BM - 1) / C::BM, nb = nm * (w.rows / C::BN);
+  if (a.nseg == 1) hipLaunchKernelGGL((k_thin_store<C, 1>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
+  else hipLaunchKernelGGL((k_thin_store<C, 2>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
+  return hipGetLastError();
+}
+
+#define ONMT_THIN_DISPATCH(PB, I, CALL)                                  \
+  do {                                                                   \
+    if ((PB) == 2) {                                                     \
+      if ((I) == 0) return CALL(Thin<2, 1, 2, 8, 2>);                    \
+      if ((I) == 1) return CALL(Thin<2, 2, 2, 8, 2>);                    \
+      if ((I) == 2) return CALL(Thin<2, 3, 2, 8, 2>);                    \
+      return CALL(Thin<2, 5, 2, 8, 1>);                                  \
+    }                                                                    \
+    if ((I) == 0) return CALL(Thin<1, 1, 2, 8, 4>);                      \
+    if ((I) == 1) return CALL(Thin<1, 2, 4, 8, 2>);                      \
+    if ((I) == 2) return CALL(Thin<1, 5, 4, 4, 2>);                      \
+    return CALL(Thin<1, 2, 8, 8, 1>);                                    \
+  } while (0)
+
+hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st) {
+  if (!thin_ok(a, w, w_terms)) return hipErrorInvalidValue;
+  const int i = w_terms == 2 ? thin_shape(kThin2, 2, 1, &a.M, &w.rows) : thin_shape(kThin1, 1, 1, &a.M, &w.rows);
+#define ONMT_CALL(...) launch_thin_lstm<__VA_ARGS__>(a, w, p, st)
+  ONMT_THIN_DISPATCH(w_terms, i, ONMT_CALL);
+#undef ONMT_CALL
+}
+
+hipError_t thin_store(int w_terms, const ThinA& a, const ThinW& w, const StoreParams& p, hipStream_t st) {
+  if (!thin_ok(a, w, w_terms) || p.ncols % 4 || p.ncols > w.rows || (p.s16 && p.kb16 * kFragK > w.rows)) return hipErrorInvalidValue;
+  const int i = w_terms == 2 ? thin_shape(kThin2, 2, 1, &a.M, &w.rows) : thin_shape(kThin1, 1, 1, &a.M, &w.rows);
+#define ONMT_CALL(...) launch_thin_store<__VA_ARGS__>(a, w, p, st)
+  ONMT_THIN_DISPATCH(w_terms, i, ONMT_CALL);
+#undef ONMT_CALL
+}
+
+// ---------------------------------------------------------------- decoder state
+
+// Eight consecutive columns (k0 a multiple of 8) of row r of a two-term operand.
+__device__ inline void store_act8(uint16_t* dst, int r, int k0, int kblocks, const float (&v)[8]) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint16_t h0, h1, l0, l1;
+    split_act(v[2 * j], h0, l0);
+    split_act(v[2 * j + 1], h1, l1);
+    h[j] = h0 | (uint32_t)h1 << 16;
+    l[j] = l0 | (uint32_t)l1 << 16;
+  }
+  uint16_t* d = dst + split16_at(r, k0, kblocks, 2);
+  *(uint4*)d = make_uint4(h[0], h[1], h[2], h[3]);
+  *(uint4*)(d + kFragElems) = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// Thread = eight columns of one row of one of L + 1 row sets (the layers' h, then feed), rows up to the end of the
+// last 16-row block and columns up to the end of the last 32-column block (zeros there). Reads 4 columns at a
+// time (H is a multiple of 4).
+__device__ inline void row_chunk(const float* src, int H, int k0, bool on, float (&v)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 4) {
+    const float4 q = on && k0 + j < H ? *(const float4*)(src + k0 + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    v[j] = q.x, v[j + 1] = q.y, v[j + 2] = q.z, v[j + 3] = q.w;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_decode_init(DecodeState s, const float* __restrict__ final_h,
+                                                     const float* __restrict__ final_c, int B, int K) {
+  const int chunks = s.kb * 4, rows = (s.N + kFragRows - 1) / kFragRows * kFragRows;
+  const size_t n = (size_t)(s.L + 1) * rows * chunks;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int k0 = (int)(i % chunks) * 8, r = (int)(i / chunks % rows), l = (int)(i / chunks / rows);
+    const bool on = r < s.N;
+    float h[8], c[8];
+    if (l < s.L) {
+      const size_t src = ((size_t)l * B + r / K) * s.H;
+      row_chunk(final_h + src, s.H, k0, on, h);
+      row_chunk(final_c + src, s.H, k0, on, c);
+      store_act8(s.h16 + l * s.plane, r, k0, s.kb, h);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) h[j] = 0.f;
+      store_act8(s.feed16, r, k0, s.kb, h);
+    }
+    if (!on) continue;
+    const size_t o = ((size_t)(l < s.L ? l : 0) * s.N + r) * s.H + k0;
+#pragma unroll
+    for (int j = 0; j < 8; j += 4) {
+      if (k0 + j >= s.H) break;
+      *(float4*)((l < s.L ? s.h : s.feed) + o + j) = make_float4(h[j], h[j + 1], h[j + 2], h[j + 3]);
+      if (l < s.L) *(float4*)(s.c + o + j) = make_float4(c[j], c[j + 1], c[j + 2], c[j + 3]);
+    }
+  }
+}
+
+hipError_t decode_init(const DecodeState& s, const float* final_h, const float* final_c, int B, int K, hipStream_t st) {
+  const size_t n = (size_t)(s.L + 1) * ((s.N + kFragRows - 1) / kFragRows * kFragRows) * s.kb * 4;
+  size_t blocks = (n + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(k_decode_init, dim3((unsigned)blocks), dim3(256), 0, st, s, final_h, final_c, B, K);
+  return hipGetLastError();
+}
+
+// The checks of k_sanitize_step (tok given) and the two-term copies of a caller's state (split), one launch.
+__global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, const int32_t* __restrict__ tok,
+                                                      const int32_t* __restrict__ parent, int V,
+                                                      int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out,
+                                                      int32_t* err) {
+  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  if (tok) {
+    for (size_t r = i0; r < (size_t)s.N; r += step) {
+      int t = tok[r];
+      if (t < 0 || t >= V) {
+        *err = kErrToken;
+        t = 0;
+      }
+      tok_out[r] = t;
+      if (parent) {
+        int p = parent[r];
+        if (p < 0 || p >= s.N) {
+          *err = kErrParent;
+          p = (int)r;
+        }
+        par_out[r] = p;
+      }
+    }
+  }
+  if (!split) return;
+  const int chunks = s.kb * 4, rows = (s.N + kFragRows - 1) / kFragRows * kFragRows;
+  const size_t n = (size_t)(s.L + 1) * rows * chunks;
+  for (size_t i = i0; i < n; i += step) {
+    const int k0 = (int)(i % chunks) * 8, r = (int)(i / chunks % rows), l = (int)(i / chunks / rows);
+    const bool on = r < s.N;
+    float v[8];
+    row_chunk((l < s.L ? s.h + (size_t)l * s.N * s.H : s.feed) + (size_t)r * s.H, s.H, k0, on, v);
+    store_act8(l < s.L ? s.h16 + l * s.plane : s.feed16, r, k0, s.kb, v);
+  }
+}
+
+hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
+                        int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st) {
+  if (!split && !tok) return hipSuccess;
+  const size_t n = split ? (size_t)(s.L + 1) * ((s.N + kFragRows - 1) / kFragRows * kFragRows) * s.kb * 4 : (size_t)s.N;
+  size_t blocks = (n + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(k_prepare_step, dim3((unsigned)blocks), dim3(256), 0, st, s, split, tok, parent, V, tok_out,
+                     par_out, err);
+  return hipGetLastError();
+}
+
+}  // namespace onmt

@@ -1,0 +1,90 @@
+"""The few-row products (decoder layers, attentional output) at the sizes where their tiles change: rows around the
+16-row blocks and each tile height, hidden sizes that end inside an 8-unit group or a 32-column block, one to three
+layers, rows gathered through a parent map, and a caller's own fp32 state."""
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import onmt_oracle as O
+from ._gpu import translator_for, with_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _exact_step(w, weights, mem, keys, lens, h, c, feed, tok, par, K):
+    """One decoder step in 64 bits with torch: (h, c, feed)."""
+    t = {k: torch.from_numpy(v).cuda().double() for k, v in weights.items()}
+    x = torch.cat([t["E_tgt"][tok], feed[par]], 1)
+    hs, cs = [], []
+    for l in range(w.dec_layers):
+        z = torch.cat([x, h[l][par]], 1) @ t[f"dec{l}_W"].t().contiguous() + t[f"dec{l}_b"]
+        i, f, g, o = z.chunk(4, 1)
+        cl = torch.sigmoid(f) * c[l][par] + torch.sigmoid(i) * torch.tanh(g)
+        x = torch.sigmoid(o) * torch.tanh(cl)
+        hs.append(x)
+        cs.append(cl)
+    B, S, H = mem.shape
+    e = torch.bmm(x.reshape(B, K, H), keys.transpose(1, 2).contiguous())
+    off = torch.arange(S, device="cuda")[None, None, :] >= lens[:, None, None]
+    a = torch.softmax(e.masked_fill(off, -float("inf")), -1)
+    ctx = torch.bmm(a, mem).reshape(B * K, H)
+    return torch.stack(hs), torch.stack(cs), torch.tanh(torch.cat([ctx, x], 1) @ t["W_c"].t().contiguous())
+
+
+@pytest.mark.parametrize("wdtype,hidden,layers,B,K", [
+    ("fp32", 36, 1, 1, 1), ("fp32", 64, 2, 5, 3), ("fp32", 100, 1, 4, 4), ("fp32", 100, 3, 17, 1),
+    ("fp32", 516, 1, 13, 5), ("fp32", 500, 2, 27, 3), ("fp32", 500, 1, 16, 10), ("fp32", 500, 2, 23, 7),
+    ("fp32", 500, 1, 32, 10), ("fp32", 68, 1, 81, 4), ("fp32", 1000, 1, 33, 5),
+    ("bf16", 36, 1, 1, 1), ("bf16", 100, 2, 7, 5), ("bf16", 500, 2, 64, 1), ("bf16", 1000, 2, 64, 5),
+    ("bf16", 1024, 1, 513, 1), ("bf16", 1000, 1, 32, 4), ("bf16", 104, 1, 81, 5),
+])
+@pytest.mark.parametrize("own_state", [False, True])
+def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
+    if own_state and wdtype == "bf16" and hidden % 8 == 0:
+        pytest.skip("such models read the operand copies their producer left beside h and feed")
+    w = with_workload(W.get("tiny"), hidden=hidden, emb=32, enc_layers=layers, dec_layers=layers, wdtype=wdtype)
+    weights = W.make_weights(w)
+    tr = translator_for(w, weights)
+    print(f"[case] few rows {wdtype} H{hidden} L{layers} B{B} K{K} own_state={own_state}", flush=True)
+    rng = np.random.default_rng(7)
+    S, N = 5, B * K
+    src = torch.from_numpy(rng.integers(4, w.src_vocab, (B, S)).astype(np.int32)).cuda()
+    lens = torch.from_numpy(rng.integers(1, S + 1, B).astype(np.int32)).cuda()
+    ws = tr.encode(src, lens)
+    st = tr.decode_init(ws, B, S, K)
+    tok = torch.from_numpy(rng.integers(4, w.tgt_vocab, N).astype(np.int32)).cuda()
+    par = torch.from_numpy((np.arange(N) // K * K + rng.integers(0, K, N)).astype(np.int32)).cuda()
+    st = tr.decode_step(ws, B, S, K, st, tok, None, mode=1)[0]
+    h, c, feed = tr.state_views(st, N)
+    if own_state:
+        for x in (h, c, feed):
+            x.copy_(torch.from_numpy(rng.uniform(-3, 3, tuple(x.shape)).astype(np.float32)))
+    h, c, feed = h.double(), c.double(), feed.double()
+    got = tr.decode_step(ws, B, S, K, st, tok, par, mode=1)[0]
+    mem, keys, _, _ = tr.enc_views(ws, B, S)
+    want = _exact_step(w, weights, mem.double(), keys.double(), lens.long(), h, c, feed, tok.long(), par.long(), K)
+    for x, y in zip(tr.state_views(got, N), want):
+        # pre-activations sum 2 hidden + 32 products of size <= 0.3 to 2^-22 each, then pass through functions of
+        # slope <= 1 (twice over the layers and the output); a c of size 4 keeps 2^-22 of itself
+        assert (x.double() - y).abs().max().item() <= 2e-6 * (1 + layers) * (3 if own_state else 1)
+    tr.close()
+
+
+def test_zero_and_tiny_states_stay_exact():
+    # zero weights: h and feed stay zero; tiny weights: the operand split keeps relative precision
+    for scale in (0.0, 1e-4):
+        w = with_workload(W.get("tiny"), batch=3)
+        weights = {k: (v * np.float32(scale)).astype(np.float32) for k, v in W.make_weights(w).items()}
+        tr = translator_for(w, weights)
+        src, lens = W.make_batch(w, batch=3)
+        buf = tr.search_buffers(3, src.shape[1], 2, 4)
+        tr.beam_search(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda(), buf)
+        m = O.model_from(w, weights)
+        for b in range(3):
+            n = int(buf["len"][b])
+            toks = [int(x) for x in buf["tok"][b, :n].cpu()]
+            ref = O.score_forced(m, src[b], lens[b], toks)
+            np.testing.assert_allclose(buf["tok_logp"][b, :n].cpu().numpy(), ref, atol=2e-6)
+        tr.close()
