@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libonmt.so")
-SOURCES = ["onmt_api.hip", "gemm.hip", "thin.hip", "gen.hip", "attention.hip", "beam.hip"]
+SOURCES = ["onmt_api.hip", "thin.hip", "gen.hip", "wide.hip", "attention.hip", "beam.hip"]
 
 # Packed-FP32 VALU ops are switched off for all device code (only plain fp32 VALU and MFMA are used).
 HIPCC_FLAGS = [

@@ -606,8 +606,7 @@ hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, con
 // recorded in *err (a word of host-visible memory the host reads once the stream is synchronized). Several
 // threads may store different codes; any nonzero code reports the failure.
 __global__ void k_sanitize_src(const int32_t* __restrict__ src, const int32_t* __restrict__ len, int B, int S, int V,
-                               int32_t* __restrict__ clean, int32_t* __restrict__ lens, int32_t* __restrict__ rowmap,
-                               int32_t* err) {
+                               int32_t* __restrict__ clean, int32_t* __restrict__ lens, int32_t* err) {
   const size_t n = (size_t)B * S;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
     const int b = (int)(i / S), s = (int)(i % S);
@@ -625,18 +624,16 @@ __global__ void k_sanitize_src(const int32_t* __restrict__ src, const int32_t* _
         id = 0;
       }
     }
-    clean[i] = id;
-    rowmap[(size_t)s * B + b] = (int32_t)i;
+    clean[(size_t)s * B + b] = id;
   }
 }
 
 hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
-                        int32_t* rowmap, int32_t* err, hipStream_t st) {
+                        int32_t* err, hipStream_t st) {
   const size_t n = (size_t)B * S;
   size_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_sanitize_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, clean, lens, rowmap,
-                     err);
+  hipLaunchKernelGGL(k_sanitize_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, clean, lens, err);
   return hipGetLastError();
 }
 
@@ -654,15 +651,24 @@ hipError_t fill_f32(float* dst, size_t n, float v, hipStream_t st) {
   return hipGetLastError();
 }
 
-__global__ void k_copy_cols(const float* src, int ld_src, float* dst, int ld_dst, int ncols) {
-  const int r = blockIdx.y;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncols; c += gridDim.x * blockDim.x)
-    dst[(size_t)r * ld_dst + c] = src[(size_t)r * ld_src + c];
+__global__ void k_zero_pad16(uint16_t* a, uint16_t* b, int rows, int width, int kblocks) {
+  uint16_t* dst = blockIdx.y ? b : a;
+  const int w = kblocks * kFragK - width;
+  const size_t n = (size_t)rows * w;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    uint16_t* d = dst + split16_at(i % rows, width + (int)(i / rows), kblocks, 2);
+    d[0] = 0;
+    d[kFragElems] = 0;
+  }
 }
 
-hipError_t copy_cols(const float* src, int ld_src, float* dst, int ld_dst, int rows, int ncols, hipStream_t st) {
-  if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_cols, dim3((ncols + 255) / 256, rows), dim3(256), 0, st, src, ld_src, dst, ld_dst, ncols);
+hipError_t zero_pad16(uint16_t* a, uint16_t* b, int rows, int width, int kblocks, hipStream_t st) {
+  rows = (rows + kFragRows - 1) / kFragRows * kFragRows;
+  const size_t n = (size_t)rows * (kblocks * kFragK - width);
+  if (n == 0) return hipSuccess;
+  size_t blocks = (n + 255) / 256;
+  if (blocks > 2048) blocks = 2048;
+  hipLaunchKernelGGL(k_zero_pad16, dim3((unsigned)blocks, b ? 2 : 1), dim3(256), 0, st, a, b, rows, width, kblocks);
   return hipGetLastError();
 }
 

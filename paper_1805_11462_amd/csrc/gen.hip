@@ -21,6 +21,7 @@
 #include "gemm_device.h"
 #include "kernels.h"
 #include "split16.h"
+#include "wide_loop.h"
 
 namespace onmt {
 
@@ -40,20 +41,14 @@ struct GenTile {
   static constexpr int LDS = NSTG * STG;
 };
 
-// More rows: 16 TM x 256 tile, four waves of all 16 TM rows x 64 columns. A wave's weights are its own, so they
-// go straight into registers, D stages ahead, and LDS holds the rows all four waves read: with both operands
-// in LDS its bandwidth was the bound (reads plus stage writes 90% of 128 bytes per clock at 160 x 128 tiles).
+// More rows: the wide tiles (wide_loop.h), 16 TM x 256, four waves of all 16 TM rows x 64 columns.
 // 320 rows x 50000 x 512, fp32 weights: 56 us (160 x 128 tiles through LDS 64; six bf16 term products in 64 x 128
 // tiles 110-126); bf16 weights, 512 x 32000 x 1024: 58 us with the weights in the caches, 72 from HBM (two
-// products; with two bf16 terms 65-67 in the same step). 6400 rows, fp32 weights: 0.88 ms = 1.1 PFLOP/s of fp16 products, 0.94 of the rate an 8192-cubed library
-// product reaches on the same card.
-template <int TM_, int PB_, int NSTG_, int D_>
-struct GenWide {
-  static constexpr int TM = TM_, PB = PB_, NSTG = NSTG_, TN = 4, WN = 4, D = D_;
-  static constexpr int BM = 16 * TM, BN = 256, NT = 256;
-  static constexpr int LPA = (2 * TM + 3) / 4;                // 1 KB A loads per wave and stage
-  static constexpr int STG = 2 * TM * 1024;
-  static constexpr int LDS = NSTG * STG;
+// products; with two bf16 terms 65-67 in the same step). 6400 rows, fp32 weights: 0.88 ms = 1.1 PFLOP/s of fp16
+// products, 0.94 of the rate an 8192-cubed library product reaches on the same card.
+template <int TM, int PB, int NSTG, int D>
+struct GenWide : WideTile<TM, 4, 2, PB, NSTG, D> {
+  static constexpr int WN = 4;
 };
 
 // Top-K lists of a 64 x 128 tile staged in LDS: 4 threads per row, 32 interleaved columns each, K rounds of a
@@ -339,87 +334,22 @@ __global__ __launch_bounds__(C::NT, 2) void k_gen(Split16 a, Split16 w, GenParam
 
 template <class C>
 __global__ __launch_bounds__(C::NT, 2) void k_gen_wide(Split16 a, Split16 w, GenParams p, int nm, int nblocks) {
-  constexpr int TM = C::TM, TN = C::TN, PB = C::PB, NSTG = C::NSTG, D = C::D;
+  constexpr int TM = C::TM, TN = C::TN, PB = C::PB;
   __shared__ __attribute__((aligned(16))) char smem[C::LDS];
   const int L = xcd_remap(blockIdx.x, nblocks);
   const int mt = L % nm, nt = L / nm;
   const int m0 = mt * C::BM, n0 = nt * C::BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  // A blocks (row block, then term) of a stage: load i of a wave moves block wave + 4 i (past the last: the last
-  // again); row blocks past the operand's last re-read that (those rows are never stored), as do weight
-  // rows past the packed matrix
   const int nrb = (a.rows + 15) / 16, kb = a.kblocks;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.base, (uint32_t)nrb * kb * 2048u);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(w.base, (uint32_t)(w.rows / 16) * kb * (PB * 1024u));
   uint32_t aoff[C::LPA], woff[TN];
-  int alds[C::LPA];
-#pragma unroll
-  for (int i = 0; i < C::LPA; ++i) {
-    const int q = min(wave + 4 * i, 2 * TM - 1);
-    aoff[i] = (uint32_t)min(m0 / 16 + q / 2, nrb - 1) * kb * 2048u + (q & 1) * 1024u + lane * 16u;
-    alds[i] = q * 1024;
-  }
+  wide_rows<C>(m0, nrb, kb, aoff);
 #pragma unroll
   for (int y = 0; y < TN; ++y)
     woff[y] = (uint32_t)min(n0 / 16 + wave * TN + y, w.rows / 16 - 1) * kb * (PB * 1024u) + lane * 16u;
-  auto issue_a = [&](int st) {       // stages past the last re-load it into a buffer that is never read
-    char* sb = smem + (st % NSTG) * C::STG;
-    const uint32_t ks = (uint32_t)min(st, kb - 1);
-#pragma unroll
-    for (int i = 0; i < C::LPA; ++i) dma16(ra, sb + alds[i], aoff[i], ks * 2048u);
-  };
-  // stages past the last read zeros, so the loop runs whole groups of D stages (the A buffer then holds a copy
-  // of the last stage: finite or, where the operand is not, as in the products before)
-  uint4 wr[D][TN][PB];
-  auto load_w = [&](int st, uint4 (&r)[TN][PB]) {
-    const bool on = st < kb;
-#pragma unroll
-    for (int y = 0; y < TN; ++y)
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb)
-        r[y][pb] = buf_load16s(rw, on ? woff[y] : kPastEnd, on ? (uint32_t)(st * PB + pb) * 1024u : 0u);
-  };
-
   f32x4 c0[TM][TN], c1[TM][TN];
-#pragma unroll
-  for (int x = 0; x < TM; ++x)
-#pragma unroll
-    for (int y = 0; y < TN; ++y) c0[x][y] = c1[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int d = 0; d < NSTG - 1; ++d) issue_a(d);
-#pragma unroll
-  for (int d = 0; d < D - 1; ++d) load_w(d, wr[d]);
-  for (int st0 = 0; st0 < kb; st0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int st = st0 + d;
-      // A(st) has landed when at most the NSTG - 2 younger stages' A loads are outstanding (weights of younger
-      // stages are in the count too, which only waits longer); then a bare barrier, as in k_gen
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTG - 2) * C::LPA));
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      load_w(st + D - 1, wr[(d + D - 1) % D]);
-      issue_a(st + NSTG - 1);
-      const char* base = smem + (st % NSTG) * C::STG + lane * 16;
-#pragma unroll
-      for (int x = 0; x < TM; ++x) {
-        const f16x8 ah = *(const f16x8*)(base + x * 2048), al = *(const f16x8*)(base + x * 2048 + 1024);
-#pragma unroll
-        for (int y = 0; y < TN; ++y) c0[x][y] = mfma_f16(wr[d][y][0], ah, c0[x][y]);
-#pragma unroll
-        for (int y = 0; y < TN; ++y) c1[x][y] = mfma_f16(wr[d][y][0], al, c1[x][y]);
-        if constexpr (PB == 2) {
-#pragma unroll
-          for (int y = 0; y < TN; ++y) c1[x][y] = mfma_f16(wr[d][y][PB - 1], ah, c1[x][y]);
-        }
-      }
-    }
-  }
-  // every load (including the re-loads past the end) has landed before the epilogue reuses the buffers
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  __syncthreads();
+  wide_main<C>(smem, make_rsrc(a.base, (uint32_t)nrb * kb * 2048u), aoff,
+               make_rsrc(w.base, (uint32_t)(w.rows / 16) * kb * (PB * 1024u)), woff, kb, c0, c1);
   gen_epilogue<C>(smem, p, a.rows, w.rows, m0, n0, 0, wave, c0, c1);
 }
 

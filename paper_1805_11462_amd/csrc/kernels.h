@@ -8,56 +8,17 @@
 
 namespace onmt {
 
-// K segments of GEMM operands are padded to multiples of this many elements; every tile's K stage
-// (32, 64 or 128 elements) divides it, so a stage never straddles two segments.
+// Model-size refusals count K segments padded to multiples of this many elements.
 constexpr int kSegK = 128;
 
-// bf16 products carry each fp32 activation as this many bf16 terms (RNE of the value, then of each
-// remainder), ~24 significant bits: the products see the fp32 value itself.
-constexpr int kPlanes = 3;
-
-// One K-segment of a GEMM's A operand: A[r, off + k] = base[map(r) * ld + k] for k < width,
-// 0 for width <= k < kpad. map(r) = idx ? idx[r] : r. The buffer must be smaller than 2 GiB.
-struct Seg {
-  const void* base;
-  const int32_t* idx;
-  int rows;      // rows in the source buffer (reads are bounded by rows * ld elements)
-  int ld;
-  int width;
-  int kpad;
-  int bf16;      // 1: base holds bf16 values (exact operands)
-  const void* lo;   // bf16 products only: base, lo and lo2 are the kPlanes bf16 term planes of fp32 values
-  const void* lo2;  // (bf16 = 1, width a multiple of 8); the operand is their sum, as if split on load
-};
-
-struct AOp {
-  Seg seg[3];
-  int nseg;
-  int M;
-};
-
-// Packed weight matrix [Np, Kp], K contiguous. Np is a multiple of 128, Kp of kSegK.
-struct BOp {
-  const void* W;
-  int Np;
-  int Kp;
-};
-
-// Plain store epilogue: out[r, n] = act(acc + bias[n]) for n < ncols. act: 0 none, 1 tanh.
-// Optionally (hi != nullptr) the same values split into the bf16 term planes hi, lo, lo2 [rows, ld_hl]
-// for columns n < ncols_hl (columns past ncols hold act(0), zero for the tanh stores), and (s16 != nullptr)
-// as a two-term fp16 operand whose row r0_16 + r holds columns n < 32 kb16.
+// Plain store epilogue: out[r, n] = act(acc + bias[n]) for n < ncols. act: 0 none, 1 tanh. Optionally
+// (s16 != nullptr) also as a two-term fp16 operand whose row r0_16 + r holds columns n < 32 kb16 (zeros past ncols).
 struct StoreParams {
   const float* bias;
   float* out;
   int ldo;
   int ncols;
   int act;
-  uint16_t* hi;
-  uint16_t* lo;
-  int ld_hl;
-  int ncols_hl;
-  uint16_t* lo2;
   uint16_t* s16;
   int kb16, r0_16;
 };
@@ -77,18 +38,14 @@ struct LstmParams {
   float* h_out;
   float* c_out;
   int ld_out;
-  uint16_t* h_hi;               // optional bf16 term planes of h_out (row stride ld_hl)
-  uint16_t* h_lo;
-  int ld_hl;
-  uint16_t* h_lo2;
   float* y_out;                 // optional layer output row b * y_S + y_s, column offset y_col0
   int ld_y, y_S, y_s, y_col0;
   const int32_t* lens;          // optional: GEMM row b is active iff y_s < lens[b]
   int H;                        // real units
   uint16_t* h16;                // optional two-term copy of h_out (kb16 blocks of 32 columns)
   int kb16;
-  uint16_t* y16;                // optional two-term copy of y_out
-  int y_kb16;
+  uint16_t* y16;                // optional two-term copy of the layer output, row y_r0 + b, columns as y_out
+  int y_kb16, y_r0;
 };
 
 // Operands of the few-row GEMMs: A rows in up to two two-term segments (row r of segment s is row
@@ -114,14 +71,14 @@ struct ThinW {
   int kb0;
 };
 
-// Two LSTM GEMM problems for one launch (nm/nt/nb are filled in by the launcher).
-struct LstmPair {
-  AOp a[2];
-  BOp b[2];
+// Two LSTM problems for one launch (nm/nt/nb0 are filled in by the launcher).
+struct ThinPair {
+  ThinA a[2];
+  ThinW w[2];
   LstmParams p[2];
   int nm[2];     // row tiles
   int nt[2];     // tiles
-  int nb[2];     // blocks (problem 0's rounded up to a multiple of 8)
+  int nb0;       // blocks of problem 0, rounded up to a multiple of 8
 };
 
 // Generator epilogue: per (row, column tile) max and sum of exp, and the raw logits or per-tile top-K lists.
@@ -148,8 +105,10 @@ struct GenParams {
   float* pfmax;                 // [M, ntiles]
 };
 
-// w_terms: fp16 terms per weight (1 or 2). thin_store: StoreParams without bf16 term planes.
+// w_terms: fp16 terms per weight (1 or 2).
 hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st);
+// Two problems of segment counts 1+1, 1+2 or 2+2 in one launch.
+hipError_t thin_lstm2(int w_terms, const ThinPair& q, hipStream_t st);
 hipError_t thin_store(int w_terms, const ThinA& a, const ThinW& w, const StoreParams& p, hipStream_t st);
 
 // A decoder state of N rows: fp32 h, c [L, N, H] and feed [N, H], and the two-term copies of h (one operand of
@@ -170,14 +129,27 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st);
 
-// kShapeMid: 32 x 64 tiles with two waves splitting K, for bf16 LSTM GEMMs of a few hundred rows (fp32 maps
-// it to the thin tile); when every A segment is a pre-split plane pair the operands go straight into LDS.
-enum GemmShape { kShapeWide = 0, kShapeSplitK = 1, kShapeSplitKThin = 2, kShapeMid = 3 };
+// M rows of an operand of `rows` rows and kblocks blocks of `terms` terms: the first M, or (idx) rows idx[m], clamped
+// to the operand; aexp (optional): power of two added to the columns' for each operand row.
+struct WideA {
+  const void* base;
+  const int32_t* idx;
+  const int32_t* aexp;
+  int M;
+  int rows;
+  int kblocks;
+  int terms;
+};
+// out[row(m), n] = product + bias[n] for n < ncols; row(m) = m, or (B > 0) (m % B) * S + m / B.
+struct WideOut {
+  const float* bias;
+  float* out;
+  int ldo;
+  int ncols;
+  int B, S;
+};
+hipError_t wide_store(const WideA& a, const ThinW& w, int w_terms, const WideOut& p, hipStream_t st);
 
-hipError_t gemm_store(int bf16, int shape, const AOp& a, const BOp& b, const StoreParams& p, hipStream_t st);
-hipError_t gemm_lstm(int bf16, int shape, const AOp& a, const BOp& b, const LstmParams& p, hipStream_t st);
-// Two independent thin-shape LSTM GEMMs in one launch (segment counts 1+1, 1+2 or 2+2).
-hipError_t gemm_lstm2(int bf16, int shape, const LstmPair& g, hipStream_t st);
 // The generator: a two-term operand of M = a.rows rows against the vocabulary's weights (w.rows = ceil128(V)
 // rows of w_terms terms).
 hipError_t gemm_gen(const Split16& a, const Split16& w, int w_terms, const GenParams& p, hipStream_t st);
@@ -271,11 +243,12 @@ hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, con
 
 // Device-side input validation (see beam.hip): error kinds recorded in the host-visible word.
 enum { kErrLength = 1, kErrSourceId = 2, kErrToken = 3, kErrParent = 4 };
-// clean [B, S] = src with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S];
-// rowmap [S, B] = b * S + s.
+// clean [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S].
 hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
-                        int32_t* rowmap, int32_t* err, hipStream_t st);
+                        int32_t* err, hipStream_t st);
+
 hipError_t fill_f32(float* dst, size_t n, float v, hipStream_t st);
-hipError_t copy_cols(const float* src, int ld_src, float* dst, int ld_dst, int rows, int ncols, hipStream_t st);
+// Zeros in columns width .. 32 kblocks of every row (rows rounded up to whole blocks) of up to two two-term operands.
+hipError_t zero_pad16(uint16_t* a, uint16_t* b, int rows, int width, int kblocks, hipStream_t st);
 
 }  // namespace onmt

@@ -1,5 +1,6 @@
 // C ABI of libonmt: validation, weight packing, workspace carving and the encode / decode-step /
-// beam-search orchestration. All arithmetic runs in the kernels of gemm.hip, attention.hip and beam.hip.
+// beam-search orchestration. All arithmetic runs in the kernels of thin.hip, wide.hip, gen.hip, attention.hip and
+// beam.hip.
 
 #include <hip/hip_runtime.h>
 
@@ -54,42 +55,14 @@ struct Carver {
   }
 };
 
-struct Packed {      // packed weight matrix inside the model buffer
-  const void* W = nullptr;
-  int Np = 0, Kp = 0;
-  size_t off = 0;
-};
-
-Seg seg(const void* base, const int32_t* idx, int rows, int ld, int width, int kpad, int bf16) {
-  Seg s;
-  s.base = base;
-  s.idx = idx;
-  s.rows = rows;
-  s.ld = ld;
-  s.width = width;
-  s.kpad = kpad;
-  s.bf16 = bf16;
-  s.lo = nullptr;
-  s.lo2 = nullptr;
-  return s;
-}
-
-// Weights of a few-row GEMM: `rows` (a multiple of 128) rows in fragment blocks of 1 or 2 fp16 terms and each
-// row's power of two, inside the model buffer.
+// A weight matrix (rows a multiple of 128) or embedding table in fragment blocks of 1 or 2 fp16 terms, with each row's
+// power of two, inside the model buffer.
 struct ThinMat {
   size_t off = 0, exp_off = 0;
   int rows = 0, kblocks = 0;
   const char* base = nullptr;
   ThinW w(int kb0 = 0) const { return ThinW{base + off, (const int32_t*)(base + exp_off), rows, kblocks, kb0}; }
 };
-
-BOp bop(const Packed& p) {
-  BOp b;
-  b.W = p.W;
-  b.Np = p.Np;
-  b.Kp = p.Kp;
-  return b;
-}
 
 struct Dims {
   int L, ndir, Hd, Hm, H, E, Vs, Vt;
@@ -99,8 +72,7 @@ struct Dims {
   int attn;            // ONMT_ATTN_GENERAL / _DOT / _CONCAT
   // fp16 terms per weight of the two-term products (split16.h): bf16 weights fit one, fp32 weights take two
   int wterms;
-  // Every K segment of a GEMM operand is padded to a multiple of kSegK so that no K stage of any tile
-  // shape straddles two segments.
+  // columns as the model-size refusals count them
   int pad(int w) const { return ceil_to(w, kSegK); }
   int kb(int w) const { return ceil_to(w, kFragK) / kFragK; }     // 32-column blocks of a two-term operand
 };
@@ -208,19 +180,18 @@ struct onmt_model {
   onmt_config cfg;
   Dims d;
   char* dev = nullptr;
-  const void* E_src = nullptr;
-  const void* E_tgt = nullptr;
+  ThinMat E_src, E_tgt;                    // rows carry the power of two that undoes their own scale
   // Encoder. Bidirectional: every layer has an input projection (both directions stacked) and a recurrent
   // matrix per direction. Unidirectional: layer 0 likewise; layers >= 1 keep [input | recurrent] in one
   // matrix, so that they can run one timestep behind the layer below in the same launch.
-  std::vector<Packed> enc_x;               // per layer: both directions stacked [ndir * 4 Hd_pad, pad(in)]
+  std::vector<ThinMat> enc_x;              // per layer: both directions stacked [ndir * 4 Hd_pad, in]
   std::vector<const float*> enc_bias;      // per layer [ndir * 4 Hd_pad]
-  std::vector<Packed> enc_h;               // per layer * ndir: [4 Hd_pad, pad(Hd)]
-  std::vector<Packed> enc_xh;              // unidirectional layers >= 1: [4 Hd_pad, pad(in) + pad(Hd)]
-  Packed dec_emb;                          // layer 0's embedding columns (for emb_gates) [4 H_pad, pad(E)]
+  std::vector<ThinMat> enc_h;              // per layer * ndir: [4 Hd_pad, Hd]
+  std::vector<ThinMat> enc_xh;             // unidirectional layers >= 1: [4 Hd_pad, [in | Hd]]
+  ThinMat dec_emb;                         // decoder layer 0's embedding columns (for emb_gates) [4 H_pad, E]
   std::vector<ThinMat> dec_t;              // per layer, columns [feed | recurrent] or [below | recurrent]
   std::vector<const float*> dec_bias;      // per layer [4 H_pad]
-  Packed W_a;                              // memory side of the score: general W_a, concat's memory columns
+  ThinMat W_a;                             // memory side of the score: general W_a, concat's memory columns
   ThinMat W_q;                             // concat: the query columns of W_a
   const float* v_a = nullptr;              // concat [H]
   ThinMat W_c;                             // columns [context | query]
@@ -260,16 +231,6 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
   Dims d;
   dims_of(c, &d);
   Carver cv;
-  auto mat = [&](int Np, int Kp) {
-    Packed p;
-    cv.off = align_up(cv.off);
-    p.off = cv.off;
-    p.Np = Np;
-    p.Kp = Kp;
-    cv.off += (size_t)Np * Kp * d.esz;
-    if (mats) mats->push_back((uint64_t)Np * Kp * d.esz);
-    return p;
-  };
   auto vec = [&](size_t n) {
     cv.off = align_up(cv.off);
     size_t o = cv.off;
@@ -288,35 +249,35 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
     if (mats) mats->push_back(limit);
     return t;
   };
-  Packed esrc = mat(d.Vs, d.E);
-  std::vector<Packed> ex, eh, exh;
-  std::vector<ThinMat> dt;
+  auto lim = [&](int rows, int kp) { return (uint64_t)rows * kp * d.esz; };
+  const ThinMat esrc = thin(d.Vs, d.kb(d.E), lim(d.Vs, d.E));
+  std::vector<ThinMat> ex, eh, exh, dt;
   std::vector<size_t> eb, db;
   for (int l = 0; l < d.L; ++l) {
-    const int in = l == 0 ? d.E : d.Hm;
+    const int in = l == 0 ? d.E : d.Hm, r = 4 * d.Hd_pad;
     if (d.ndir == 1 && l > 0) {
-      ex.push_back(Packed{});
-      eh.push_back(Packed{});
-      exh.push_back(mat(4 * d.Hd_pad, d.pad(in) + d.pad(d.Hd)));
+      ex.push_back(ThinMat{});
+      eh.push_back(ThinMat{});
+      exh.push_back(thin(r, d.kb(in) + d.kb(d.Hd), lim(r, d.pad(in) + d.pad(d.Hd))));
     } else {
-      ex.push_back(mat(d.ndir * 4 * d.Hd_pad, d.pad(in)));
-      for (int dir = 0; dir < d.ndir; ++dir) eh.push_back(mat(4 * d.Hd_pad, d.pad(d.Hd)));
-      exh.push_back(Packed{});
+      ex.push_back(thin(d.ndir * r, d.kb(in), lim(d.ndir * r, d.pad(in))));
+      for (int dir = 0; dir < d.ndir; ++dir) eh.push_back(thin(r, d.kb(d.Hd), lim(r, d.pad(d.Hd))));
+      exh.push_back(ThinMat{});
     }
-    eb.push_back(vec((size_t)d.ndir * 4 * d.Hd_pad));
+    eb.push_back(vec((size_t)d.ndir * r));
   }
-  Packed etgt = mat(d.Vt, d.E);
+  const ThinMat etgt = thin(d.Vt, d.kb(d.E), lim(d.Vt, d.E));
   for (int l = 0; l < d.L; ++l) {
     const uint64_t kp = (l == 0 ? d.pad(d.E) : 0) + 2 * d.pad(d.H);
     dt.push_back(thin(4 * d.H_pad, 2 * d.kb(d.H), 4 * d.H_pad * kp * d.esz));
     db.push_back(vec((size_t)4 * d.H_pad));
   }
-  Packed demb = mat(4 * d.H_pad, d.pad(d.E));
-  Packed wa = d.attn != ONMT_ATTN_DOT ? mat(ceil_to(d.H, 128), d.pad(d.Hm)) : Packed{};
+  const ThinMat demb = thin(4 * d.H_pad, d.kb(d.E), lim(4 * d.H_pad, d.pad(d.E)));
   const int hr = ceil_to(d.H, 128);
-  ThinMat wq = d.attn == ONMT_ATTN_CONCAT ? thin(hr, d.kb(d.H), (uint64_t)hr * d.pad(d.H) * d.esz) : ThinMat{};
+  const ThinMat wa = d.attn != ONMT_ATTN_DOT ? thin(hr, d.kb(d.Hm), lim(hr, d.pad(d.Hm))) : ThinMat{};
+  ThinMat wq = d.attn == ONMT_ATTN_CONCAT ? thin(hr, d.kb(d.H), lim(hr, d.pad(d.H))) : ThinMat{};
   const size_t va = d.attn == ONMT_ATTN_CONCAT ? vec(d.H) : 0;
-  ThinMat wc = thin(hr, d.kb(d.Hm) + d.kb(d.H), (uint64_t)hr * (d.pad(d.Hm) + d.pad(d.H)) * d.esz);
+  ThinMat wc = thin(hr, d.kb(d.Hm) + d.kb(d.H), lim(hr, d.pad(d.Hm) + d.pad(d.H)));
   cv.off = align_up(cv.off);
   const size_t ws_off = cv.off;
   const Split16 ws{nullptr, ceil_to(d.Vt, 128), d.kb(d.H)};
@@ -330,24 +291,20 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
   const size_t total = align_up(cv.off);
   if (m) {
     char* base = m->dev;
-    auto fix = [&](Packed p) {
-      p.W = base + p.off;
-      return p;
-    };
-    m->E_src = base + esrc.off;
-    m->E_tgt = base + etgt.off;
-    for (auto& p : ex) m->enc_x.push_back(fix(p));
-    for (auto o : eb) m->enc_bias.push_back((const float*)(base + o));
-    for (auto& p : eh) m->enc_h.push_back(fix(p));
-    for (auto& p : exh) m->enc_xh.push_back(fix(p));
     auto fix_thin = [&](ThinMat t) {
       t.base = base;
       return t;
     };
-    m->dec_emb = fix(demb);
+    m->E_src = fix_thin(esrc);
+    m->E_tgt = fix_thin(etgt);
+    for (auto& t : ex) m->enc_x.push_back(fix_thin(t));
+    for (auto o : eb) m->enc_bias.push_back((const float*)(base + o));
+    for (auto& t : eh) m->enc_h.push_back(fix_thin(t));
+    for (auto& t : exh) m->enc_xh.push_back(fix_thin(t));
+    m->dec_emb = fix_thin(demb);
     for (auto& t : dt) m->dec_t.push_back(fix_thin(t));
     for (auto o : db) m->dec_bias.push_back((const float*)(base + o));
-    if (d.attn != ONMT_ATTN_DOT) m->W_a = fix(wa);
+    if (d.attn != ONMT_ATTN_DOT) m->W_a = fix_thin(wa);
     if (d.attn == ONMT_ATTN_CONCAT) {
       m->W_q = fix_thin(wq);
       m->v_a = (const float*)(base + va);
@@ -368,33 +325,23 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
 struct HostImage {
   std::vector<char> buf;
   bool bf16;
-  void put(size_t off, size_t idx, float v) {
-    if (bf16) {
-      ((uint16_t*)(buf.data() + off))[idx] = f32_to_bf16_bits(v);
-    } else {
-      ((float*)(buf.data() + off))[idx] = v;
-    }
-  }
   void putf(size_t off, size_t idx, float v) { ((float*)(buf.data() + off))[idx] = v; }
 };
 
-// Copy columns [c0, c0 + w) of src rows into packed row `prow` at packed column pc0.
-void pack_row(HostImage& img, const Packed& p, int prow, int pc0, const float* src_row, int c0, int w) {
-  for (int j = 0; j < w; ++j) img.put(p.off, (size_t)prow * p.Kp + pc0 + j, src_row[c0 + j]);
-}
-
-// Row r of a few-row GEMM's matrix: columns w[i] values of src[i] from K block kb[i] on, under one row exponent.
+// Row r of a matrix or embedding table: columns w[i] values of src[i] from K block kb[i] on, under one row exponent.
 struct RowPart {
   const float* src;
   int w, kb;
 };
-void pack_thin(HostImage& img, const ThinMat& t, int terms, int r, const std::vector<RowPart>& parts) {
+void pack_thin(HostImage& img, const ThinMat& t, int terms, int r, const std::vector<RowPart>& parts,
+               bool table = false) {
   std::vector<float> row((size_t)t.kblocks * kFragK, 0.f);
   for (const RowPart& q : parts)
     for (int j = 0; j < q.w; ++j)
       row[(size_t)q.kb * kFragK + j] = img.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(q.src[j])) : q.src[j];
   const int e = host_row_exp(row.data(), (int)row.size());
-  ((int32_t*)(img.buf.data() + t.exp_off))[r] = -(kActExp + e);
+  // a product column is undone by -(kActExp + e); a table's rows take the place of activations scaled by kActExp
+  ((int32_t*)(img.buf.data() + t.exp_off))[r] = table ? kActExp - e : -(kActExp + e);
   host_pack_row((uint16_t*)(img.buf.data() + t.off), r, 0, t.kblocks, terms, row.data(), (int)row.size(), e);
 }
 
@@ -493,8 +440,7 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   // E_src
   {
     const float* s = host_weights[wi++];
-    const size_t o = off_of(m->E_src);
-    for (size_t i = 0; i < (size_t)d.Vs * d.E; ++i) img.put(o, i, s[i]);
+    for (int r = 0; r < d.Vs; ++r) pack_thin(img, m->E_src, d.wterms, r, {{s + (size_t)r * d.E, d.E, 0}}, true);
   }
   for (int l = 0; l < d.L; ++l) {
     const int in = l == 0 ? d.E : d.Hm;
@@ -508,11 +454,10 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
           const float* row = W + (size_t)(g * d.Hd + u) * (in + d.Hd);
           const int xr = dir * 4 * d.Hd_pad + gate_row(g, u);
           if (joint) {   // segments [layer below | recurrent]
-            pack_row(img, m->enc_xh[l], xr, 0, row, 0, in);
-            pack_row(img, m->enc_xh[l], xr, d.pad(in), row, in, d.Hd);
+            pack_thin(img, m->enc_xh[l], d.wterms, xr, {{row, in, 0}, {row + in, d.Hd, d.kb(in)}});
           } else {
-            pack_row(img, m->enc_x[l], xr, 0, row, 0, in);
-            pack_row(img, m->enc_h[l * d.ndir + dir], gate_row(g, u), 0, row, in, d.Hd);
+            pack_thin(img, m->enc_x[l], d.wterms, xr, {{row, in, 0}});
+            pack_thin(img, m->enc_h[l * d.ndir + dir], d.wterms, gate_row(g, u), {{row + in, d.Hd, 0}});
           }
           img.putf(bo, xr, bvec[g * d.Hd + u]);
         }
@@ -520,8 +465,7 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   }
   {
     const float* s = host_weights[wi++];
-    const size_t o = off_of(m->E_tgt);
-    for (size_t i = 0; i < (size_t)d.Vt * d.E; ++i) img.put(o, i, s[i]);
+    for (int r = 0; r < d.Vt; ++r) pack_thin(img, m->E_tgt, d.wterms, r, {{s + (size_t)r * d.E, d.E, 0}}, true);
   }
   for (int l = 0; l < d.L; ++l) {
     const float* W = host_weights[wi++];
@@ -533,7 +477,7 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
         const float* row = W + (size_t)(g * d.H + u) * (in + d.H);
         const int pr = gate_row(g, u);
         if (l == 0) {   // [embedding] apart; [feed | recurrent]
-          pack_row(img, m->dec_emb, pr, 0, row, 0, d.E);
+          pack_thin(img, m->dec_emb, d.wterms, pr, {{row, d.E, 0}});
           pack_thin(img, m->dec_t[l], d.wterms, pr, {{row + d.E, d.H, 0}, {row + d.E + d.H, d.H, kb}});
         } else {        // [layer below | recurrent]
           pack_thin(img, m->dec_t[l], d.wterms, pr, {{row, d.H, 0}, {row + d.H, d.H, kb}});
@@ -544,12 +488,12 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   {
     if (d.attn == ONMT_ATTN_GENERAL) {
       const float* Wa = host_weights[wi++];
-      for (int r = 0; r < d.H; ++r) pack_row(img, m->W_a, r, 0, Wa + (size_t)r * d.Hm, 0, d.Hm);
+      for (int r = 0; r < d.H; ++r) pack_thin(img, m->W_a, d.wterms, r, {{Wa + (size_t)r * d.Hm, d.Hm, 0}});
     } else if (d.attn == ONMT_ATTN_CONCAT) {   // columns [query | memory]
       const float* Wa = host_weights[wi++];
       for (int r = 0; r < d.H; ++r) {
         pack_thin(img, m->W_q, d.wterms, r, {{Wa + (size_t)r * (d.H + d.Hm), d.H, 0}});
-        pack_row(img, m->W_a, r, 0, Wa + (size_t)r * (d.H + d.Hm), d.H, d.Hm);
+        pack_thin(img, m->W_a, d.wterms, r, {{Wa + (size_t)r * (d.H + d.Hm) + d.H, d.Hm, 0}});
       }
       const float* va = host_weights[wi++];
       const size_t vo = off_of(m->v_a);
@@ -581,12 +525,8 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   hipError_t e = hipMemcpyAsync(dev_buf, img.buf.data(), m->image_bytes, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) {
     // decoder layer 0: the embedding columns of its packed matrix against every target embedding row
-    AOp a{};
-    a.M = d.Vt;
-    a.nseg = 1;
-    a.seg[0] = seg(m->E_tgt, nullptr, d.Vt, d.E, d.E, d.pad(d.E), d.bf16);
-    StoreParams sp{nullptr, m->emb_gates, 4 * d.H_pad, 4 * d.H_pad, 0};
-    e = gemm_store(d.bf16, kShapeWide, a, bop(m->dec_emb), sp, st);
+    const WideA a{m->E_tgt.w().base, nullptr, m->E_tgt.w().wexp, d.Vt, d.Vt, d.kb(d.E), d.wterms};
+    e = wide_store(a, m->dec_emb.w(), d.wterms, WideOut{nullptr, m->emb_gates, 4 * d.H_pad, 4 * d.H_pad, 0, 0}, st);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess) {
@@ -628,16 +568,20 @@ namespace {
 
 struct EncWs {
   int32_t* lens;
-  int32_t* src;
+  int32_t* src;      // [S, B] checked token ids
   float* memory;     // [B*S, Hm]
   float* keys;       // [B*S, H]: W_a m_s (general), the memory-side term of concat, the memory itself (dot)
   float* final_h;    // [L, B, H]
   float* final_c;
-  float* gx;         // [B*S, ndir * 4 Hd_pad]
-  float* y[2];       // [B*S, Hm]
-  float* hs[2];      // [max(ndir, L), B, Hd]: state after an even / odd timestep, one slot per direction or layer
+  float* gx;         // [S*B, ndir * 4 Hd_pad], row s * B + b
+  // Two-term operands of the layers' outputs (one layer writes y16[l & 1] while it reads the other), row s * B + b
+  uint16_t* y16[2];
+  // state after an even / odd timestep, one slot per layer and direction: h, c [slots, B, Hd] and h as an operand
+  float* hs[2];
   float* cs[2];
-  int32_t* rowmap;   // [S, B]: rowmap[s * B + b] = b * S + s (row of position s of sentence b)
+  uint16_t* hs16[2];
+  size_t hs_plane;   // halfwords of one slot of hs16
+  size_t zero_n;     // floats from hs[1] on that hold the zero state before the first step (hs[1], cs[1], hs16[1])
 };
 
 size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
@@ -652,11 +596,17 @@ size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
   t.final_h = c.take<float>((size_t)d.L * B * d.H);
   t.final_c = c.take<float>((size_t)d.L * B * d.H);
   t.gx = c.take<float>(BS * d.ndir * 4 * d.Hd_pad);
-  for (int i = 0; i < 2; ++i) t.y[i] = c.take<float>(BS * d.Hm);
-  const size_t slots = (size_t)(d.ndir > d.L ? d.ndir : d.L);
-  for (int i = 0; i < 2; ++i) t.hs[i] = c.take<float>(slots * B * d.Hd);
-  for (int i = 0; i < 2; ++i) t.cs[i] = c.take<float>(slots * B * d.Hd);
-  t.rowmap = c.take<int32_t>(BS);
+  for (int i = 0; i < 2; ++i) t.y16[i] = c.take<uint16_t>(split16_bytes(BS, d.kb(d.Hm), 2) / 2);
+  const size_t slots = (size_t)d.ndir * d.L;
+  t.hs_plane = split16_bytes(B, d.kb(d.Hd), 2) / 2;
+  size_t zero0 = 0;
+  for (int i = 0; i < 2; ++i) {
+    zero0 = align_up(c.off);
+    t.hs[i] = c.take<float>(slots * B * d.Hd);
+    t.cs[i] = c.take<float>(slots * B * d.Hd);
+    t.hs16[i] = c.take<uint16_t>(slots * t.hs_plane);
+  }
+  t.zero_n = (c.off - zero0) / sizeof(float);
   if (w) *w = t;
   return align_up(c.off);
 }
@@ -850,31 +800,12 @@ int check_ws_limits(const Dims& d, long long B, long long S, long long K, long l
   return ONMT_OK;
 }
 
-// Small-M GEMMs: the 16-row split-K tile unless the 32-row tile already gives this many workgroups
-// (measured on the decoder layers: more, smaller workgroups win while M is a few hundred rows).
-#ifndef ONMT_SMALL_M_TILES
-#define ONMT_SMALL_M_TILES 4096
-#endif
 // Unidirectional encoders with fewer rows than this run their layers as a wavefront (see encode_compute).
 constexpr int kWavefrontMaxRows = 256;
 
-int small_shape(int M, int Np) {
-  const long tiles32 = (long)((M + 31) / 32) * (Np / 64);
-  return tiles32 >= ONMT_SMALL_M_TILES ? kShapeSplitK : kShapeSplitKThin;
-}
-
-// LSTM GEMMs: bf16 models with at least this many rows use the 32-row two-way split-K tile.
-constexpr int kMidMinRows = 256;
-int lstm_shape(const Dims& d, int M, int Np) {
-  if (d.bf16 && M >= kMidMinRows) return kShapeMid;
-  return small_shape(M, Np);
-}
-
-// Copies src/len to the host, validates them, and uploads the token ids with every position at or beyond
-// its sentence's length replaced by 0 into clean_src (device, [B, S]), so no kernel gathers an embedding
-// row through an unchecked id.
+// Copies src/len to the host and validates them (one stream sync); *max_len is the longest length.
 int check_len_src(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, hipStream_t st,
-                  int* max_len, int32_t* clean_src, int32_t* rowmap) {
+                  int* max_len) {
   if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
   if (B < 1 || S < 1) return fail(ONMT_EINVAL, "B and S_max must be >= 1");
   if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
@@ -891,129 +822,122 @@ int check_len_src(const onmt_model* m, const int32_t* src, const int32_t* len, i
       if (v < 0 || v >= m->cfg.src_vocab) return fail(ONMT_EINVAL, "src[%d, %d] = %d outside [0, %d)", b, s, v, m->cfg.src_vocab);
     }
   }
-  for (int b = 0; b < B; ++b)
-    for (int s = hl[b]; s < S; ++s) hs[(size_t)b * S + s] = 0;
-  HIP_TRY(hipMemcpyAsync(clean_src, hs.data(), sizeof(int32_t) * hs.size(), hipMemcpyHostToDevice, st));
-  std::vector<int32_t> rm((size_t)B * S);
-  for (int s = 0; s < S; ++s)
-    for (int b = 0; b < B; ++b) rm[(size_t)s * B + b] = b * S + s;
-  HIP_TRY(hipMemcpyAsync(rowmap, rm.data(), sizeof(int32_t) * rm.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipStreamSynchronize(st));
   *max_len = mx;
   return ONMT_OK;
 }
 
 // Source ids and lengths, checked either on the host (ONMT_VALIDATE_HOST: copied over, one stream sync; the
-// longest length bounds the encoder's steps) or on the device (ONMT_VALIDATE_DEVICE: a kernel writes the
-// checked copies and records violations; the encoder then steps over all S_max positions, which the packed
-// padding leaves unchanged past each sentence's length). On return w.src, w.rowmap and (device mode)
-// w.lens hold the checked inputs; *lens_src is what encode_compute copies into w.lens (nullptr: in place).
+// longest length bounds the encoder's steps) or on the device (ONMT_VALIDATE_DEVICE: the kernel that writes the
+// working copies w.src and w.lens also records violations; the encoder then steps over all S_max positions, which
+// the packed padding leaves unchanged past each sentence's length).
 int checked_source(onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, hipStream_t st,
-                   int* max_len, const int32_t** lens_src) {
+                   int* max_len) {
   if (m->validation == ONMT_VALIDATE_DEVICE) {
     if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
     if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
-    HIP_TRY(sanitize_src(src, len, B, S, m->cfg.src_vocab, w.src, w.lens, w.rowmap, m->err_host, st));
     *max_len = S;
-    *lens_src = nullptr;
-    return ONMT_OK;
+  } else {
+    const int rc = check_len_src(m, src, len, B, S, st, max_len);
+    if (rc) return rc;
   }
-  *lens_src = len;
-  return check_len_src(m, src, len, B, S, st, max_len, w.src, w.rowmap);
+  HIP_TRY(sanitize_src(src, len, B, S, m->cfg.src_vocab, w.src, w.lens, m->err_host, st));
+  return ONMT_OK;
 }
 
-// Encoder compute on validated inputs (Section 2 encoder RNN; Tables 3-4 bidirectional; readings R2-R5).
-// len == nullptr: the lengths are already in w.lens (checked on the device).
-int encode_compute(onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, int max_len, const EncWs& w,
-                   hipStream_t st) {
+// Encoder compute on checked inputs in w.src and w.lens (Section 2 encoder RNN; Tables 3-4 bidirectional; readings
+// R2-R5). Positions are the outer index of every per-position operand (row s * B + b), so a step reads whole
+// fragment blocks of consecutive rows.
+int encode_compute(onmt_model* m, int B, int S, int max_len, const EncWs& w, hipStream_t st) {
   const Dims& d = m->d;
-  const int BS = B * S;
-  (void)src;   // the validated, pad-cleaned ids are already in w.src
-  if (len) HIP_TRY(hipMemcpyAsync(w.lens, len, sizeof(int32_t) * B, hipMemcpyDeviceToDevice, st));
-  HIP_TRY(fill_f32(w.memory, (size_t)BS * d.Hm, 0.f, st));
+  const int BS = B * S, kbm = d.kb(d.Hm), kbd = d.kb(d.Hd);
   const int gxw = d.ndir * 4 * d.Hd_pad;
   const size_t SB = (size_t)B * d.Hd;       // one state slot
-  // Recurrent GEMM of (layer l, direction dir) at position s, its step-th step, state slot `slot`: the
-  // state after step k goes to buffer k & 1 and step k reads the other buffer (buffer 1 holds the zero
-  // state before step 0).
+  const bool uni = d.ndir == 1, keys = d.attn != ONMT_ATTN_DOT;
+  HIP_TRY(fill_f32(w.hs[1], w.zero_n, 0.f, st));
+  if (max_len < S) {   // positions no step reaches: memory 0, and 0 as the keys' operand
+    HIP_TRY(fill_f32(w.memory, (size_t)BS * d.Hm, 0.f, st));
+    if (keys) HIP_TRY(fill_f32((float*)w.y16[(d.L - 1) & 1], split16_bytes(BS, kbm, 2) / 4, 0.f, st));
+  }
+  HIP_TRY(zero_pad16(w.y16[0], d.L > 1 ? w.y16[1] : nullptr, BS, d.Hm, kbm, st));
+  // Recurrent product of (layer l, direction dir) at position s, its step-th step: the state after step k goes to
+  // buffer k & 1 and step k reads the other buffer (buffer 1 holds the zero state before step 0); after the last
+  // step it goes to the final states.
   // Unidirectional layers >= 1 keep [W_x | W_h] in one matrix: `joint` steps read [y_{l-1} at s | h]
   // against all of it; otherwise the step reads h against the W_h columns and adds the projection gx.
-  const bool uni = d.ndir == 1;
-  auto recurrent = [&](int l, int dir, int s, int step, int slot, bool joint, AOp& r, BOp& wb, LstmParams& lp) {
-    const int pin = (step + 1) & 1;
-    const float* hp = w.hs[pin] + slot * SB;
-    const float* cp = w.cs[pin] + slot * SB;
-    r = AOp{};
+  auto recurrent = [&](int l, int dir, int s, int step, bool joint, ThinA& r, ThinW& wb, LstmParams& lp) {
+    const int pin = (step + 1) & 1, slot = l * d.ndir + dir;
+    r = ThinA{};
     r.M = B;
+    ThinSeg h{w.hs16[pin] + slot * w.hs_plane, nullptr, 0, kbd, (uint32_t)(w.hs_plane * 2)};
     if (joint) {   // [output of layer l-1 at position s | h]
       r.nseg = 2;
-      r.seg[0] = seg(w.y[(l - 1) & 1], w.rowmap + (size_t)s * B, BS, d.Hm, d.Hm, d.pad(d.Hm), 0);
-      r.seg[1] = seg(hp, nullptr, B, d.Hd, d.Hd, d.pad(d.Hd), 0);
-      wb = bop(m->enc_xh[l]);
+      r.seg[0] = ThinSeg{w.y16[(l - 1) & 1], nullptr, s * B, kbm, (uint32_t)split16_bytes(BS, kbm, 2)};
+      r.seg[1] = h;
+      wb = m->enc_xh[l].w();
     } else {       // h, plus the precomputed input projection
       r.nseg = 1;
-      r.seg[0] = seg(hp, nullptr, B, d.Hd, d.Hd, d.pad(d.Hd), 0);
-      if (uni && l > 0) {   // the W_h columns of the joint matrix (row stride unchanged)
-        wb = bop(m->enc_xh[l]);
-        wb.W = (const char*)wb.W + (size_t)d.pad(d.Hm) * d.esz;
-      } else {
-        wb = bop(m->enc_h[l * d.ndir + dir]);
-      }
+      r.seg[0] = h;
+      wb = uni && l > 0 ? m->enc_xh[l].w(kbm) : m->enc_h[slot].w();
     }
     lp = LstmParams{};
     lp.bias = joint ? m->enc_bias[l] : nullptr;
     lp.gx = joint ? nullptr : w.gx;
     lp.ld_gx = gxw;
     lp.gx_col0 = dir * 4 * d.Hd_pad;
-    lp.gx_S = S;
-    lp.gx_s = s;
-    lp.c_in = cp;
-    lp.c_idx = nullptr;
+    lp.gx_S = 1;
+    lp.gx_s = s * B;
+    lp.c_in = w.cs[pin] + slot * SB;
     lp.ld_c = d.Hd;
-    lp.h_in = hp;
+    lp.h_in = w.hs[pin] + slot * SB;
     lp.ld_h_in = d.Hd;
-    lp.h_out = w.hs[pin ^ 1] + slot * SB;
-    lp.c_out = w.cs[pin ^ 1] + slot * SB;
-    lp.ld_out = d.Hd;
-    lp.y_out = (l == d.L - 1) ? w.memory : w.y[l & 1];
+    if (step == max_len - 1) {
+      const size_t o = (size_t)l * B * d.H + (size_t)dir * d.Hd;
+      lp.h_out = w.final_h + o;
+      lp.c_out = w.final_c + o;
+      lp.ld_out = d.H;
+    } else {
+      lp.h_out = w.hs[pin ^ 1] + slot * SB;
+      lp.c_out = w.cs[pin ^ 1] + slot * SB;
+      lp.ld_out = d.Hd;
+      lp.h16 = w.hs16[pin ^ 1] + slot * w.hs_plane;
+      lp.kb16 = kbd;
+    }
+    const bool top = l == d.L - 1;
+    lp.y_out = top ? w.memory : nullptr;
     lp.ld_y = d.Hm;
     lp.y_S = S;
     lp.y_s = s;
     lp.y_col0 = dir * d.Hd;
+    lp.y16 = !top || keys ? w.y16[l & 1] : nullptr;
+    lp.y_kb16 = kbm;
+    lp.y_r0 = s * B;
     lp.lens = w.lens;
     lp.H = d.Hd;
   };
-  auto run_one = [&](int l, int dir, int s, int step, int slot, bool joint) -> int {
-    AOp r;
-    BOp wb;
+  auto run_one = [&](int l, int dir, int s, int step, bool joint) -> int {
+    ThinA r;
+    ThinW wb;
     LstmParams lp;
-    recurrent(l, dir, s, step, slot, joint, r, wb, lp);
-    HIP_TRY(gemm_lstm(d.bf16, lstm_shape(d, B, wb.Np), r, wb, lp, st));
+    recurrent(l, dir, s, step, joint, r, wb, lp);
+    HIP_TRY(thin_lstm(d.wterms, r, wb, lp, st));
     return ONMT_OK;
   };
-  auto run_two = [&](int l0, int dir0, int s0, int step0, int slot0, bool joint0, int l1, int dir1, int s1,
-                     int step1, int slot1, bool joint1) -> int {
-    LstmPair g{};
-    recurrent(l0, dir0, s0, step0, slot0, joint0, g.a[0], g.b[0], g.p[0]);
-    recurrent(l1, dir1, s1, step1, slot1, joint1, g.a[1], g.b[1], g.p[1]);
-    HIP_TRY(gemm_lstm2(d.bf16, d.bf16 && B >= kMidMinRows ? kShapeMid : kShapeSplitKThin, g, st));
+  auto run_two = [&](int l0, int dir0, int s0, int step0, bool joint0, int l1, int dir1, int s1, int step1,
+                     bool joint1) -> int {
+    ThinPair q{};
+    recurrent(l0, dir0, s0, step0, joint0, q.a[0], q.w[0], q.p[0]);
+    recurrent(l1, dir1, s1, step1, joint1, q.a[1], q.w[1], q.p[1]);
+    HIP_TRY(thin_lstm2(d.wterms, q, st));
     return ONMT_OK;
   };
   auto project = [&](int l) -> int {   // input projection of every position, both directions at once
-    AOp a{};
-    a.M = BS;
-    a.nseg = 1;
-    if (l == 0) a.seg[0] = seg(m->E_src, w.src, d.Vs, d.E, d.E, d.pad(d.E), d.bf16);
-    else a.seg[0] = seg(w.y[(l - 1) & 1], nullptr, BS, d.Hm, d.Hm, d.pad(d.Hm), 0);
-    StoreParams sp{m->enc_bias[l], w.gx, gxw, gxw, 0};
-    // unidirectional layers >= 1: the W_x columns of the joint matrix (the product reads only pad(Hm))
-    HIP_TRY(gemm_store(d.bf16, kShapeWide, a, bop(uni && l > 0 ? m->enc_xh[l] : m->enc_x[l]), sp, st));
+    const WideA a = l == 0 ? WideA{m->E_src.w().base, w.src, m->E_src.w().wexp, max_len * B, d.Vs, d.kb(d.E), d.wterms}
+                           : WideA{w.y16[(l - 1) & 1], nullptr, nullptr, max_len * B, BS, kbm, 2};
+    // unidirectional layers >= 1: the W_x columns of the joint matrix
+    HIP_TRY(wide_store(a, uni && l > 0 ? m->enc_xh[l].w() : m->enc_x[l].w(), d.wterms,
+                       WideOut{m->enc_bias[l], w.gx, gxw, gxw, 0, 0}, st));
     return ONMT_OK;
   };
-  const int slots = d.ndir > d.L ? d.ndir : d.L;
-  HIP_TRY(fill_f32(w.hs[1], (size_t)slots * SB, 0.f, st));
-  HIP_TRY(fill_f32(w.cs[1], (size_t)slots * SB, 0.f, st));
-  const int last = (max_len - 1) & 1;      // buffer holding the state after the last step
   int rc = ONMT_OK;
   if (uni && B < kWavefrontMaxRows) {
     // few rows per step (launch-bound): layer l processes position s = wave - l, one step behind the
@@ -1024,14 +948,9 @@ int encode_compute(onmt_model* m, const int32_t* src, const int32_t* len, int B,
       const int hi = wave < d.L - 1 ? wave : d.L - 1;
       for (int l = lo; l <= hi; l += 2) {
         const int t0 = wave - l, t1 = wave - l - 1;   // position = step for a forward layer
-        rc = l + 1 <= hi ? run_two(l, 0, t0, t0, l, l > 0, l + 1, 0, t1, t1, l + 1, true)
-                         : run_one(l, 0, t0, t0, l, l > 0);
+        rc = l + 1 <= hi ? run_two(l, 0, t0, t0, l > 0, l + 1, 0, t1, t1, true) : run_one(l, 0, t0, t0, l > 0);
         if (rc) return rc;
       }
-    }
-    for (int l = 0; l < d.L; ++l) {
-      HIP_TRY(copy_cols(w.hs[last] + l * SB, d.Hd, w.final_h + (size_t)l * B * d.H, d.H, B, d.Hd, st));
-      HIP_TRY(copy_cols(w.cs[last] + l * SB, d.Hd, w.final_c + (size_t)l * B * d.H, d.H, B, d.Hd, st));
     }
   } else if (uni) {
     // many rows per step (compute-bound): layer by layer, each with its input projection of every
@@ -1039,36 +958,20 @@ int encode_compute(onmt_model* m, const int32_t* src, const int32_t* len, int B,
     for (int l = 0; l < d.L; ++l) {
       if ((rc = project(l))) return rc;
       for (int step = 0; step < max_len; ++step)
-        if ((rc = run_one(l, 0, step, step, l, false))) return rc;
-    }
-    for (int l = 0; l < d.L; ++l) {
-      HIP_TRY(copy_cols(w.hs[last] + l * SB, d.Hd, w.final_h + (size_t)l * B * d.H, d.H, B, d.Hd, st));
-      HIP_TRY(copy_cols(w.cs[last] + l * SB, d.Hd, w.final_c + (size_t)l * B * d.H, d.H, B, d.Hd, st));
+        if ((rc = run_one(l, 0, step, step, false))) return rc;
     }
   } else {
     // both directions of a layer step together, one launch per step
     for (int l = 0; l < d.L; ++l) {
       if ((rc = project(l))) return rc;
-      if (l > 0) {
-        HIP_TRY(fill_f32(w.hs[1], (size_t)slots * SB, 0.f, st));
-        HIP_TRY(fill_f32(w.cs[1], (size_t)slots * SB, 0.f, st));
-      }
       for (int step = 0; step < max_len; ++step)
-        if ((rc = run_two(l, 0, step, step, 0, false, l, 1, max_len - 1 - step, step, 1, false))) return rc;
-      for (int dir = 0; dir < d.ndir; ++dir) {
-        HIP_TRY(copy_cols(w.hs[last] + dir * SB, d.Hd, w.final_h + (size_t)l * B * d.H + dir * d.Hd, d.H, B, d.Hd, st));
-        HIP_TRY(copy_cols(w.cs[last] + dir * SB, d.Hd, w.final_c + (size_t)l * B * d.H + dir * d.Hd, d.H, B, d.Hd, st));
-      }
+        if ((rc = run_two(l, 0, step, step, false, l, 1, max_len - 1 - step, step, false))) return rc;
     }
   }
   // attention keys W_a m_s (concat: its memory columns), once per batch; dot scores read the memory
-  if (d.attn == ONMT_ATTN_DOT) return ONMT_OK;
-  AOp a{};
-  a.M = BS;
-  a.nseg = 1;
-  a.seg[0] = seg(w.memory, nullptr, BS, d.Hm, d.Hm, d.pad(d.Hm), 0);
-  StoreParams kp{nullptr, w.keys, d.H, d.H, 0};
-  HIP_TRY(gemm_store(d.bf16, kShapeWide, a, bop(m->W_a), kp, st));
+  if (!keys) return ONMT_OK;
+  HIP_TRY(wide_store(WideA{w.y16[(d.L - 1) & 1], nullptr, nullptr, BS, BS, kbm, 2}, m->W_a.w(), d.wterms,
+                     WideOut{nullptr, w.keys, d.H, d.H, B, S}, st));
   return ONMT_OK;
 }
 
@@ -1298,10 +1201,9 @@ int onmt_encode(onmt_model* m, const int32_t* src, const int32_t* len, int B, in
   EncWs w;
   enc_layout(m->d, B, S, (char*)ws, &w);
   int mx = 0;
-  const int32_t* lsrc = nullptr;
-  rc = checked_source(m, src, len, B, S, w, st, &mx, &lsrc);
+  rc = checked_source(m, src, len, B, S, w, st, &mx);
   if (rc) return rc;
-  return encode_compute(m, src, lsrc, B, S, mx, w, st);
+  return encode_compute(m, B, S, mx, w, st);
 }
 
 size_t onmt_state_bytes(const onmt_model* m, int N) {
@@ -1458,8 +1360,7 @@ int onmt_beam_search(onmt_model* m, const int32_t* src, const int32_t* len, int 
   SearchWs w;
   search_layout(m->d, B, S, K, T, (char*)ws, &w);
   int mx = 0;
-  const int32_t* lsrc = nullptr;
-  rc = checked_source(m, src, len, B, S, w.enc, st, &mx, &lsrc);
+  rc = checked_source(m, src, len, B, S, w.enc, st, &mx);
   if (rc) return rc;
 
   BeamParams bp = w.bp;
@@ -1484,7 +1385,7 @@ int onmt_beam_search(onmt_model* m, const int32_t* src, const int32_t* len, int 
   gp.pid = w.step.pid;
   gp.ld_logits = w.step.ld_logits;
   gp.V = m->cfg.tgt_vocab;
-  rc = encode_compute(m, src, lsrc, B, S, mx, w.enc, st);
+  rc = encode_compute(m, B, S, mx, w.enc, st);
   if (rc) return rc;
   rc = decode_init_compute(m, w.enc, B, K, w.st[0], st);
   if (rc) return rc;
@@ -1586,7 +1487,7 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
   ScoreWs w;
   score_layout(m->d, B, S, T, (char*)ws, &w);
   int mx = 0;
-  rc = check_len_src(m, src, len, B, S, st, &mx, w.enc.src, w.enc.rowmap);
+  rc = check_len_src(m, src, len, B, S, st, &mx);
   if (rc) return rc;
   // targets: validated on the host, then laid out per step (decoder input and predicted token)
   std::vector<int32_t> ht((size_t)B * T), hl(B);
@@ -1614,7 +1515,8 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
   HIP_TRY(hipMemcpyAsync(w.want, want.data(), sizeof(int32_t) * want.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(w.tlen, hl.data(), sizeof(int32_t) * B, hipMemcpyHostToDevice, st));
 
-  rc = encode_compute(m, src, len, B, S, mx, w.enc, st);
+  HIP_TRY(sanitize_src(src, len, B, S, m->cfg.src_vocab, w.enc.src, w.enc.lens, m->err_host, st));
+  rc = encode_compute(m, B, S, mx, w.enc, st);
   if (rc) return rc;
   rc = decode_init_compute(m, w.enc, B, 1, w.st[0], st);
   if (rc) return rc;

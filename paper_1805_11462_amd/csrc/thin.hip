@@ -192,7 +192,7 @@ struct ThinLstm {
       if (p.y16 && on) {
         uint16_t hi, lo;
         split_act(y, hi, lo);
-        uint16_t* d = p.y16 + split16_at((size_t)row * p.y_S + p.y_s, p.y_col0 + unit, p.y_kb16, 2);
+        uint16_t* d = p.y16 + split16_at((size_t)p.y_r0 + row, p.y_col0 + unit, p.y_kb16, 2);
         d[0] = hi;
         d[kFragElems] = lo;
       }
@@ -216,6 +216,20 @@ template <class C, int NSEG>
 __global__ __launch_bounds__(C::NT) void k_thin_lstm(ThinA a, ThinW w, LstmParams p, int nm, int nblocks) {
   __shared__ __attribute__((aligned(16))) float red[C::LDS / 4];
   thin_lstm_tile<C, NSEG>(a, w, p, nm, nblocks, blockIdx.x, red);
+}
+
+// Two independent LSTM products in one launch (the encoder's two directions at one step, or two stacked layers at
+// consecutive timesteps): blocks [0, nb[0]) run problem 0, the next nt[1] blocks problem 1. nb[0] is a multiple of
+// 8, so both problems see the same block-to-XCD dealing.
+template <class C, int NS0, int NS1>
+__global__ __launch_bounds__(C::NT) void k_thin_lstm2(ThinPair q) {
+  __shared__ __attribute__((aligned(16))) float red[C::LDS / 4];
+  const int bid = blockIdx.x;
+  if (bid < q.nb0) {
+    if (bid < q.nt[0]) thin_lstm_tile<C, NS0>(q.a[0], q.w[0], q.p[0], q.nm[0], q.nt[0], bid, red);
+  } else {
+    thin_lstm_tile<C, NS1>(q.a[1], q.w[1], q.p[1], q.nm[1], q.nt[1], bid - q.nb0, red);
+  }
 }
 
 template <class C, int NSEG>
@@ -296,6 +310,22 @@ static hipError_t launch_thin_store(const ThinA& a, const ThinW& w, const StoreP
   return hipGetLastError();
 }
 
+template <class C>
+static hipError_t launch_thin_lstm2(ThinPair q, hipStream_t st) {
+  for (int i = 0; i < 2; ++i) {
+    q.nm[i] = (q.a[i].M + C::BM - 1) / C::BM;
+    q.nt[i] = q.nm[i] * (q.w[i].rows / C::BN);
+  }
+  q.nb0 = (q.nt[0] + 7) / 8 * 8;
+  const dim3 grid(q.nb0 + q.nt[1]), block(C::NT);
+  const int n0 = q.a[0].nseg, n1 = q.a[1].nseg;
+  if (n0 == 1 && n1 == 1) hipLaunchKernelGGL((k_thin_lstm2<C, 1, 1>), grid, block, 0, st, q);
+  else if (n0 == 1) hipLaunchKernelGGL((k_thin_lstm2<C, 1, 2>), grid, block, 0, st, q);
+  else if (n1 == 2) hipLaunchKernelGGL((k_thin_lstm2<C, 2, 2>), grid, block, 0, st, q);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 #define ONMT_THIN_DISPATCH(PB, I, CALL)                                  \
   do {                                                                   \
     if ((PB) == 2) {                                                     \
@@ -314,6 +344,15 @@ hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmPara
   if (!thin_ok(a, w, w_terms)) return hipErrorInvalidValue;
   const int i = w_terms == 2 ? thin_shape(kThin2, 2, 1, &a.M, &w.rows) : thin_shape(kThin1, 1, 1, &a.M, &w.rows);
 #define ONMT_CALL(...) launch_thin_lstm<__VA_ARGS__>(a, w, p, st)
+  ONMT_THIN_DISPATCH(w_terms, i, ONMT_CALL);
+#undef ONMT_CALL
+}
+
+hipError_t thin_lstm2(int w_terms, const ThinPair& q, hipStream_t st) {
+  if (!thin_ok(q.a[0], q.w[0], w_terms) || !thin_ok(q.a[1], q.w[1], w_terms)) return hipErrorInvalidValue;
+  const int M[2] = {q.a[0].M, q.a[1].M}, rows[2] = {q.w[0].rows, q.w[1].rows};
+  const int i = w_terms == 2 ? thin_shape(kThin2, 2, 2, M, rows) : thin_shape(kThin1, 1, 2, M, rows);
+#define ONMT_CALL(...) launch_thin_lstm2<__VA_ARGS__>(q, st)
   ONMT_THIN_DISPATCH(w_terms, i, ONMT_CALL);
 #undef ONMT_CALL
 }
