@@ -65,7 +65,7 @@ def copy_calibration(nbytes):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("gen.hip", "gemm_device.h", "split16.h", "common.h", "kernels.h"):
+    for f in ("gen.hip", "wide_loop.h", "gemm_device.h", "split16.h", "common.h", "kernels.h"):
         h.update(open(os.path.join(ROOT, "paper_1805_11462_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -599,44 +599,6 @@ hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, con
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ input validation on the device
-// The checks the host otherwise makes after copying the inputs over (one stream sync per call), done by a
-// kernel instead: invalid values are replaced by safe ones (length clamped to [1, S], ids by 0, a parent
-// by the row itself), so every later kernel stays in bounds, and the first kind of violation seen is
-// recorded in *err (a word of host-visible memory the host reads once the stream is synchronized). Several
-// threads may store different codes; any nonzero code reports the failure.
-__global__ void k_sanitize_src(const int32_t* __restrict__ src, const int32_t* __restrict__ len, int B, int S, int V,
-                               int32_t* __restrict__ clean, int32_t* __restrict__ lens, int32_t* err) {
-  const size_t n = (size_t)B * S;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int b = (int)(i / S), s = (int)(i % S);
-    const int l = len[b];
-    const int lc = l < 1 ? 1 : (l > S ? S : l);
-    if (s == 0) {
-      lens[b] = lc;
-      if (l != lc) *err = kErrLength;
-    }
-    int id = 0;
-    if (s < lc) {
-      id = src[i];
-      if (id < 0 || id >= V) {
-        *err = kErrSourceId;
-        id = 0;
-      }
-    }
-    clean[(size_t)s * B + b] = id;
-  }
-}
-
-hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
-                        int32_t* err, hipStream_t st) {
-  const size_t n = (size_t)B * S;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_sanitize_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, clean, lens, err);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ layout helpers
 __global__ void k_fill(float* dst, size_t n, float v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)

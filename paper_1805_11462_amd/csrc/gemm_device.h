@@ -1,5 +1,5 @@
-// Device-side pieces shared by the GEMM kernels (gemm.hip, thin.hip): tile numbering, bf16 term splits and
-// buffer-descriptor loads.
+// Device-side pieces shared by the GEMM kernels (thin.hip, wide.hip, gen.hip): tile numbering, buffer-descriptor and
+// LDS-destination loads, operand stores.
 #pragma once
 
 #include "common.h"
@@ -17,52 +17,15 @@ __device__ inline int xcd_remap(int bid, int nblocks) {
   return xcd * full + (xcd < rem ? xcd : rem) + local;
 }
 
-__device__ inline uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
-
-// Split 8 fp32 values into three bf16 terms p0 = RNE(x), p1 = RNE(x - p0), p2 = RNE(x - p0 - p1). Each
-// remainder is exact in fp32 (it drops leading bits of x), so p0 + p1 + p2 keeps about 24 significant
-// bits of x: the fp32 value itself, as the bf16 products see it. (Two terms keep ~16 bits, which over the
-// 120 steps of the 4 x 1000 decoder recurrence let a hypothesis's log-prob drift to the bf16 tolerance.)
-// The conversions are gfx950's packed fp32 -> bf16 (round to nearest even), two values per instruction.
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ inline void split_bf16x8(const float4& a, const float4& b, uint4& p0, uint4& p1, uint4& p2) {
-  const f32x2_t x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
-  uint32_t t0[4], t1[4], t2[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const bf16x2_t v0 = __builtin_convertvector(x[i], bf16x2_t);
-    const f32x2_t r1 = x[i] - __builtin_convertvector(v0, f32x2_t);
-    const bf16x2_t v1 = __builtin_convertvector(r1, bf16x2_t);
-    const f32x2_t r2 = r1 - __builtin_convertvector(v1, f32x2_t);
-    const bf16x2_t v2 = __builtin_convertvector(r2, bf16x2_t);
-    t0[i] = __builtin_bit_cast(uint32_t, v0);
-    t1[i] = __builtin_bit_cast(uint32_t, v1);
-    t2[i] = __builtin_bit_cast(uint32_t, v2);
-  }
-  p0 = make_uint4(t0[0], t0[1], t0[2], t0[3]);
-  p1 = make_uint4(t1[0], t1[1], t1[2], t1[3]);
-  p2 = make_uint4(t2[0], t2[1], t2[2], t2[3]);
-}
-
-__device__ inline void split_bf16(float x, uint16_t& p0, uint16_t& p1, uint16_t& p2) {
-  uint4 a, b, c;
-  split_bf16x8(make_float4(x, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f), a, b, c);
-  p0 = (uint16_t)(a.x & 0xffffu);
-  p1 = (uint16_t)(b.x & 0xffffu);
-  p2 = (uint16_t)(c.x & 0xffffu);
-}
-
-// Buffer resource descriptor (gfx9 family word 3). Loads through it return zeros past num_records, so
-// an invalid row is given an offset beyond every buffer instead of a branch.
+// Buffer resource descriptor (gfx9 family word 3). Loads through it return zeros past num_records, so a block past
+// the last is given an offset beyond every buffer instead of a branch.
 constexpr int kBufWord3 = 0x00020000;
-constexpr uint32_t kNoRow = 0x80000000u;      // byte offset past the end of any buffer (buffers < 2 GiB)
 
 __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, kBufWord3);
 }
 
-// The same with a wave-uniform byte offset on top, and an offset past the end of a buffer of up to 4 GiB.
+// 16 bytes at a lane's byte offset plus a wave-uniform one, and an offset past the end of a buffer of up to 4 GiB.
 constexpr uint32_t kPastEnd = 0xfffffff0u;
 __device__ inline uint4 buf_load16s(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
@@ -78,10 +41,6 @@ __device__ inline f32x4 mfma_f16(const A& a, const B& b, const f32x4& c) {
 // being emitted.)
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 __device__ inline lds_ptr_t lds_at(char* p) { return (lds_ptr_t)p; }
-
-__device__ inline uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-}
 
 // One 16-byte-per-lane buffer load into LDS (lane l writes 16 bytes at lds + 16 l). (A function of its
 // own: called directly under control flow inside a kernel template, the builtin stops the host-side

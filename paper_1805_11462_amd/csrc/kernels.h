@@ -129,11 +129,11 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st);
 
-// M rows of an operand of `rows` rows and kblocks blocks of `terms` terms: the first M, or (idx) rows idx[m], clamped
-// to the operand; aexp (optional): power of two added to the columns' for each operand row.
+// The first M rows of an operand of `rows` rows and kblocks blocks of `terms` terms; aexp (optional): power of two
+// aexp[eidx ? eidx[m] : m] added to the columns' for row m.
 struct WideA {
   const void* base;
-  const int32_t* idx;
+  const int32_t* eidx;
   const int32_t* aexp;
   int M;
   int rows;
@@ -243,9 +243,10 @@ hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, con
 
 // Device-side input validation (see beam.hip): error kinds recorded in the host-visible word.
 enum { kErrLength = 1, kErrSourceId = 2, kErrToken = 3, kErrParent = 4 };
-// clean [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S].
-hipError_t sanitize_src(const int32_t* src, const int32_t* len, int B, int S, int V, int32_t* clean, int32_t* lens,
-                        int32_t* err, hipStream_t st);
+// ids [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S]; out =
+// the ids' rows of the embedding table ([V][terms][32 kblocks] halfwords) as an operand of S * B rows.
+hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, hipStream_t st);
 
 hipError_t fill_f32(float* dst, size_t n, float v, hipStream_t st);
 // Zeros in columns width .. 32 kblocks of every row (rows rounded up to whole blocks) of up to two two-term operands.

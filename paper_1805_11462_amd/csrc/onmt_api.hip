@@ -180,7 +180,8 @@ struct onmt_model {
   onmt_config cfg;
   Dims d;
   char* dev = nullptr;
-  ThinMat E_src, E_tgt;                    // rows carry the power of two that undoes their own scale
+  ThinMat E_src, E_tgt;                    // rows carry the power of two that undoes their own scale; E_src's rows are
+                                           // contiguous ([terms][32 kblocks]), gathered by token id
   // Encoder. Bidirectional: every layer has an input projection (both directions stacked) and a recurrent
   // matrix per direction. Unidirectional: layer 0 likewise; layers >= 1 keep [input | recurrent] in one
   // matrix, so that they can run one timestep behind the layer below in the same launch.
@@ -440,7 +441,15 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   // E_src
   {
     const float* s = host_weights[wi++];
-    for (int r = 0; r < d.Vs; ++r) pack_thin(img, m->E_src, d.wterms, r, {{s + (size_t)r * d.E, d.E, 0}}, true);
+    std::vector<float> row(d.E);
+    const int ld = d.kb(d.E) * kFragK;
+    for (int r = 0; r < d.Vs; ++r) {
+      for (int k = 0; k < d.E; ++k) row[k] = d.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(s[(size_t)r * d.E + k])) : s[(size_t)r * d.E + k];
+      const int e = host_row_exp(row.data(), d.E);
+      ((int32_t*)(img.buf.data() + m->E_src.exp_off))[r] = kActExp - e;
+      uint16_t* hi = (uint16_t*)(img.buf.data() + m->E_src.off) + (size_t)r * ld * d.wterms;
+      for (int k = 0; k < d.E; ++k) host_split(ldexpf(row[k], e), hi + k, d.wterms == 2 ? hi + ld + k : nullptr);
+    }
   }
   for (int l = 0; l < d.L; ++l) {
     const int in = l == 0 ? d.E : d.Hm;
@@ -574,6 +583,7 @@ struct EncWs {
   float* final_h;    // [L, B, H]
   float* final_c;
   float* gx;         // [S*B, ndir * 4 Hd_pad], row s * B + b
+  uint16_t* x16;     // the source embeddings as an operand of wterms terms, row s * B + b
   // Two-term operands of the layers' outputs (one layer writes y16[l & 1] while it reads the other), row s * B + b
   uint16_t* y16[2];
   // state after an even / odd timestep, one slot per layer and direction: h, c [slots, B, Hd] and h as an operand
@@ -596,6 +606,7 @@ size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
   t.final_h = c.take<float>((size_t)d.L * B * d.H);
   t.final_c = c.take<float>((size_t)d.L * B * d.H);
   t.gx = c.take<float>(BS * d.ndir * 4 * d.Hd_pad);
+  t.x16 = c.take<uint16_t>(split16_bytes(BS, d.kb(d.E), d.wterms) / 2);
   for (int i = 0; i < 2; ++i) t.y16[i] = c.take<uint16_t>(split16_bytes(BS, d.kb(d.Hm), 2) / 2);
   const size_t slots = (size_t)d.ndir * d.L;
   t.hs_plane = split16_bytes(B, d.kb(d.Hd), 2) / 2;
@@ -826,6 +837,12 @@ int check_len_src(const onmt_model* m, const int32_t* src, const int32_t* len, i
   return ONMT_OK;
 }
 
+// The checked ids and lengths (w.src, w.lens) and the source embeddings (w.x16).
+hipError_t embed(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, hipStream_t st) {
+  return embed_src(src, len, B, S, m->cfg.src_vocab, m->E_src.w().base, m->d.wterms, m->d.kb(m->d.E), w.src, w.lens,
+                   w.x16, m->err_host, st);
+}
+
 // Source ids and lengths, checked either on the host (ONMT_VALIDATE_HOST: copied over, one stream sync; the
 // longest length bounds the encoder's steps) or on the device (ONMT_VALIDATE_DEVICE: the kernel that writes the
 // working copies w.src and w.lens also records violations; the encoder then steps over all S_max positions, which
@@ -840,7 +857,7 @@ int checked_source(onmt_model* m, const int32_t* src, const int32_t* len, int B,
     const int rc = check_len_src(m, src, len, B, S, st, max_len);
     if (rc) return rc;
   }
-  HIP_TRY(sanitize_src(src, len, B, S, m->cfg.src_vocab, w.src, w.lens, m->err_host, st));
+  HIP_TRY(embed(m, src, len, B, S, w, st));
   return ONMT_OK;
 }
 
@@ -931,7 +948,7 @@ int encode_compute(onmt_model* m, int B, int S, int max_len, const EncWs& w, hip
     return ONMT_OK;
   };
   auto project = [&](int l) -> int {   // input projection of every position, both directions at once
-    const WideA a = l == 0 ? WideA{m->E_src.w().base, w.src, m->E_src.w().wexp, max_len * B, d.Vs, d.kb(d.E), d.wterms}
+    const WideA a = l == 0 ? WideA{w.x16, w.src, m->E_src.w().wexp, max_len * B, BS, d.kb(d.E), d.wterms}
                            : WideA{w.y16[(l - 1) & 1], nullptr, nullptr, max_len * B, BS, kbm, 2};
     // unidirectional layers >= 1: the W_x columns of the joint matrix
     HIP_TRY(wide_store(a, uni && l > 0 ? m->enc_xh[l].w() : m->enc_x[l].w(), d.wterms,
@@ -1515,7 +1532,7 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
   HIP_TRY(hipMemcpyAsync(w.want, want.data(), sizeof(int32_t) * want.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemcpyAsync(w.tlen, hl.data(), sizeof(int32_t) * B, hipMemcpyHostToDevice, st));
 
-  HIP_TRY(sanitize_src(src, len, B, S, m->cfg.src_vocab, w.enc.src, w.enc.lens, m->err_host, st));
+  HIP_TRY(embed(m, src, len, B, S, w.enc, st));
   rc = encode_compute(m, B, S, mx, w.enc, st);
   if (rc) return rc;
   rc = decode_init_compute(m, w.enc, B, 1, w.st[0], st);

@@ -80,14 +80,18 @@ inline float host_f16_to_f32(uint16_t h) {
   return __builtin_bit_cast(float, sign | ((e + 112u) << 23) | (m << 13));
 }
 
+// The terms of a weight already scaled by its row exponent (lo == nullptr: one term).
+inline void host_split(float s, uint16_t* hi, uint16_t* lo) {
+  const uint16_t h = host_f32_to_f16(s);
+  *hi = h;
+  if (lo) *lo = (h & 0x7c00u) == 0x7c00u ? 0 : host_f32_to_f16((s - host_f16_to_f32(h)) * kLoScale);
+}
+
 // Packs row `r` (w columns at column k0) of a weight matrix already scaled by its row exponent e.
 inline void host_pack_row(uint16_t* dst, int r, int k0, int kblocks, int terms, const float* src, int w, int e) {
   for (int j = 0; j < w; ++j) {
     const size_t at = split16_at(r, k0 + j, kblocks, terms);
-    const float s = ldexpf(src[j], e);
-    const uint16_t h = host_f32_to_f16(s);
-    dst[at] = h;
-    if (terms == 2) dst[at + kFragElems] = (h & 0x7c00u) == 0x7c00u ? 0 : host_f32_to_f16((s - host_f16_to_f32(h)) * kLoScale);
+    host_split(ldexpf(src[j], e), dst + at, terms == 2 ? dst + at + kFragElems : nullptr);
   }
 }
 // Row exponent: the largest finite magnitude of the row goes to [2^14, 2^15); 0 for a row without one.

@@ -260,16 +260,20 @@ __global__ __launch_bounds__(C::NT) void k_thin_store(ThinA a, ThinW w, StorePar
 // ---------------------------------------------------------------- launchers
 
 // Tile by the operand bytes a CU reads per K element when `blocks` workgroups are dealt to 256 CUs: rounds x (4
-// per row of the tile + 2 per column and weight term), the least of the shapes below. Measured (us, weights cold,
-// two-segment LSTM layers; the 16 x 32 tiles with LDS stages before in brackets), fp32 weights, 2 x 500 columns,
-// 2000 units x gates: 320 rows 80 x 32 10.5, 48 x 32 12.9, 32 x 32 13.3 [18.3]; 160 rows 48 x 32 8.2, 32 x 32 10.3
-// [13.4]; 64 rows 16 x 32 5.8, 32 x 32 6.8 [11.5]; 5 rows 5.5 [11.0]; bf16 weights, 320 x 2 x 1000 x 4000: 80 x 64
-// 21.2, 32 x 64 27.6 [31]; 512 x 2 x 1024 x 4096: 32 x 128 31.1, 80 x 64 38.4 [42].
+// per row of the tile + 2 per column and weight term), the least of the shapes below. Measured in us, weights cold,
+// LSTM layers of two segments (the 16 x 32 / 32 x 64 tiles with LDS stages before in brackets):
+//   fp32 weights, 2 x 500 columns, 2000 rows: 320 rows of A 80 x 32 11.0, 32 x 32 and 48 x 32 12.3 [18.3]; 160: 48 x 32
+//   7.7, 32 x 32 9.5 [13.4]; 64: 16 x 32 5.8, 32 x 32 6.4 [11.5]; 5: 16 x 32 5.7 [11.0];
+//   bf16 weights, 2 x 1000, 4000 rows: 320: 80 x 64 21.3, 32 x 64 22.7 [31]; 128: 32 x 64 9.9, 32 x 32 11.7; 64: 32 x 32
+//   7.8, 16 x 32 8.7; 512 (2 x 1024, 4096 rows): 32 x 128 31.6, 32 x 64 30.9, 80 x 64 39 [42].
+// Eight waves and one K block in flight each beat four waves with two or more nearly everywhere (64 rows fp32 5.8
+// against 6.2, two problems of 64 rows bf16 4.6 against 5.2), as two workgroups then share a CU; the 80 x 64 tile
+// needs the registers of four.
 struct ThinShape {
   int tm, tn;
 };
 constexpr ThinShape kThin2[] = {{1, 2}, {2, 2}, {3, 2}, {5, 2}};      // two weight terms
-constexpr ThinShape kThin1[] = {{1, 2}, {2, 4}, {5, 4}, {2, 8}};      // one
+constexpr ThinShape kThin1[] = {{1, 2}, {2, 2}, {2, 4}, {5, 4}, {2, 8}};      // one
 template <int N>
 static int thin_shape(const ThinShape (&list)[N], int pb, int nprob, const int* M, const int* rows) {
   int best = 0;
@@ -329,14 +333,15 @@ static hipError_t launch_thin_lstm2(ThinPair q, hipStream_t st) {
 #define ONMT_THIN_DISPATCH(PB, I, CALL)                                  \
   do {                                                                   \
     if ((PB) == 2) {                                                     \
-      if ((I) == 0) return CALL(Thin<2, 1, 2, 8, 2>);                    \
-      if ((I) == 1) return CALL(Thin<2, 2, 2, 8, 2>);                    \
-      if ((I) == 2) return CALL(Thin<2, 3, 2, 8, 2>);                    \
+      if ((I) == 0) return CALL(Thin<2, 1, 2, 8, 1>);                    \
+      if ((I) == 1) return CALL(Thin<2, 2, 2, 8, 1>);                    \
+      if ((I) == 2) return CALL(Thin<2, 3, 2, 8, 1>);                    \
       return CALL(Thin<2, 5, 2, 8, 1>);                                  \
     }                                                                    \
-    if ((I) == 0) return CALL(Thin<1, 1, 2, 8, 4>);                      \
-    if ((I) == 1) return CALL(Thin<1, 2, 4, 8, 2>);                      \
-    if ((I) == 2) return CALL(Thin<1, 5, 4, 4, 2>);                      \
+    if ((I) == 0) return CALL(Thin<1, 1, 2, 8, 1>);                      \
+    if ((I) == 1) return CALL(Thin<1, 2, 2, 8, 1>);                      \
+    if ((I) == 2) return CALL(Thin<1, 2, 4, 8, 1>);                      \
+    if ((I) == 3) return CALL(Thin<1, 5, 4, 4, 2>);                      \
     return CALL(Thin<1, 2, 8, 8, 1>);                                    \
   } while (0)
 

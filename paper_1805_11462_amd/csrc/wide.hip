@@ -1,10 +1,11 @@
 // Products over many rows with a plain store for gfx950: the encoder's input projections of every position, the
-// attention keys, and the embedding-gate table. The main loop is the generator's (wide_loop.h); rows are either
-// consecutive rows of a two-term activation operand or rows of an embedding table picked by token id, which carry
-// a power of two of their own (weights are in range only row by row).
+// attention keys, and the embedding-gate table. The main loop is the generator's (wide_loop.h); the rows are those of
+// a split operand, with a power of two of their own where they are embeddings (weights are in range only row by
+// row), which are first copied into such an operand by token id (reading the 16-byte chunks of table rows inside the
+// loop, 64 lines per load, took 65 us at 3840 x 1000 x 4000 bf16 and 215 at 20480 x 512 x 4096).
 //
-// Bounds: at the default batch (3200 positions x 512 x 2048, fp32) the products take 17 us at the rate a large
-// library product reaches as three fp16 terms; a 64 x 128 fp32 MFMA tile took 70.
+// Bound by the products: 20480 x 1024 x 4096, two terms, 340 us = 1.0 PFLOP/s of fp16 products; 3200 x 512 x 2048,
+// three terms, 40 us (64 x 128 fp32 MFMA tiles 70).
 
 #include "common.h"
 #include "gemm_device.h"
@@ -24,17 +25,7 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
   const int i16 = lane & 15, g = lane >> 4;
   const int kb = a.kblocks, nrb = (a.rows + 15) / 16;
   uint32_t aoff[C::LPA], woff[TN];
-  if (a.idx) {              // rows by id (clamped to the table): the lane's 16 bytes of its block row
-#pragma unroll
-    for (int i = 0; i < C::LPA; ++i) {
-      const int q = wide_block<C>(wave, i);
-      const int m = min(m0 + q / PA * 16 + i16, a.M - 1);
-      const uint32_t r = min((uint32_t)a.idx[m], (uint32_t)a.rows - 1u);
-      aoff[i] = (r / 16) * kb * (PA * 1024u) + (q % PA) * 1024u + g * 256u + (r % 16) * 16u;
-    }
-  } else {
-    wide_rows<C>(m0, nrb, kb, aoff);
-  }
+  wide_rows<C>(m0, nrb, kb, aoff);
 #pragma unroll
   for (int y = 0; y < TN; ++y)
     woff[y] = ((uint32_t)min(n0 / 16 + wave * TN + y, w.rows / 16 - 1) * w.kblocks + w.kb0) * (PB * 1024u) + lane * 16u;
@@ -51,7 +42,7 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
     for (int x = 0; x < TM; ++x) {
       const int m = m0 + 16 * x + i16;
       if (m >= a.M) continue;
-      const int ae = a.aexp ? a.aexp[a.idx ? min((uint32_t)a.idx[m], (uint32_t)a.rows - 1u) : (uint32_t)m] : 0;
+      const int ae = a.aexp ? a.aexp[a.eidx ? a.eidx[m] : m] : 0;
       f32x4 v;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -62,6 +53,49 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
                       ldexpf(v[2], ex.z + ae) + bias.z, ldexpf(v[3], ex.w + ae) + bias.w);
     }
   }
+}
+
+// Position m = s * B + b of the batch: its id and length checked as in the host's validation (violations recorded
+// in *err, the id 0 past the length or where invalid), the id kept in ids[m], the lengths in lens, and the id's
+// table row ([terms][32 kblocks] halfwords) copied into row m of the operand. A thread moves 16 bytes; a row's reads
+// are consecutive.
+__global__ __launch_bounds__(256) void k_embed_src(const int32_t* __restrict__ src, const int32_t* __restrict__ len,
+                                                   int B, int S, int V, const uint4* __restrict__ table, int terms,
+                                                   int kblocks, int32_t* __restrict__ ids, int32_t* __restrict__ lens,
+                                                   uint16_t* __restrict__ out, int32_t* err) {
+  const int cpt = kblocks * 4, cpr = cpt * terms;         // 16-byte chunks per term and per row
+  const size_t n = (size_t)B * S * cpr;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int m = (int)(i / cpr), c = (int)(i % cpr);
+    const int s = m / B, b = m % B;
+    const int l = len[b], lc = l < 1 ? 1 : (l > S ? S : l);
+    int id = 0;
+    if (s < lc) {
+      id = src[(size_t)b * S + s];
+      if (id < 0 || id >= V) {
+        if (c == 0) *err = kErrSourceId;
+        id = 0;
+      }
+    }
+    if (c == 0) {
+      ids[m] = id;
+      if (s == 0) {
+        lens[b] = lc;
+        if (l != lc) *err = kErrLength;
+      }
+    }
+    *(uint4*)(out + split16_at(m, c % cpt * 8, kblocks, terms) + (size_t)(c / cpt) * kFragElems) = table[(size_t)id * cpr + c];
+  }
+}
+
+hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, hipStream_t st) {
+  const size_t n = (size_t)B * S * kblocks * 4 * terms;
+  size_t blocks = (n + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
+  hipLaunchKernelGGL(k_embed_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, (const uint4*)table,
+                     terms, kblocks, ids, lens, out, err);
+  return hipGetLastError();
 }
 
 template <class C>
@@ -83,7 +117,7 @@ static hipError_t wide_dispatch(const WideA& a, const ThinW& w, const WideOut& p
 hipError_t wide_store(const WideA& a, const ThinW& w, int w_terms, const WideOut& p, hipStream_t st) {
   const uint64_t lim = 1ull << 32;          // 32-bit byte offsets
   if (a.M < 1 || a.rows < 1 || a.kblocks < 1 || w.kb0 < 0 || w.kb0 + a.kblocks > w.kblocks || w.rows % 128 ||
-      p.ncols % 4 || p.ncols > w.rows || (!a.idx && a.M > a.rows) ||
+      p.ncols % 4 || p.ncols > w.rows || a.M > a.rows ||
       split16_bytes(a.rows, a.kblocks, a.terms) >= lim || split16_bytes(w.rows, w.kblocks, w_terms) >= lim)
     return hipErrorInvalidValue;
   if (a.terms == 2 && w_terms == 2) return wide_dispatch<2, 2>(a, w, p, st);
