@@ -21,9 +21,9 @@
  * Conventions for every function:
  *   - Return 0 (ONMT_OK) or a negative error code; never throw or abort. onmt_last_error() gives a
  *     thread-local message for the last failure.
- *   - All size and id checks happen before any compute is enqueued. On error no kernel has been
- *     launched and output buffers are unspecified. (With ONMT_VALIDATE_DEVICE, ids and lengths are
- *     instead checked by a kernel on the stream; see "Input validation".)
+ *   - All size and id checks happen before any compute is enqueued. On error no kernel but the one that
+ *     checks ids and lengths has been launched and output buffers are unspecified. (With
+ *     ONMT_VALIDATE_DEVICE the call does not wait for that kernel; see "Input validation".)
  *   - The caller owns all device memory: it allocates the buffers whose sizes the *_bytes queries
  *     return and passes device pointers. The library never allocates device memory (the allocation-free
  *     decoder step uses a scratch array built into the library).
@@ -138,9 +138,9 @@ int onmt_model_destroy(onmt_model* model);
  * ids in [0, src_vocab). Positions >= len[b] are ignored. Writes the memory bank, the attention keys
  * (general: W_a m_s; concat: the memory columns of W_a times m_s; dot: none, the scores read the
  * memory) and the final states into enc_ws (>= onmt_encode_ws_bytes(model, B, S_max)), which the
- * decoder calls then read. With host validation (the default) src and len are copied to the host and
- * checked (one stream sync), then the encoder is enqueued asynchronously; with device validation nothing
- * waits. The GEMMs read operands through 2 GiB buffer descriptors: a batch whose memory bank
+ * decoder calls then read. With host validation (the default) src and len are checked by a kernel the
+ * call waits for (one stream sync), then the encoder is enqueued asynchronously; with device validation
+ * nothing waits. The GEMMs read operands through 2 GiB buffer descriptors: a batch whose memory bank
  * (B * S_max rows of the memory width padded to 128 columns, fp32) or decoder state rows (B * beam rows)
  * would reach 2 GiB is refused with ONMT_EUNSUPPORTED, as is a model whose embedding table or packed
  * weight matrix would (onmt_num_weights / onmt_model_bytes report it), and scoring over B * T_max rows. */
@@ -164,8 +164,8 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
  *   lse [N] (optional) = logsumexp of each row's logits. attn [N, S_max] (optional) = attention weights,
  *   exactly 0 at pads.
  * step_ws holds onmt_step_ws_bytes(model, B, S_max, K) bytes of scratch. With host validation (the default)
- * prev_tok and parent are copied to the host and checked (one stream sync), then the compute is enqueued
- * asynchronously; with device validation (onmt_set_validation below) nothing waits. */
+ * prev_tok and parent are checked by a kernel the call waits for (one stream sync), then the compute is
+ * enqueued asynchronously; with device validation (onmt_set_validation below) nothing waits. */
 size_t onmt_state_bytes(const onmt_model* model, int N);
 size_t onmt_step_ws_bytes(const onmt_model* model, int B, int S_max, int K);
 int onmt_decode_init(onmt_model* model, const void* enc_ws, int B, int S_max, int K, void* state_out,
@@ -175,10 +175,9 @@ int onmt_decode_step(onmt_model* model, const void* enc_ws, int B, int S_max, in
                      int32_t* ids, float* lse, float* attn, void* step_ws, size_t step_ws_bytes, void* stream);
 
 /* ---- Input validation ---------------------------------------------------------------------------------
- * ONMT_VALIDATE_HOST (the default): onmt_encode, onmt_decode_step and onmt_beam_search copy their device
- * id / length inputs to the host and check them before enqueuing anything, returning ONMT_EINVAL on a bad
- * value (one stream sync per call). ONMT_VALIDATE_DEVICE: a kernel enqueued on the stream checks them
- * instead, so the call does not wait for the device; a bad value is replaced by a safe one (a length
+ * ONMT_VALIDATE_HOST (the default): onmt_encode, onmt_decode_step and onmt_beam_search wait for a kernel
+ * that checks their device id / length inputs before enqueuing anything else, returning ONMT_EINVAL on a
+ * bad value (one stream sync per call). ONMT_VALIDATE_DEVICE: the call does not wait for that kernel; a bad value is replaced by a safe one (a length
  * clamped to [1, S_max], an id by 0, a parent by the row itself), the computation goes on, and the model
  * records the failure. In this mode the encoder steps over all S_max positions (the host does not learn
  * the longest length), which gives the same results. onmt_device_status sets *code to ONMT_OK or
@@ -243,8 +242,7 @@ int onmt_replace_unk(onmt_model* model, const int32_t* src, int B, int S_max, co
  * For sentence b the decoder is fed BOS, tgt[b, 0], ..., tgt[b, tgt_len[b] - 2] and scores the next target
  * token at every step: out_logp[b, t] = log p(tgt[b, t] | tgt[b, <t], src_b) for t < tgt_len[b], 0 after;
  * out_nll[b] = -sum_t out_logp[b, t] (fp64). tgt [B, T_max] and tgt_len [B] are device int32 arrays
- * (1 <= tgt_len[b] <= T_max, ids in [0, tgt_vocab) below the length); they are copied to the host for
- * validation. src/len as in onmt_encode. ws holds onmt_score_ws_bytes(model, B, S_max, T_max) bytes.
+ * (1 <= tgt_len[b] <= T_max, ids in [0, tgt_vocab) below the length), checked by a kernel the call waits for. src/len as in onmt_encode. ws holds onmt_score_ws_bytes(model, B, S_max, T_max) bytes.
  * out_logp [B, T_max] fp32 and out_nll [B] fp64 are device pointers. Returns when the outputs are
  * written (the stream is synchronized). */
 size_t onmt_score_ws_bytes(const onmt_model* model, int B, int S_max, int T_max);

@@ -241,12 +241,17 @@ hipError_t backtrack(const BeamParams& p, int32_t* out_tok, int32_t* out_len, do
 hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, const int32_t* len, const int32_t* align,
                        int T, int unk, int32_t* out, hipStream_t st);
 
-// Device-side input validation (see beam.hip): error kinds recorded in the host-visible word.
+// Input validation on the device: kinds of violation recorded in a host-visible word (several threads may store
+// different ones; any nonzero value reports the failure). Invalid values are replaced by safe ones.
 enum { kErrLength = 1, kErrSourceId = 2, kErrToken = 3, kErrParent = 4 };
-// ids [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S]; out =
+// max_len (optional): the longest length. ids [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S]; out =
 // the ids' rows of the embedding table ([V][terms][32 kblocks] halfwords) as an operand of S * B rows.
 hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
-                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, hipStream_t st);
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, int32_t* max_len,
+                     hipStream_t st);
+// Teacher-forced targets per step: in_tok, want [T, B], tlen [B]; violations in *err, the longest length in *max_len.
+hipError_t targets(const int32_t* tgt, const int32_t* len, int B, int T, int V, int bos, int pad, int32_t* in_tok,
+                   int32_t* want, int32_t* tlen, int32_t* err, int32_t* max_len, hipStream_t st);
 
 hipError_t fill_f32(float* dst, size_t n, float v, hipStream_t st);
 // Zeros in columns width .. 32 kblocks of every row (rows rounded up to whole blocks) of up to two two-term operands.

@@ -218,8 +218,9 @@ struct onmt_model {
   // finish checks of the beam search: two pinned host words the done count is copied into, one event each
   int32_t* done_host = nullptr;
   hipEvent_t done_ev[2] = {nullptr, nullptr};
-  // input validation: ONMT_VALIDATE_HOST or ONMT_VALIDATE_DEVICE; the device checks report into err_host
-  // (pinned host memory, written by the validation kernels, read by onmt_device_status)
+  // input validation: ONMT_VALIDATE_HOST or ONMT_VALIDATE_DEVICE. err_host: pinned words the checking kernels write:
+  // [0] violations since the last onmt_device_status (device mode), then, for calls that wait for their checks
+  // (host mode), [1] violations and [2], [3] the longest source and target length.
   int validation = ONMT_VALIDATE_HOST;
   int32_t* err_host = nullptr;
 };
@@ -539,8 +540,8 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess) {
-    e = hipHostMalloc((void**)&m->err_host, sizeof(int32_t), hipHostMallocDefault);
-    if (e == hipSuccess) *m->err_host = 0;
+    e = hipHostMalloc((void**)&m->err_host, 4 * sizeof(int32_t), hipHostMallocDefault);
+    if (e == hipSuccess) memset(m->err_host, 0, 4 * sizeof(int32_t));
   }
   if (e != hipSuccess) {
     if (m->err_host) hipHostFree(m->err_host);
@@ -814,50 +815,53 @@ int check_ws_limits(const Dims& d, long long B, long long S, long long K, long l
 // Unidirectional encoders with fewer rows than this run their layers as a wavefront (see encode_compute).
 constexpr int kWavefrontMaxRows = 256;
 
-// Copies src/len to the host and validates them (one stream sync); *max_len is the longest length.
-int check_len_src(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, hipStream_t st,
-                  int* max_len) {
-  if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
-  if (B < 1 || S < 1) return fail(ONMT_EINVAL, "B and S_max must be >= 1");
-  if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
-  std::vector<int32_t> hl(B), hs((size_t)B * S);
-  HIP_TRY(hipMemcpyAsync(hl.data(), len, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(hs.data(), src, sizeof(int32_t) * hs.size(), hipMemcpyDeviceToHost, st));
+// The checked ids and lengths (w.src, w.lens) and the source embeddings (w.x16).
+hipError_t embed(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, int32_t* err,
+                 int32_t* max_len, hipStream_t st) {
+  return embed_src(src, len, B, S, m->cfg.src_vocab, m->E_src.w().base, m->d.wterms, m->d.kb(m->d.E), w.src, w.lens,
+                   w.x16, err, max_len, st);
+}
+
+// What the checking kernel found wrong with ids [rows, ld] and their lengths, named by a second look on the host.
+int name_violation(const int32_t* ids, const int32_t* len, int rows, int ld, int V, const char* name, const char* lname,
+                   hipStream_t st) {
+  std::vector<int32_t> hl(rows), hs((size_t)rows * ld);
+  HIP_TRY(hipMemcpyAsync(hl.data(), len, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(hs.data(), ids, sizeof(int32_t) * hs.size(), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  int mx = 0;
-  for (int b = 0; b < B; ++b) {
-    if (hl[b] < 1 || hl[b] > S) return fail(ONMT_EINVAL, "len[%d] = %d outside [1, %d]", b, hl[b], S);
-    mx = hl[b] > mx ? hl[b] : mx;
+  for (int b = 0; b < rows; ++b) {
+    if (hl[b] < 1 || hl[b] > ld) return fail(ONMT_EINVAL, "%s[%d] = %d outside [1, %d]", lname, b, hl[b], ld);
     for (int s = 0; s < hl[b]; ++s) {
-      const int v = hs[(size_t)b * S + s];
-      if (v < 0 || v >= m->cfg.src_vocab) return fail(ONMT_EINVAL, "src[%d, %d] = %d outside [0, %d)", b, s, v, m->cfg.src_vocab);
+      const int v = hs[(size_t)b * ld + s];
+      if (v < 0 || v >= V) return fail(ONMT_EINVAL, "%s[%d, %d] = %d outside [0, %d)", name, b, s, v, V);
     }
   }
-  *max_len = mx;
   return ONMT_OK;
 }
 
-// The checked ids and lengths (w.src, w.lens) and the source embeddings (w.x16).
-hipError_t embed(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, hipStream_t st) {
-  return embed_src(src, len, B, S, m->cfg.src_vocab, m->E_src.w().base, m->d.wterms, m->d.kb(m->d.E), w.src, w.lens,
-                   w.x16, m->err_host, st);
-}
-
-// Source ids and lengths, checked either on the host (ONMT_VALIDATE_HOST: copied over, one stream sync; the
-// longest length bounds the encoder's steps) or on the device (ONMT_VALIDATE_DEVICE: the kernel that writes the
-// working copies w.src and w.lens also records violations; the encoder then steps over all S_max positions, which
-// the packed padding leaves unchanged past each sentence's length).
+// Source ids and lengths: a kernel checks them and writes the working copies w.src, w.lens and w.x16. Host mode
+// (ONMT_VALIDATE_HOST): the call waits for it and refuses bad inputs before any compute is enqueued; the longest
+// length bounds the encoder's steps. (Copying the inputs over instead, two pageable copies with their waits, took
+// about 40 us more.) Device mode: nothing waits, violations are recorded, and the encoder steps over all S_max
+// positions, which the packed padding leaves unchanged past each sentence's length.
 int checked_source(onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, hipStream_t st,
-                   int* max_len) {
-  if (m->validation == ONMT_VALIDATE_DEVICE) {
-    if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
-    if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
+                   int* max_len, bool host) {
+  if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
+  if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
+  if (!host) {
+    HIP_TRY(embed(m, src, len, B, S, w, m->err_host, nullptr, st));
     *max_len = S;
-  } else {
-    const int rc = check_len_src(m, src, len, B, S, st, max_len);
-    if (rc) return rc;
+    return ONMT_OK;
   }
-  HIP_TRY(embed(m, src, len, B, S, w, st));
+  volatile int32_t* words = m->err_host;
+  words[1] = 0;
+  HIP_TRY(embed(m, src, len, B, S, w, m->err_host + 1, m->err_host + 2, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  if (words[1]) {
+    const int rc = name_violation(src, len, B, S, m->cfg.src_vocab, "src", "len", st);
+    return rc ? rc : fail(ONMT_EINVAL, "invalid src or len");
+  }
+  *max_len = words[2];
   return ONMT_OK;
 }
 
@@ -1218,7 +1222,7 @@ int onmt_encode(onmt_model* m, const int32_t* src, const int32_t* len, int B, in
   EncWs w;
   enc_layout(m->d, B, S, (char*)ws, &w);
   int mx = 0;
-  rc = checked_source(m, src, len, B, S, w, st, &mx);
+  rc = checked_source(m, src, len, B, S, w, st, &mx, m->validation == ONMT_VALIDATE_HOST);
   if (rc) return rc;
   return encode_compute(m, B, S, mx, w, st);
 }
@@ -1264,23 +1268,27 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
   State si, so;
   state_layout(m->d, N, (char*)state_in, &si);
   state_layout(m->d, N, (char*)state_out, &so);
-  if (m->validation == ONMT_VALIDATE_DEVICE) {
-    HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), prev_tok, parent, m->cfg.tgt_vocab, sw.tok_s,
-                         sw.par_s, m->err_host, st));
-    prev_tok = sw.tok_s;
-    parent = parent ? sw.par_s : nullptr;
-  } else {
-    std::vector<int32_t> ht(N), hp(parent ? N : 0);
-    HIP_TRY(hipMemcpyAsync(ht.data(), prev_tok, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
-    if (parent) HIP_TRY(hipMemcpyAsync(hp.data(), parent, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
+  const bool host = m->validation == ONMT_VALIDATE_HOST;
+  volatile int32_t* words = m->err_host;
+  if (host) words[1] = 0;
+  HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), prev_tok, parent, m->cfg.tgt_vocab, sw.tok_s,
+                       sw.par_s, m->err_host + (host ? 1 : 0), st));
+  if (host) {
     HIP_TRY(hipStreamSynchronize(st));
-    for (int r = 0; r < N; ++r) {
-      if (ht[r] < 0 || ht[r] >= m->cfg.tgt_vocab) return fail(ONMT_EINVAL, "prev_tok[%d] = %d out of range", r, ht[r]);
-      if (parent && (hp[r] < 0 || hp[r] >= N)) return fail(ONMT_EINVAL, "parent[%d] = %d out of range", r, hp[r]);
+    if (words[1]) {                     // name the value with a second look on the host
+      std::vector<int32_t> ht(N), hp(parent ? N : 0);
+      HIP_TRY(hipMemcpyAsync(ht.data(), prev_tok, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
+      if (parent) HIP_TRY(hipMemcpyAsync(hp.data(), parent, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      for (int r = 0; r < N; ++r) {
+        if (ht[r] < 0 || ht[r] >= m->cfg.tgt_vocab) return fail(ONMT_EINVAL, "prev_tok[%d] = %d out of range", r, ht[r]);
+        if (parent && (hp[r] < 0 || hp[r] >= N)) return fail(ONMT_EINVAL, "parent[%d] = %d out of range", r, hp[r]);
+      }
+      return fail(ONMT_EINVAL, "invalid prev_tok or parent");
     }
-    HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), nullptr, nullptr, 0, nullptr, nullptr, nullptr,
-                         st));
   }
+  prev_tok = sw.tok_s;
+  parent = parent ? sw.par_s : nullptr;
   EncWs w;
   enc_layout(m->d, B, S, (char*)enc_ws, &w);
   rc = decode_compute(m, w, B, S, K, si, so, prev_tok, parent, mode, logp, ids, lse, attn, sw, st);
@@ -1377,7 +1385,7 @@ int onmt_beam_search(onmt_model* m, const int32_t* src, const int32_t* len, int 
   SearchWs w;
   search_layout(m->d, B, S, K, T, (char*)ws, &w);
   int mx = 0;
-  rc = checked_source(m, src, len, B, S, w.enc, st, &mx);
+  rc = checked_source(m, src, len, B, S, w.enc, st, &mx, m->validation == ONMT_VALIDATE_HOST);
   if (rc) return rc;
 
   BeamParams bp = w.bp;
@@ -1504,35 +1512,22 @@ int onmt_score(onmt_model* m, const int32_t* src, const int32_t* len, int B, int
   ScoreWs w;
   score_layout(m->d, B, S, T, (char*)ws, &w);
   int mx = 0;
-  rc = check_len_src(m, src, len, B, S, st, &mx);
-  if (rc) return rc;
-  // targets: validated on the host, then laid out per step (decoder input and predicted token)
-  std::vector<int32_t> ht((size_t)B * T), hl(B);
-  HIP_TRY(hipMemcpyAsync(hl.data(), tgt_len, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(ht.data(), tgt, sizeof(int32_t) * ht.size(), hipMemcpyDeviceToHost, st));
+  // sources and targets checked by kernels that also lay them out; the call waits once for both
+  if (!src || !len) return fail(ONMT_EINVAL, "src/len is NULL");
+  if ((long long)B * S > (1LL << 28)) return fail(ONMT_EUNSUPPORTED, "B * S_max too large");
+  volatile int32_t* words = m->err_host;
+  words[1] = 0;
+  HIP_TRY(embed(m, src, len, B, S, w.enc, m->err_host + 1, m->err_host + 2, st));
+  HIP_TRY(targets(tgt, tgt_len, B, T, m->cfg.tgt_vocab, m->cfg.bos_id, m->cfg.pad_id, w.in_tok, w.want, w.tlen,
+                  m->err_host + 1, m->err_host + 3, st));
   HIP_TRY(hipStreamSynchronize(st));
-  int steps = 0;
-  for (int b = 0; b < B; ++b) {
-    if (hl[b] < 1 || hl[b] > T) return fail(ONMT_EINVAL, "tgt_len[%d] = %d outside [1, %d]", b, hl[b], T);
-    steps = hl[b] > steps ? hl[b] : steps;
-    for (int t = 0; t < hl[b]; ++t) {
-      const int v = ht[(size_t)b * T + t];
-      if (v < 0 || v >= m->cfg.tgt_vocab)
-        return fail(ONMT_EINVAL, "tgt[%d, %d] = %d outside [0, %d)", b, t, v, m->cfg.tgt_vocab);
-    }
+  if (words[1]) {
+    if ((rc = name_violation(src, len, B, S, m->cfg.src_vocab, "src", "len", st))) return rc;
+    if ((rc = name_violation(tgt, tgt_len, B, T, m->cfg.tgt_vocab, "tgt", "tgt_len", st))) return rc;
+    return fail(ONMT_EINVAL, "invalid src, len, tgt or tgt_len");
   }
-  std::vector<int32_t> in((size_t)T * B), want((size_t)T * B);
-  for (int t = 0; t < T; ++t)
-    for (int b = 0; b < B; ++b) {
-      const bool on = t < hl[b];
-      in[(size_t)t * B + b] = !on ? m->cfg.pad_id : (t == 0 ? m->cfg.bos_id : ht[(size_t)b * T + t - 1]);
-      want[(size_t)t * B + b] = on ? ht[(size_t)b * T + t] : 0;
-    }
-  HIP_TRY(hipMemcpyAsync(w.in_tok, in.data(), sizeof(int32_t) * in.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(w.want, want.data(), sizeof(int32_t) * want.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(w.tlen, hl.data(), sizeof(int32_t) * B, hipMemcpyHostToDevice, st));
-
-  HIP_TRY(embed(m, src, len, B, S, w.enc, st));
+  mx = words[2];
+  const int steps = words[3];
   rc = encode_compute(m, B, S, mx, w.enc, st);
   if (rc) return rc;
   rc = decode_init_compute(m, w.enc, B, 1, w.st[0], st);

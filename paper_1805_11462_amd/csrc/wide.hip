@@ -58,11 +58,21 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
 // Position m = s * B + b of the batch: its id and length checked as in the host's validation (violations recorded
 // in *err, the id 0 past the length or where invalid), the id kept in ids[m], the lengths in lens, and the id's
 // table row ([terms][32 kblocks] halfwords) copied into row m of the operand. A thread moves 16 bytes; a row's reads
-// are consecutive.
+// are consecutive. max_len (optional): the longest length. err and max_len are host-visible words.
 __global__ __launch_bounds__(256) void k_embed_src(const int32_t* __restrict__ src, const int32_t* __restrict__ len,
                                                    int B, int S, int V, const uint4* __restrict__ table, int terms,
                                                    int kblocks, int32_t* __restrict__ ids, int32_t* __restrict__ lens,
-                                                   uint16_t* __restrict__ out, int32_t* err) {
+                                                   uint16_t* __restrict__ out, int32_t* err, int32_t* max_len) {
+  if (max_len && blockIdx.x == 0) {
+    __shared__ int longest;
+    if (threadIdx.x == 0) longest = 1;
+    __syncthreads();
+    int v = 1;
+    for (int b = threadIdx.x; b < B; b += blockDim.x) v = max(v, min(len[b], S));
+    atomicMax(&longest, v);
+    __syncthreads();
+    if (threadIdx.x == 0) *max_len = longest;
+  }
   const int cpt = kblocks * 4, cpr = cpt * terms;         // 16-byte chunks per term and per row
   const size_t n = (size_t)B * S * cpr;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
@@ -89,12 +99,58 @@ __global__ __launch_bounds__(256) void k_embed_src(const int32_t* __restrict__ s
 }
 
 hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
-                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, hipStream_t st) {
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, int32_t* max_len,
+                     hipStream_t st) {
   const size_t n = (size_t)B * S * kblocks * 4 * terms;
   size_t blocks = (n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(k_embed_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, (const uint4*)table,
-                     terms, kblocks, ids, lens, out, err);
+                     terms, kblocks, ids, lens, out, err, max_len);
+  return hipGetLastError();
+}
+
+// Teacher-forced targets, checked and laid out per step: in_tok [T, B] the decoder's input (BOS, then the previous
+// target; pad past the length), want [T, B] the target (0 past the length), tlen [B] the lengths clamped to [1, T].
+__global__ __launch_bounds__(256) void k_targets(const int32_t* __restrict__ tgt, const int32_t* __restrict__ len, int B,
+                                                 int T, int V, int bos, int pad, int32_t* __restrict__ in_tok,
+                                                 int32_t* __restrict__ want, int32_t* __restrict__ tlen, int32_t* err,
+                                                 int32_t* max_len) {
+  if (blockIdx.x == 0) {
+    __shared__ int longest;
+    if (threadIdx.x == 0) longest = 1;
+    __syncthreads();
+    int v = 1;
+    for (int b = threadIdx.x; b < B; b += blockDim.x) v = max(v, min(len[b], T));
+    atomicMax(&longest, v);
+    __syncthreads();
+    if (threadIdx.x == 0) *max_len = longest;
+  }
+  const size_t n = (size_t)B * T;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int t = (int)(i / B), b = (int)(i % B);
+    const int l = len[b], lc = l < 1 ? 1 : (l > T ? T : l);
+    if (t == 0) {
+      tlen[b] = lc;
+      if (l != lc) *err = kErrLength;
+    }
+    const bool on = t < lc;
+    int v = on ? tgt[(size_t)b * T + t] : 0, prev = on && t > 0 ? tgt[(size_t)b * T + t - 1] : 0;
+    if (v < 0 || v >= V) {
+      *err = kErrToken;
+      v = 0;
+    }
+    if (prev < 0 || prev >= V) prev = 0;
+    in_tok[i] = !on ? pad : (t == 0 ? bos : prev);
+    want[i] = v;
+  }
+}
+
+hipError_t targets(const int32_t* tgt, const int32_t* len, int B, int T, int V, int bos, int pad, int32_t* in_tok,
+                   int32_t* want, int32_t* tlen, int32_t* err, int32_t* max_len, hipStream_t st) {
+  size_t blocks = ((size_t)B * T + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(k_targets, dim3((unsigned)blocks), dim3(256), 0, st, tgt, len, B, T, V, bos, pad, in_tok, want,
+                     tlen, err, max_len);
   return hipGetLastError();
 }
 
