@@ -108,11 +108,9 @@ __global__ __launch_bounds__(kScoreThreads) void k_attn_scores(const float* __re
     }
   }
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-#pragma unroll
-    for (int o = kScoreLanes / 2; o > 0; o >>= 1) acc[k] += __shfl_xor(acc[k], o, kWave);
-  }
-  if (sub == 0 && s < n) {
+  for (int k = 0; k < KMAX; ++k)
+    if (k < K) acc[k] = group_sum<kScoreLanes>(acc[k]);        // in the group's last lane
+  if (sub == kScoreLanes - 1 && s < n) {
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
       if (k < K) e[(size_t)(r0 + k) * S_max + s] = acc[k];
@@ -121,7 +119,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_attn_scores(const float* __re
 
 // Thread (pl, c): pl = one of PL position lanes (adjacent lanes of a wave), c = one float4 column of the
 // group's CW = kCtxThreads / PL columns. Positions pl, pl + PL, ... are summed per thread, then across
-// the PL lanes by butterfly shuffles.
+// the PL lanes.
 template <int KMAX, int PL>
 __global__ __launch_bounds__(kCtxThreads) void k_attn_context(const float* __restrict__ e,
                                                               const float* __restrict__ mem,
@@ -254,19 +252,16 @@ __global__ __launch_bounds__(kCtxThreads) void k_attn_context(const float* __res
   }
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
-    if (k < K) {                                      // uniform: no shuffles for the rows past K
-#pragma unroll
-      for (int o = PL / 2; o > 0; o >>= 1) {
-        acc[k].x += __shfl_xor(acc[k].x, o, kWave);
-        acc[k].y += __shfl_xor(acc[k].y, o, kWave);
-        acc[k].z += __shfl_xor(acc[k].z, o, kWave);
-        acc[k].w += __shfl_xor(acc[k].w, o, kWave);
-      }
+    if (k < K) {                                      // uniform: no reductions for the rows past K
+      acc[k].x = group_sum<PL>(acc[k].x);             // in the group's last lane
+      acc[k].y = group_sum<PL>(acc[k].y);
+      acc[k].z = group_sum<PL>(acc[k].z);
+      acc[k].w = group_sum<PL>(acc[k].w);
     }
   }
   // written as the two-term operand the attentional output reads, zeros up to its last block's end
   const int kb = (Hm + kFragK - 1) / kFragK;
-  if (pl == 0 && 4 * c < kb * kFragK) {
+  if (pl == PL - 1 && 4 * c < kb * kFragK) {
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
       if (k < K) {

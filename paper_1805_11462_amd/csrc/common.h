@@ -49,15 +49,35 @@ __device__ inline long long readlane_ll(long long v, int l) {
   return ((long long)hi << 32) | (unsigned int)lo;
 }
 
+// Reductions over groups of N consecutive lanes (N = 2 .. 64, a power of two) with DPP moves, which cost a few cycles
+// each where a shuffle is a round trip through LDS: within rows of 16 lanes by shifts, then the rows' last lanes
+// broadcast to the next row (row_bcast 15) and half (row_bcast 31). The last lane of each group ends up with the
+// group's result. Every lane of the wave must be active.
+template <int CTRL, int ROWS>
+__device__ inline float dpp_move(float old, float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
+                                                               CTRL, ROWS, 0xf, false));
+}
+template <int N>
+__device__ inline float group_sum(float v) {
+  if constexpr (N >= 2) v += dpp_move<0x111, 0xf>(0.f, v);
+  if constexpr (N >= 4) v += dpp_move<0x112, 0xf>(0.f, v);
+  if constexpr (N >= 8) v += dpp_move<0x114, 0xf>(0.f, v);
+  if constexpr (N >= 16) v += dpp_move<0x118, 0xf>(0.f, v);
+  if constexpr (N >= 32) v += dpp_move<0x142, 0xa>(0.f, v);
+  if constexpr (N >= 64) v += dpp_move<0x143, 0xc>(0.f, v);
+  return v;
+}
+// The same over the whole wave, the result in every lane.
 __device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+  v = fmaxf(v, dpp_move<0x111, 0xf>(v, v));
+  v = fmaxf(v, dpp_move<0x112, 0xf>(v, v));
+  v = fmaxf(v, dpp_move<0x114, 0xf>(v, v));
+  v = fmaxf(v, dpp_move<0x118, 0xf>(v, v));
+  v = fmaxf(v, dpp_move<0x142, 0xa>(v, v));
+  v = fmaxf(v, dpp_move<0x143, 0xc>(v, v));
+  return readlane_f(v, 63);
 }
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
+__device__ inline float wave_sum(float v) { return readlane_f(group_sum<64>(v), 63); }
 
 }  // namespace onmt
