@@ -49,8 +49,10 @@ __device__ inline void dma16(__amdgpu_buffer_rsrc_t r, char* lds, uint32_t voff,
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 16, voff, soff, 0, 0);
 }
 
-// Vector-memory wait until at most n loads of this wave are outstanding (expcnt and lgkmcnt left alone).
-constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | (((n >> 4) & 3) << 14); }
+// Wait before the barrier of a stage: at most n of this wave's vector loads outstanding (its share of the stage has
+// landed) and none of its LDS reads. The second half is what allows another wave to refill the buffer this wave read
+// last: the compiler may move the products that consume those reads, and with them its own wait, past the barrier.
+constexpr int waitcnt_stage(int n) { return (n & 15) | (7 << 4) | (0 << 8) | (((n >> 4) & 3) << 14); }
 
 // Four consecutive columns (k0 a multiple of 4) of row r of a two-term fp16 operand.
 __device__ inline void store_act4(uint16_t* dst, int r, int k0, int kblocks, const float (&v)[4]) {

@@ -284,7 +284,7 @@ __global__ __launch_bounds__(C::NT, 2) void k_gen(Split16 a, Split16 w, GenParam
     // this wave's loads complete in issue order: its share of stage st has landed; the barrier makes the
     // whole stage visible and frees the buffer multiplied at st - 1 (bare: __syncthreads' fences would also
     // wait for the stages in flight)
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LPW * (NSTG - 2)));
+    __builtin_amdgcn_s_waitcnt(waitcnt_stage(C::LPW * (NSTG - 2)));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(C::NT, 2) void k_gen(Split16 a, Split16 w, GenParam
     }
   }
   // every load (including the re-loads past the end) has landed before the epilogue reuses the buffers
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __builtin_amdgcn_s_waitcnt(waitcnt_stage(0));
   __syncthreads();
 
   gen_epilogue<C>(smem, p, a.rows, w.rows, m0, n0, wm, wn, c0, c1);

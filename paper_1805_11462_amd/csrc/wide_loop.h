@@ -82,7 +82,7 @@ __device__ __forceinline__ void wide_main(char* smem, __amdgpu_buffer_rsrc_t ra,
       // loads are outstanding (weights of younger stages are in the count too, which only waits longer). The
       // barrier makes the whole stage visible and frees the buffer multiplied at st - 1; it is the bare
       // instruction, because __syncthreads' fences would also wait for the stages in flight.
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTG - 2) * C::LPA));
+      __builtin_amdgcn_s_waitcnt(waitcnt_stage((NSTG - 2) * C::LPA));
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
@@ -106,7 +106,7 @@ __device__ __forceinline__ void wide_main(char* smem, __amdgpu_buffer_rsrc_t ra,
       }
     }
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  __builtin_amdgcn_s_waitcnt(waitcnt_stage(0));
   __syncthreads();
 }
 
