@@ -15,10 +15,10 @@ namespace onmt {
 //
 // theta = the K-th largest of the 64 per-lane tile maxima is a lower bound on the row's K-th largest
 // logit (those K values are maxima of K distinct tiles), so only tiles whose maximum reaches theta can
-// contribute: K tiles or a few more. Their logits are read (a tile's 128 in one access of the wave, four tiles in
-// flight), the allowed entries >= theta are appended to LDS, and each survivor's position in the result is the
-// number of survivors that come before it, which every lane counts for its own entry independently. Rows with
-// more qualifying tiles or survivors than fit (ties at theta) take K rounds of an argmax over all columns.
+// contribute: K tiles or a few more. Their logits are read (eight tiles in flight, two logits of each per lane),
+// the allowed entries >= theta are appended to LDS, and each survivor's position in the result is the number of
+// survivors that come before it, which every lane counts for its own entry independently. Rows with more
+// qualifying tiles or survivors than fit (ties at theta) take K rounds of an argmax over all columns.
 constexpr int kMaxTilesPerLane = 16;          // tiles per row <= 64 * 16 (vocabulary <= 131072)
 constexpr int kSurvivorCap = 256;
 constexpr int kQualCap = 256;                 // qualifying tiles listed per row
@@ -120,7 +120,7 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
   };
   const float* lrow = gp.logits ? gp.logits + (size_t)row * gp.ld_logits : nullptr;
   if (nq <= kQualCap && lrow) {
-    constexpr int kBatch = 4;
+    constexpr int kBatch = 8;        // K = 5 qualifies 5 or 6 tiles: one round trip (64-sentence search 4.67 -> 4.64 ms)
     for (int q0 = 0; q0 < nq && n <= kSurvivorCap; q0 += kBatch) {
       float v[kBatch][2];
       int c0[kBatch];
@@ -370,6 +370,7 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
   // trip instead of three dependent ones; a finished sentence's loads are simply not used)
   const int done = p.done[b];
   const double my_score = p.score[r0 + w];
+  const double sc = lane < K ? p.score[r0 + lane] : ninf;
   const size_t base = (size_t)(r0 + w) * gp.ntiles;
   float tm[kMaxTilesPerLane], tq[kMaxTilesPerLane];
   row_tiles_load(gp.pmax + base, gp.psum + base, gp.ntiles, tm, tq);
@@ -388,7 +389,6 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
   if (w != 0) return;
 
   // K-way merge: lane k < K holds slot k's score and the head of its list
-  const double sc = lane < K ? p.score[r0 + lane] : ninf;
   int h = 0;
   double my_v = ninf;
   int my_slot = 0, my_tok = 0;
