@@ -342,14 +342,13 @@ __global__ __launch_bounds__(C::NT, 2) void k_gen_wide(Split16 a, Split16 w, Gen
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
   const int nrb = (a.rows + 15) / 16, kb = a.kblocks;
-  uint32_t aoff[C::LPA], woff[TN];
-  wide_rows<C>(m0, nrb, kb, aoff);
+  uint32_t woff[TN];
 #pragma unroll
   for (int y = 0; y < TN; ++y)
     woff[y] = (uint32_t)min(n0 / 16 + wave * TN + y, w.rows / 16 - 1) * kb * (PB * 1024u) + lane * 16u;
   f32x4 c0[TM][TN], c1[TM][TN];
-  wide_main<C>(smem, make_rsrc(a.base, (uint32_t)nrb * kb * 2048u), aoff,
-               make_rsrc(w.base, (uint32_t)(w.rows / 16) * kb * (PB * 1024u)), woff, kb, c0, c1);
+  wide_main<C>(smem, WideRows<C>(a.base, m0, nrb, kb), make_rsrc(w.base, (uint32_t)(w.rows / 16) * kb * (PB * 1024u)),
+               woff, kb, c0, c1);
   gen_epilogue<C>(smem, p, a.rows, w.rows, m0, n0, 0, wave, c0, c1);
 }
 

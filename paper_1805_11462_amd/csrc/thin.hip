@@ -14,6 +14,7 @@
 #include "gemm_device.h"
 #include "kernels.h"
 #include "split16.h"
+#include "wide_loop.h"
 
 namespace onmt {
 
@@ -218,6 +219,64 @@ __global__ __launch_bounds__(C::NT) void k_thin_lstm(ThinA a, ThinW w, LstmParam
   thin_lstm_tile<C, NSEG>(a, w, p, nm, nblocks, blockIdx.x, red);
 }
 
+// LSTM products of many rows against one-term weights: 32 x 128 tiles whose rows go through LDS, shared by the four
+// waves (wide_loop.h), and whose weights go straight into registers. Both kinds are bound by what a CU can read from
+// L2; per row of A this one reads half of what the K-splitting 32 x 128 tile does: 512 x 2048 x 4096 28.1 us against
+// 30.9, 512 x 1024 x 4096 17.4 against 20.0, 640 rows 36 against 42; at 320 rows 25.4 against 22.5 (32 x 64).
+struct ThinWide : WideTile<2, 2, 2, 1, 6, 4> {
+  static constexpr int NW = 1, CROW = BN + 4, PART = BM * CROW;
+  static constexpr int BYTES = LDS > PART * 4 ? LDS : PART * 4;
+};
+
+template <int NSEG>
+__global__ __launch_bounds__(ThinWide::NT) void k_thin_lstm_wide(ThinA a, ThinW w, LstmParams p, int nm, int nblocks) {
+  using C = ThinWide;
+  constexpr int TM = C::TM, TN = C::TN, S1 = NSEG - 1;
+  __shared__ __attribute__((aligned(16))) char smem[C::BYTES];
+  const int L = xcd_remap(blockIdx.x, nblocks);
+  const int m0 = (L % nm) * C::BM, n0 = (L / nm) * C::BN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  ThinLstm<C> ep;
+  ep.load(p, w.wexp, a.M, m0, n0);
+  uint32_t aoff[NSEG][C::LPA], woff[TN];
+#pragma unroll
+  for (int s = 0; s < NSEG; ++s)
+#pragma unroll
+    for (int i = 0; i < C::LPA; ++i) {
+      const int q = wide_block<C>(wave, i), m = min(m0 + q / 2 * 16 + i16, a.M - 1);
+      const uint32_t r = a.seg[s].row0 + (a.seg[s].idx ? a.seg[s].idx[m] : m);
+      aoff[s][i] = (r / kFragRows) * a.seg[s].kblocks * 2048u + (q & 1) * 1024u + g * 256u + (r % kFragRows) * 16u;
+    }
+#pragma unroll
+  for (int y = 0; y < TN; ++y) woff[y] = ((uint32_t)(n0 / 16 + wave * TN + y) * w.kblocks + w.kb0) * 1024u + lane * 16u;
+  const int kb0 = a.seg[0].kblocks;
+  auto load_a = [&](int st, char* base) {
+    const bool s1 = NSEG > 1 && st >= kb0;
+    const __amdgpu_buffer_rsrc_t ra =
+        make_rsrc(s1 ? a.seg[S1].base : a.seg[0].base, s1 ? a.seg[S1].bytes : a.seg[0].bytes);
+#pragma unroll
+    for (int i = 0; i < C::LPA; ++i)
+      dma16(ra, base + wide_block<C>(wave, i) * 1024, s1 ? aoff[S1][i] : aoff[0][i],
+            (uint32_t)(s1 ? st - kb0 : st) * 2048u);
+  };
+  f32x4 c0[TM][TN], c1[TM][TN];
+  wide_main<C>(smem, load_a, make_rsrc(w.base, (uint32_t)(w.rows / 16) * w.kblocks * 1024u), woff,
+               kb0 + (NSEG > 1 ? a.seg[S1].kblocks : 0), c0, c1);
+  float* red = (float*)smem;
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = fmaf(c1[x][y][j], 1.f / kLoScale, c0[x][y][j]);
+      *(f32x4*)(red + (16 * x + i16) * C::CROW + wave * 16 * TN + 16 * y + 4 * g) = v;
+    }
+  __syncthreads();
+  ep.finish(red, p, a.M, m0, n0);
+}
+
 // Two independent LSTM products in one launch (the encoder's two directions at one step, or two stacked layers at
 // consecutive timesteps): blocks [0, nb[0]) run problem 0, the next nt[1] blocks problem 1. nb[0] is a multiple of
 // 8, so both problems see the same block-to-XCD dealing.
@@ -347,6 +406,14 @@ static hipError_t launch_thin_lstm2(ThinPair q, hipStream_t st) {
 
 hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st) {
   if (!thin_ok(a, w, w_terms)) return hipErrorInvalidValue;
+  // one-term weights with two or more 32 x 128 tiles for every CU (k_thin_lstm_wide's comment has both sides)
+  const int nm = (a.M + ThinWide::BM - 1) / ThinWide::BM, nb = nm * (w.rows / ThinWide::BN);
+  if (w_terms == 1 && nb >= 512) {
+    const dim3 grid(nb), block(ThinWide::NT);
+    if (a.nseg == 1) hipLaunchKernelGGL(k_thin_lstm_wide<1>, grid, block, 0, st, a, w, p, nm, nb);
+    else hipLaunchKernelGGL(k_thin_lstm_wide<2>, grid, block, 0, st, a, w, p, nm, nb);
+    return hipGetLastError();
+  }
   const int i = w_terms == 2 ? thin_shape(kThin2, 2, 1, &a.M, &w.rows) : thin_shape(kThin1, 1, 1, &a.M, &w.rows);
 #define ONMT_CALL(...) launch_thin_lstm<__VA_ARGS__>(a, w, p, st)
   ONMT_THIN_DISPATCH(w_terms, i, ONMT_CALL);
@@ -436,7 +503,7 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
   return hipGetLastError();
 }
 
-// The checks of k_sanitize_step (tok given) and the two-term copies of a caller's state (split), one launch.
+// The id checks (tok given) and the two-term copies of a caller's state (split), one launch.
 __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, const int32_t* __restrict__ tok,
                                                       const int32_t* __restrict__ parent, int V,
                                                       int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out,

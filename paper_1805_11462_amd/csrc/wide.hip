@@ -24,13 +24,12 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   const int kb = a.kblocks, nrb = (a.rows + 15) / 16;
-  uint32_t aoff[C::LPA], woff[TN];
-  wide_rows<C>(m0, nrb, kb, aoff);
+  uint32_t woff[TN];
 #pragma unroll
   for (int y = 0; y < TN; ++y)
     woff[y] = ((uint32_t)min(n0 / 16 + wave * TN + y, w.rows / 16 - 1) * w.kblocks + w.kb0) * (PB * 1024u) + lane * 16u;
   f32x4 c0[TM][TN], c1[TM][TN];
-  wide_main<C>(smem, make_rsrc(a.base, (uint32_t)nrb * kb * (PA * 1024u)), aoff,
+  wide_main<C>(smem, WideRows<C>(a.base, m0, nrb, kb),
                make_rsrc(w.base, (uint32_t)(w.rows / 16) * w.kblocks * (PB * 1024u)), woff, kb, c0, c1);
 #pragma unroll
   for (int y = 0; y < TN; ++y) {

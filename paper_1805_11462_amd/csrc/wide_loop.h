@@ -40,21 +40,36 @@ __device__ __forceinline__ void wide_rows(int m0, int nrb, int kb, uint32_t (&ao
   }
 }
 
-// c0: sums of the leading products, c1: of the others (scaled by 2^kLoExp). woff: byte offsets of the wave's
-// 16-column weight blocks at the first K block. The weights are the MFMA's row operand: a lane ends up with four
-// consecutive columns (16 y + 4 g + v) of row 16 x + i16. Every load has landed on return, behind a barrier.
+// load_a for such rows.
 template <class C>
-__device__ __forceinline__ void wide_main(char* smem, __amdgpu_buffer_rsrc_t ra, const uint32_t (&aoff)[C::LPA],
-                                          __amdgpu_buffer_rsrc_t rw, const uint32_t (&woff)[C::TN], int kb,
-                                          f32x4 (&c0)[C::TM][C::TN], f32x4 (&c1)[C::TM][C::TN]) {
-  constexpr int TM = C::TM, TN = C::TN, PA = C::PA, PB = C::PB, NSTG = C::NSTG, D = C::D;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  auto issue_a = [&](int st) {       // stages past the last re-load it into a buffer that is never read
-    char* sb = smem + (st % NSTG) * C::STG;
-    const uint32_t ks = (uint32_t)min(st, kb - 1);
+struct WideRows {
+  __amdgpu_buffer_rsrc_t ra;
+  uint32_t off[C::LPA];
+  int wave;
+  __device__ __forceinline__ WideRows(const void* base, int m0, int nrb, int kb)
+      : ra(make_rsrc(base, (uint32_t)nrb * kb * (C::PA * 1024u))),
+        wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    wide_rows<C>(m0, nrb, kb, off);
+  }
+  __device__ __forceinline__ void operator()(int st, char* base) const {
 #pragma unroll
-    for (int i = 0; i < C::LPA; ++i) dma16(ra, sb + wide_block<C>(wave, i) * 1024, aoff[i], ks * (PA * 1024u));
-  };
+    for (int i = 0; i < C::LPA; ++i)
+      dma16(ra, base + wide_block<C>(wave, i) * 1024, off[i], (uint32_t)st * (C::PA * 1024u));
+  }
+};
+
+// c0: sums of the leading products, c1: of the others (scaled by 2^kLoExp). load_a(st, base): moves the wave's A blocks
+// of K block st (one of the operand's) to base. woff: byte offsets of the wave's 16-column weight blocks at the first
+// K block. The weights are the MFMA's row operand: a lane ends up with four consecutive columns (16 y + 4 g + v) of row
+// 16 x + i16. Every load has landed on return, behind a barrier.
+template <class C, class LoadA>
+__device__ __forceinline__ void wide_main(char* smem, LoadA load_a, __amdgpu_buffer_rsrc_t rw,
+                                          const uint32_t (&woff)[C::TN], int kb, f32x4 (&c0)[C::TM][C::TN],
+                                          f32x4 (&c1)[C::TM][C::TN]) {
+  constexpr int TM = C::TM, TN = C::TN, PA = C::PA, PB = C::PB, NSTG = C::NSTG, D = C::D;
+  const int lane = threadIdx.x & 63;
+  // stages past the last re-load it into a buffer that is never read
+  auto issue_a = [&](int st) { load_a(min(st, kb - 1), smem + (st % NSTG) * C::STG); };
   // stages past the last read zeros, so the loop runs whole groups of D stages (the A buffer then holds a copy
   // of the last stage: finite or, where the operand is not, as in the products before)
   uint4 wr[D][TN][PB];

@@ -23,6 +23,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 2, False, 40, 100, 3, 7, "general", 1.0), ("bf16", 3, True, 104, 120, 65, 4, "concat", 1.0),
     ("bf16", 2, False, 512, 1024, 256, 3, "general", 1.0), ("bf16", 2, True, 40, 72, 300, 3, "dot", 1.0),
     ("bf16", 1, False, 40, 36, 1, 30, "general", 1e3),
+    ("bf16", 2, False, 40, 1000, 510, 3, "dot", 1.0),
 ])
 @pytest.mark.parametrize("short", [False, True])
 def test_encoder_rows(wdtype, layers, bi, emb, hidden, B, S, attn, scale, short):

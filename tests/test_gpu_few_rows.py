@@ -39,6 +39,7 @@ def _exact_step(w, weights, mem, keys, lens, h, c, feed, tok, par, K):
     ("fp32", 500, 1, 32, 10), ("fp32", 68, 1, 81, 4), ("fp32", 1000, 1, 33, 5),
     ("bf16", 36, 1, 1, 1), ("bf16", 100, 2, 7, 5), ("bf16", 500, 2, 64, 1), ("bf16", 1000, 2, 64, 5),
     ("bf16", 1024, 1, 513, 1), ("bf16", 1000, 1, 32, 4), ("bf16", 104, 1, 81, 5),
+    ("bf16", 1000, 2, 128, 4), ("bf16", 500, 1, 205, 5),
 ])
 @pytest.mark.parametrize("own_state", [False, True])
 def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
