@@ -40,6 +40,7 @@ def _exact_step(w, weights, mem, keys, lens, h, c, feed, tok, par, K):
     ("bf16", 36, 1, 1, 1), ("bf16", 100, 2, 7, 5), ("bf16", 500, 2, 64, 1), ("bf16", 1000, 2, 64, 5),
     ("bf16", 1024, 1, 513, 1), ("bf16", 1000, 1, 32, 4), ("bf16", 104, 1, 81, 5),
     ("bf16", 1000, 2, 128, 4), ("bf16", 500, 1, 205, 5),
+    *(("fp32", 68, 1, 3, k) for k in (6, 8, 9, 11, 12, 13, 14, 15, 16)),     # one instantiation per beam width
 ])
 @pytest.mark.parametrize("own_state", [False, True])
 def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
