@@ -37,6 +37,23 @@ __device__ __forceinline__ void row_tiles_load(const float* __restrict__ pmax, c
   }
 }
 
+// The row's logsumexp, in every lane.
+__device__ __forceinline__ float row_lse(const float (&tm)[kMaxTilesPerLane], const float (&tq)[kMaxTilesPerLane],
+                                         int ntiles) {
+  const int lane = threadIdx.x & 63;
+  float mx = -__builtin_inff();
+#pragma unroll
+  for (int j = 0; j < kMaxTilesPerLane; ++j) mx = fmaxf(mx, tm[j]);
+  const float gmx = wave_max(mx);
+  float sm = 0.f;
+#pragma unroll
+  for (int j = 0; j < kMaxTilesPerLane; ++j) {
+    const int t = lane + j * kWave;
+    if (t < ntiles) sm += tq[j] * __expf(tm[j] - gmx);
+  }
+  return gmx + __logf(wave_sum(sm));
+}
+
 // Whether column c of a row is no candidate (blocked_unk: the row's hypothesis has used up its UNKs).
 __device__ inline bool filtered(const GenPartials& gp, bool blocked_unk, int c) {
   return (gp.banned_bits && ((gp.banned_bits[c >> 5] >> (c & 31)) & 1u)) || (blocked_unk && c == gp.unk_id);
@@ -51,33 +68,22 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
   const int lane = threadIdx.x & 63;
   const int ntiles = gp.ntiles;
   const float ninf = -__builtin_inff();
-  float mx = ninf;
-#pragma unroll
-  for (int j = 0; j < kMaxTilesPerLane; ++j) mx = fmaxf(mx, tm[j]);
-  const float gmx = wave_max(mx);
-  float sm = 0.f;
-#pragma unroll
-  for (int j = 0; j < kMaxTilesPerLane; ++j) {
-    const int t = lane + j * kWave;
-    if (t < ntiles) sm += tq[j] * __expf(tm[j] - gmx);
-  }
-  const float lse = gmx + __logf(wave_sum(sm));
+  const float lse = row_lse(tm, tq, ntiles);
   if (lane == 0 && out_lse) *out_lse = lse;
-  if (K == 0) return;
   if (gp.pfmax) {           // the largest allowed logits bound the top-K (the logsumexp covers every column)
     const float* pf = gp.pfmax + (size_t)row * ntiles;
-    mx = ninf;
 #pragma unroll
     for (int j = 0; j < kMaxTilesPerLane; ++j) {
       const int t = lane + j * kWave;
       tm[j] = t < ntiles ? pf[t] : ninf;
-      mx = fmaxf(mx, tm[j]);
     }
   }
   const bool blocked_unk = gp.pfmax && gp.unk_cnt && gp.max_unk >= 0 && gp.unk_cnt[row] >= gp.max_unk;
 
   // theta: K rounds of a wave maximum, each removing the (lowest) lane that holds it
-  float cur = mx, theta = ninf;
+  float cur = ninf, theta = ninf;
+#pragma unroll
+  for (int j = 0; j < kMaxTilesPerLane; ++j) cur = fmaxf(cur, tm[j]);
   for (int k = 0; k < K; ++k) {
     const float m = wave_max(cur);
     theta = m;
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void k_lse_topk(GenPartials gp
 
 hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, int32_t* out_id, float* out_lse,
                           hipStream_t st) {
-  if (gp.ntiles > kWave * kMaxTilesPerLane || K > kMaxBeam || (K > 0 && !gp.logits && !gp.pval)) return hipErrorInvalidValue;
+  if (gp.ntiles > kWave * kMaxTilesPerLane || K < 1 || K > kMaxBeam || (!gp.logits && !gp.pval)) return hipErrorInvalidValue;
   const dim3 grid((M + kMergeWaves - 1) / kMergeWaves), block(kMergeWaves * kWave);
   hipLaunchKernelGGL(k_lse_topk, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
   return hipGetLastError();
@@ -251,27 +257,10 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void k_score_rows(const float*
     if (lane == 0) logp[(size_t)b * ld + t] = 0.f;
     return;
   }
-  const float* pm = pmax + (size_t)row * ntiles;
-  const float* ps = psum + (size_t)row * ntiles;
-  const float ninf = -__builtin_inff();
+  const size_t base = (size_t)row * ntiles;
   float tm[kMaxTilesPerLane], tq[kMaxTilesPerLane];
-#pragma unroll
-  for (int j = 0; j < kMaxTilesPerLane; ++j) {
-    const int tt = lane + j * kWave;
-    tm[j] = tt < ntiles ? pm[tt] : ninf;
-    tq[j] = tt < ntiles ? ps[tt] : 0.f;
-  }
-  float mx = ninf;
-#pragma unroll
-  for (int j = 0; j < kMaxTilesPerLane; ++j) mx = fmaxf(mx, tm[j]);
-  const float gmx = wave_max(mx);
-  float sm = 0.f;
-#pragma unroll
-  for (int j = 0; j < kMaxTilesPerLane; ++j) {
-    const int tt = lane + j * kWave;
-    if (tt < ntiles) sm += tq[j] * __expf(tm[j] - gmx);
-  }
-  const float lse = gmx + __logf(wave_sum(sm));
+  row_tiles_load(pmax + base, psum + base, ntiles, tm, tq);
+  const float lse = row_lse(tm, tq, ntiles);
   if (lane == 0) logp[(size_t)b * ld + t] = want_logit[row] - lse;
 }
 
@@ -297,16 +286,52 @@ hipError_t score_rows(const float* pmax, const float* psum, int ntiles, const fl
   return hipGetLastError();
 }
 
-__global__ void k_subtract_rows(float* x, int ld, const float* lse, int M, int ncols) {
-  const int row = blockIdx.y;
-  const float l = lse[row];
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncols; c += gridDim.x * blockDim.x)
-    x[(size_t)row * ld + c] -= l;
+// x[row, :] -= the row's logsumexp, which each wave forms itself from the tile partials, its share of the row already
+// in flight: four 16-byte groups per thread (the row's start need not be aligned; the columns before its first group
+// and after its last go one per thread). Bound by memory: at 320 x 50004 the full-distribution step takes 126.5 us
+// against 144 with one launch for the logsumexps and one of 4-byte accesses, and 131 with loads or stores that are kept
+// in the caches.
+constexpr int kLogpGroups = 4, kLogpThreads = 256;
+
+__global__ __launch_bounds__(kLogpThreads) void k_log_probs(float* __restrict__ x, int ncols,
+                                                            const float* __restrict__ pmax,
+                                                            const float* __restrict__ psum, int ntiles,
+                                                            float* __restrict__ out_lse) {
+  const int row = blockIdx.y, tid = threadIdx.x;
+  float* r = x + (size_t)row * ncols;
+  const int head = min((int)(-((uintptr_t)r / 4) & 3), ncols), n4 = (ncols - head) / 4;
+  f32x4* r4 = (f32x4*)(r + head);
+  const int g0 = blockIdx.x * (kLogpThreads * kLogpGroups) + tid;
+  f32x4 v[kLogpGroups];
+#pragma unroll
+  for (int u = 0; u < kLogpGroups; ++u) {
+    const int g = g0 + u * kLogpThreads;
+    if (g < n4) v[u] = __builtin_nontemporal_load(r4 + g);
+  }
+  const size_t base = (size_t)row * ntiles;
+  float tm[kMaxTilesPerLane], tq[kMaxTilesPerLane];
+  row_tiles_load(pmax + base, psum + base, ntiles, tm, tq);
+  const float lse = row_lse(tm, tq, ntiles);
+#pragma unroll
+  for (int u = 0; u < kLogpGroups; ++u) {
+    const int g = g0 + u * kLogpThreads;
+    if (g < n4) __builtin_nontemporal_store(v[u] - lse, r4 + g);
+  }
+  if (blockIdx.x == 0) {
+    const int edge = ncols - 4 * n4;                // head columns, then the tail's
+    if (tid < edge) {
+      const int c = tid < head ? tid : 4 * n4 + tid;
+      r[c] -= lse;
+    }
+    if (tid == 0) out_lse[row] = lse;
+  }
 }
 
-hipError_t subtract_rows(float* x, int ld, const float* lse, int M, int ncols, hipStream_t st) {
-  dim3 grid((ncols + 255) / 256 < 64 ? (ncols + 255) / 256 : 64, M), block(256);
-  hipLaunchKernelGGL(k_subtract_rows, grid, block, 0, st, x, ld, lse, M, ncols);
+hipError_t log_probs(float* x, int ncols, const GenPartials& gp, int M, float* out_lse, hipStream_t st) {
+  if (gp.ntiles > kWave * kMaxTilesPerLane) return hipErrorInvalidValue;
+  const int per = 4 * kLogpThreads * kLogpGroups;
+  hipLaunchKernelGGL(k_log_probs, dim3((ncols + per - 1) / per, M), dim3(kLogpThreads), 0, st, x, ncols, gp.pmax,
+                     gp.psum, gp.ntiles, out_lse);
   return hipGetLastError();
 }
 

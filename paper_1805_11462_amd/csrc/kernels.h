@@ -194,14 +194,14 @@ struct GenPartials {
   int unk_id, max_unk;
 };
 
-// K = 0: the logsumexp alone.
 hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, int32_t* out_id, float* out_lse,
                           hipStream_t st);
 // Teacher-forced scoring of all steps: rows r = t * B + b of the generator partials; logp[b * ld + t] =
 // want_logit[r] - logsumexp(r) for t < len[b] (0 otherwise, t < steps); nll[b] = -sum_t logp[b, t] in fp64.
 hipError_t score_rows(const float* pmax, const float* psum, int ntiles, const float* want_logit, const int32_t* len,
                       int B, int steps, float* logp, int ld, double* nll, hipStream_t st);
-hipError_t subtract_rows(float* x, int ld, const float* lse, int M, int ncols, hipStream_t st);
+// x [M, ncols] (the logits) -= each row's logsumexp, which goes to out_lse.
+hipError_t log_probs(float* x, int ncols, const GenPartials& gp, int M, float* out_lse, hipStream_t st);
 
 struct BeamParams {
   int B, K, V, T_max, eos, pad;

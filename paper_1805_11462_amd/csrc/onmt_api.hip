@@ -1179,8 +1179,7 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
   if (mode == 2) return ONMT_OK;
   float* lse_out = lse ? lse : sw.lse;
   if (mode == 0) {
-    HIP_TRY(lse_topk_merge(part, N, 0, nullptr, nullptr, lse_out, st));
-    HIP_TRY(subtract_rows(logp, d.Vt, lse_out, N, d.Vt, st));
+    HIP_TRY(log_probs(logp, d.Vt, part, N, lse_out, st));
   } else {
     HIP_TRY(lse_topk_merge(part, N, K, logp, ids, lse_out, st));
   }
