@@ -304,10 +304,9 @@ def main():
 def bench_vendor(w):
     """Plain GEMMs of the vendor library (torch.matmul, which runs hipBLASLt on ROCm) at the shapes of one
     decoder step's GEMMs: a reference for what a library GEMM takes at these shapes without the gathers and
-    epilogues that the library's own kernels fuse in. bf16 workloads multiply several bf16 terms of each
-    activation (two in the generator, three in the decoder layers and W_c), so the reference GEMM concatenates
-    that many copies along K (A = [p0 | p1 | ...], W = [W | W | ...]): the same MFMA work. Not part of the
-    translation path; prints one JSON line per shape."""
+    epilogues that the library's own kernels fuse in. bf16 workloads multiply two 16-bit terms of each
+    activation, so the reference GEMM concatenates two copies along K (A = [p0 | p1], W = [W | W]): the same
+    MFMA work. Not part of the translation path; prints one JSON line per shape."""
     import torch
     if not torch.cuda.is_available():
         sys.exit("--mode vendor needs a GPU")
@@ -318,8 +317,8 @@ def bench_vendor(w):
     dt = torch.bfloat16 if bf16 else torch.float32
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_FP32_TFLOPS
     # (name, M, N, K, activation terms of the library's bf16 product)
-    shapes = [("generator", N, V, H, 2), ("decoder LSTM layer (feed or input ; h)", N, 4 * H, 2 * H, 3),
-              ("attentional output W_c ([ctx ; h])", N, H, Hm + H, 3),
+    shapes = [("generator", N, V, H, 2), ("decoder LSTM layer (feed or input ; h)", N, 4 * H, 2 * H, 2),
+              ("attentional output W_c ([ctx ; h])", N, H, Hm + H, 2),
               ("square 8192 (what the library reaches on a large GEMM)", 8192, 8192, 8192, 1)]
     for name, M, Ncol, K, terms in shapes:
         rep = terms if bf16 else 1
