@@ -2,8 +2,9 @@
 //
 // Values: an fp32 value x is carried as hi = fp16(s) and lo = fp16((s - hi) 2^11) of s = x 2^e, round to
 // nearest even each, so x = (hi + lo 2^-11) 2^-e to 22 significant bits or better (three values in four are
-// exact to all 24). Activations of the recurrences are outputs of tanh and sigmoid, at most 1 in size: e =
-// kActExp leaves them a factor 63 below fp16's largest value and keeps the full precision down to 6e-8.
+// exact to all 24). Activations of the recurrences are outputs of tanh and sigmoid, at most 1 in size, but a
+// caller's own state may hold more: e = kActExp takes values up to 4094 and keeps the full precision down to
+// 3.8e-6, and below that an absolute 5e-13 (e = 10 stopped at 63.9: larger states became infinities).
 // Weights are scaled per row (e = the exponent that takes the row's largest value to [2^14, 2^15)), so every
 // finite fp32 weight is in range; the kernels undo both scales in one ldexp per output. A product is
 //   hi.hi + (hi.lo + lo.hi) 2^-11
@@ -26,7 +27,7 @@ namespace onmt {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kActExp = 10;          // activations: e
+constexpr int kActExp = 4;           // activations: e
 constexpr int kLoExp = 11;           // the lo term's extra scale
 constexpr float kLoScale = 2048.f;
 constexpr int kFragRows = 16, kFragK = 32, kFragElems = kFragRows * kFragK;

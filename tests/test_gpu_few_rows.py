@@ -42,7 +42,7 @@ def _exact_step(w, weights, mem, keys, lens, h, c, feed, tok, par, K):
     ("bf16", 1000, 2, 128, 4), ("bf16", 500, 1, 205, 5),
     *(("fp32", 68, 1, 3, k) for k in (6, 8, 9, 11, 12, 13, 14, 15, 16)),     # one instantiation per beam width
 ])
-@pytest.mark.parametrize("own_state", [False, True])
+@pytest.mark.parametrize("own_state", [False, True, 1000])     # 1000: h and feed of up to 3000
 def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
     if own_state and wdtype == "bf16" and hidden % 8 == 0:
         pytest.skip("such models read the operand copies their producer left beside h and feed")
@@ -62,15 +62,17 @@ def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
     h, c, feed = tr.state_views(st, N)
     if own_state:
         for x in (h, c, feed):
-            x.copy_(torch.from_numpy(rng.uniform(-3, 3, tuple(x.shape)).astype(np.float32)))
+            big = 1 if x is c else int(own_state)
+            x.copy_(torch.from_numpy(big * rng.uniform(-3, 3, tuple(x.shape)).astype(np.float32)))
     h, c, feed = h.double(), c.double(), feed.double()
     got = tr.decode_step(ws, B, S, K, st, tok, par, mode=1)[0]
     mem, keys, _, _ = tr.enc_views(ws, B, S)
     want = _exact_step(w, weights, mem.double(), keys.double(), lens.long(), h, c, feed, tok.long(), par.long(), K)
     for x, y in zip(tr.state_views(got, N), want):
         # pre-activations sum 2 hidden + 32 products of size <= 0.3 to 2^-22 each, then pass through functions of
-        # slope <= 1 (twice over the layers and the output); a c of size 4 keeps 2^-22 of itself
-        assert (x.double() - y).abs().max().item() <= 2e-6 * (1 + layers) * (3 if own_state else 1)
+        # slope <= 1 (twice over the layers and the output); a c of size 4 keeps 2^-22 of itself; with the size of the
+        # inputs the error of their sums grows
+        assert (x.double() - y).abs().max().item() <= 2e-6 * (1 + layers) * 3 ** bool(own_state) * max(1, int(own_state))
     tr.close()
 
 
