@@ -244,11 +244,15 @@ hipError_t replace_unk(const int32_t* src, int B, int S, const int32_t* tok, con
 // Input validation on the device: kinds of violation recorded in a host-visible word (several threads may store
 // different ones; any nonzero value reports the failure). Invalid values are replaced by safe ones.
 enum { kErrLength = 1, kErrSourceId = 2, kErrToken = 3, kErrParent = 4 };
-// max_len (optional): the longest length. ids [S, B] = src [B, S] with ids past each length (and invalid ids) set to 0; lens [B] = len clamped to [1, S]; out =
-// the ids' rows of the embedding table ([V][terms][32 kblocks] halfwords) as an operand of S * B rows.
+// max_len (optional): the longest length. ids [S, B] = src [B, S] with ids past each length (and invalid ids) set to
+// 0; lens [B] = len clamped to [1, S]; out = the first `rows` ids' rows of the embedding table ([V][terms][32 kblocks]
+// halfwords) as an operand.
 hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
-                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, int32_t* max_len,
-                     hipStream_t st);
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int rows, int32_t* err,
+                     int32_t* max_len, hipStream_t st);
+// out = the table rows of n checked ids.
+hipError_t embed_rows(const int32_t* ids, int n, const void* table, int terms, int kblocks, uint16_t* out,
+                      hipStream_t st);
 // Teacher-forced targets per step: in_tok, want [T, B], tlen [B]; violations in *err, the longest length in *max_len.
 hipError_t targets(const int32_t* tgt, const int32_t* len, int B, int T, int V, int bos, int pad, int32_t* in_tok,
                    int32_t* want, int32_t* tlen, int32_t* err, int32_t* max_len, hipStream_t st);

@@ -584,7 +584,8 @@ struct EncWs {
   float* final_h;    // [L, B, H]
   float* final_c;
   float* gx;         // [S*B, ndir * 4 Hd_pad], row s * B + b
-  uint16_t* x16;     // the source embeddings as an operand of wterms terms, row s * B + b
+  uint16_t* x16;     // source embeddings as an operand of wterms terms: x16_rows of the rows s * B + b at a time
+  int x16_rows;
   // Two-term operands of the layers' outputs (one layer writes y16[l & 1] while it reads the other), row s * B + b
   uint16_t* y16[2];
   // state after an even / odd timestep, one slot per layer and direction: h, c [slots, B, Hd] and h as an operand
@@ -594,6 +595,10 @@ struct EncWs {
   size_t hs_plane;   // halfwords of one slot of hs16
   size_t zero_n;     // floats from hs[1] on that hold the zero state before the first step (hs[1], cs[1], hs16[1])
 };
+
+// The source embeddings are gathered in slices of at most this many bytes (whole 64-row tiles): their width does not
+// depend on the memory's, so a batch within the memory's limits could need more than the 4 GiB a product addresses.
+constexpr size_t kEmbedSliceBytes = 256u << 20;
 
 size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
   Carver c;
@@ -607,7 +612,9 @@ size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
   t.final_h = c.take<float>((size_t)d.L * B * d.H);
   t.final_c = c.take<float>((size_t)d.L * B * d.H);
   t.gx = c.take<float>(BS * d.ndir * 4 * d.Hd_pad);
-  t.x16 = c.take<uint16_t>(split16_bytes(BS, d.kb(d.E), d.wterms) / 2);
+  const size_t slice = kEmbedSliceBytes / (split16_bytes(64, d.kb(d.E), d.wterms)) * 64;
+  t.x16_rows = (int)(BS < slice ? BS : slice);
+  t.x16 = c.take<uint16_t>(split16_bytes(t.x16_rows, d.kb(d.E), d.wterms) / 2);
   for (int i = 0; i < 2; ++i) t.y16[i] = c.take<uint16_t>(split16_bytes(BS, d.kb(d.Hm), 2) / 2);
   const size_t slots = (size_t)d.ndir * d.L;
   t.hs_plane = split16_bytes(B, d.kb(d.Hd), 2) / 2;
@@ -815,11 +822,11 @@ int check_ws_limits(const Dims& d, long long B, long long S, long long K, long l
 // Unidirectional encoders with fewer rows than this run their layers as a wavefront (see encode_compute).
 constexpr int kWavefrontMaxRows = 256;
 
-// The checked ids and lengths (w.src, w.lens) and the source embeddings (w.x16).
+// The checked ids and lengths (w.src, w.lens) and the first slice of the source embeddings (w.x16).
 hipError_t embed(const onmt_model* m, const int32_t* src, const int32_t* len, int B, int S, const EncWs& w, int32_t* err,
                  int32_t* max_len, hipStream_t st) {
   return embed_src(src, len, B, S, m->cfg.src_vocab, m->E_src.w().base, m->d.wterms, m->d.kb(m->d.E), w.src, w.lens,
-                   w.x16, err, max_len, st);
+                   w.x16, w.x16_rows, err, max_len, st);
 }
 
 // What the checking kernel found wrong with ids [rows, ld] and their lengths, named by a second look on the host.
@@ -952,11 +959,20 @@ int encode_compute(onmt_model* m, int B, int S, int max_len, const EncWs& w, hip
     return ONMT_OK;
   };
   auto project = [&](int l) -> int {   // input projection of every position, both directions at once
-    const WideA a = l == 0 ? WideA{w.x16, w.src, m->E_src.w().wexp, max_len * B, BS, d.kb(d.E), d.wterms}
-                           : WideA{w.y16[(l - 1) & 1], nullptr, nullptr, max_len * B, BS, kbm, 2};
-    // unidirectional layers >= 1: the W_x columns of the joint matrix
-    HIP_TRY(wide_store(a, uni && l > 0 ? m->enc_xh[l].w() : m->enc_x[l].w(), d.wterms,
-                       WideOut{m->enc_bias[l], w.gx, gxw, gxw, 0, 0}, st));
+    const int rows = max_len * B;
+    if (l > 0) {   // unidirectional: the W_x columns of the joint matrix
+      HIP_TRY(wide_store(WideA{w.y16[(l - 1) & 1], nullptr, nullptr, rows, BS, kbm, 2},
+                         uni ? m->enc_xh[l].w() : m->enc_x[l].w(), d.wterms,
+                         WideOut{m->enc_bias[l], w.gx, gxw, gxw, 0, 0}, st));
+      return ONMT_OK;
+    }
+    for (int r0 = 0, n; r0 < rows; r0 += n) {   // slice by slice, the first gathered by the checking kernel
+      n = rows - r0 < w.x16_rows ? rows - r0 : w.x16_rows;
+      if (r0) HIP_TRY(embed_rows(w.src + r0, n, m->E_src.w().base, d.wterms, d.kb(d.E), w.x16, st));
+      HIP_TRY(wide_store(WideA{w.x16, w.src + r0, m->E_src.w().wexp, n, w.x16_rows, d.kb(d.E), d.wterms},
+                         m->enc_x[0].w(), d.wterms,
+                         WideOut{m->enc_bias[0], w.gx + (size_t)r0 * gxw, gxw, gxw, 0, 0}, st));
+    }
     return ONMT_OK;
   };
   int rc = ONMT_OK;

@@ -55,13 +55,14 @@ __global__ __launch_bounds__(C::NT, 2) void k_wide_store(WideA a, ThinW w, WideO
 }
 
 // Position m = s * B + b of the batch: its id and length checked as in the host's validation (violations recorded
-// in *err, the id 0 past the length or where invalid), the id kept in ids[m], the lengths in lens, and the id's
-// table row ([terms][32 kblocks] halfwords) copied into row m of the operand. A thread moves 16 bytes; a row's reads
-// are consecutive. max_len (optional): the longest length. err and max_len are host-visible words.
+// in *err, the id 0 past the length or where invalid), the id kept in ids[m], the lengths in lens, and, for m < rows,
+// the id's table row ([terms][32 kblocks] halfwords) copied into row m of the operand. A thread moves 16 bytes; a
+// row's reads are consecutive. max_len (optional): the longest length. err and max_len are host-visible words.
 __global__ __launch_bounds__(256) void k_embed_src(const int32_t* __restrict__ src, const int32_t* __restrict__ len,
                                                    int B, int S, int V, const uint4* __restrict__ table, int terms,
                                                    int kblocks, int32_t* __restrict__ ids, int32_t* __restrict__ lens,
-                                                   uint16_t* __restrict__ out, int32_t* err, int32_t* max_len) {
+                                                   uint16_t* __restrict__ out, int rows, int32_t* err,
+                                                   int32_t* max_len) {
   if (max_len && blockIdx.x == 0) {
     __shared__ int longest;
     if (threadIdx.x == 0) longest = 1;
@@ -93,18 +94,42 @@ __global__ __launch_bounds__(256) void k_embed_src(const int32_t* __restrict__ s
         if (l != lc) *err = kErrLength;
       }
     }
-    *(uint4*)(out + split16_at(m, c % cpt * 8, kblocks, terms) + (size_t)(c / cpt) * kFragElems) = table[(size_t)id * cpr + c];
+    if (m < rows)
+      *(uint4*)(out + split16_at(m, c % cpt * 8, kblocks, terms) + (size_t)(c / cpt) * kFragElems) =
+          table[(size_t)id * cpr + c];
   }
 }
 
+// Row m < n of the operand = the table row of the (checked) id ids[m].
+__global__ __launch_bounds__(256) void k_embed_rows(const int32_t* __restrict__ ids, int n,
+                                                    const uint4* __restrict__ table, int terms, int kblocks,
+                                                    uint16_t* __restrict__ out) {
+  const int cpt = kblocks * 4, cpr = cpt * terms;
+  const size_t total = (size_t)n * cpr;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+    const int m = (int)(i / cpr), c = (int)(i % cpr);
+    *(uint4*)(out + split16_at(m, c % cpt * 8, kblocks, terms) + (size_t)(c / cpt) * kFragElems) =
+        table[(size_t)ids[m] * cpr + c];
+  }
+}
+
+hipError_t embed_rows(const int32_t* ids, int n, const void* table, int terms, int kblocks, uint16_t* out,
+                      hipStream_t st) {
+  size_t blocks = ((size_t)n * kblocks * 4 * terms + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
+  hipLaunchKernelGGL(k_embed_rows, dim3((unsigned)blocks), dim3(256), 0, st, ids, n, (const uint4*)table, terms,
+                     kblocks, out);
+  return hipGetLastError();
+}
+
 hipError_t embed_src(const int32_t* src, const int32_t* len, int B, int S, int V, const void* table, int terms,
-                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int32_t* err, int32_t* max_len,
-                     hipStream_t st) {
+                     int kblocks, int32_t* ids, int32_t* lens, uint16_t* out, int rows, int32_t* err,
+                     int32_t* max_len, hipStream_t st) {
   const size_t n = (size_t)B * S * kblocks * 4 * terms;
   size_t blocks = (n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(k_embed_src, dim3((unsigned)blocks), dim3(256), 0, st, src, len, B, S, V, (const uint4*)table,
-                     terms, kblocks, ids, lens, out, err, max_len);
+                     terms, kblocks, ids, lens, out, rows, err, max_len);
   return hipGetLastError();
 }
 

@@ -59,3 +59,31 @@ def test_encoder_rows(wdtype, layers, bi, emb, hidden, B, S, attn, scale, short)
         np.testing.assert_allclose(keys, want, atol=tol * 4 + 1e-6, rtol=0)
         assert (keys[~real] == 0).all()
     tr.close()
+
+
+@pytest.mark.parametrize("wdtype,B,S", [
+    ("fp32", 300, 250),       # two slices of the embedding operand, the second ragged
+    ("bf16", 601, 250),       # half the bytes per row
+    ("fp32", 4100, 256),      # all positions' embeddings would pass 4 GiB, the memory (0.5 GiB) does not
+])
+def test_wide_embeddings_are_projected_slice_by_slice(wdtype, B, S):
+    w = with_workload(W.get("tiny"), emb=1024, hidden=64, wdtype=wdtype)
+    tr = translator_for(w, W.make_weights(w))
+    print(f"[case] embedding slices {wdtype} {B}x{S}", flush=True)
+    rng = np.random.default_rng(5)
+    lens = rng.integers(1, S + 1, B).astype(np.int32)
+    pick = [0, 1, B // 2, B - 2, B - 1]
+    lens[[0, B - 1]] = S
+    src = rng.integers(4, w.src_vocab, (B, S)).astype(np.int32)
+
+    def views(src, lens):
+        ws = tr.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+        return [x.clone() for x in tr.enc_views(ws, *src.shape)]
+
+    mem, keys, fh, fc = views(src, lens)
+    # the same sentences alone: the same sums in other tiles, each good to 1e-6 (see above), so 2e-6 apart at most
+    mem1, keys1, fh1, fc1 = views(np.ascontiguousarray(src[pick]), np.ascontiguousarray(lens[pick]))
+    tol = 4e-6
+    assert (mem[pick] - mem1).abs().max() <= tol and (keys[pick] - keys1).abs().max() <= tol
+    assert (fh[:, pick] - fh1).abs().max() <= tol and (fc[:, pick] - fc1).abs().max() <= 4 * tol
+    tr.close()
