@@ -630,11 +630,17 @@ size_t enc_layout(const Dims& d, int B, int S, char* base, EncWs* w) {
   return align_up(c.off);
 }
 
+// Whether an external step makes the two-term copies of its input state from the fp32 h and feed, which a caller may
+// have written: always for fp32 models, and for bf16 models whose hidden size is not a multiple of 8 (the others
+// read the copies their producer left beside them).
+int split_state(const Dims& d) { return !d.bf16 || d.H % 8 != 0; }
+
 struct State {
   float* h;      // [L, N, H]
   float* c;
   float* feed;   // [N, H]
-  // h and feed as two-term fp16 operands, one of `plane` halfwords per layer (written by their producers)
+  // h and feed as two-term fp16 operands, one of `plane` halfwords per layer (written by their producers). Models that
+  // split their input state have one plane more (step_input).
   uint16_t* h16;
   uint16_t* feed16;
   size_t plane;
@@ -650,7 +656,7 @@ size_t state_layout(const Dims& d, int N, char* base, State* s) {
   t.c = c.take<float>((size_t)d.L * N * d.H);
   t.feed = c.take<float>((size_t)N * d.H);
   t.plane = split16_bytes(N, d.kb(d.H), 2) / 2;
-  t.h16 = c.take<uint16_t>(d.L * t.plane);
+  t.h16 = c.take<uint16_t>((d.L + split_state(d)) * t.plane);
   t.feed16 = c.take<uint16_t>(t.plane);
   if (s) *s = t;
   return align_up(c.off);
@@ -659,6 +665,18 @@ size_t state_layout(const Dims& d, int N, char* base, State* s) {
 // The parts of a State the kernels that fill it write.
 DecodeState decode_state(const Dims& d, const State& s, int N) {
   return DecodeState{s.h, s.c, s.feed, s.h16, s.feed16, s.plane, d.L, N, d.H, d.kb(d.H)};
+// What an external step reads of the state `in` when it writes the state `out`. Copies that the step makes itself go
+// into `out` (a caller's `in` is not written): layer l's h into plane l + 1, which layer l reads while it writes plane
+// l, and the feed into the place of the next one, which is written after layer 0 has read this.
+State step_input(const Dims& d, const State& in, const State& out) {
+  State s = in;
+  if (split_state(d)) {
+    s.h16 = out.h16 + out.plane;
+    s.feed16 = out.feed16;
+  }
+  return s;
+}
+
 }
 
 struct StepWs {
@@ -1202,11 +1220,6 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
   return ONMT_OK;
 }
 
-// Whether an external step rebuilds the two-term copies of its input state from the fp32 h and feed, which a caller
-// may have written: always for fp32 models, and for bf16 models whose hidden size is not a multiple of 8 (the
-// others read the copies their producer left beside them).
-int split_state(const Dims& d) { return !d.bf16 || d.H % 8 != 0; }
-
 int check_beam(const onmt_model* m, int S, int K) {
   if (K < 1 || K > kMaxBeam) return fail(ONMT_EUNSUPPORTED, "beam %d outside [1, %d]", K, kMaxBeam);
   if (K > m->cfg.tgt_vocab) return fail(ONMT_EINVAL, "beam %d larger than the vocabulary", K);
@@ -1290,6 +1303,7 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
                        sw.par_s, m->err_host + (host ? 1 : 0), st));
   if (host) {
     HIP_TRY(hipStreamSynchronize(st));
+  si = step_input(m->d, si, so);
     if (words[1]) {                     // name the value with a second look on the host
       std::vector<int32_t> ht(N), hp(parent ? N : 0);
       HIP_TRY(hipMemcpyAsync(ht.data(), prev_tok, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
@@ -1357,6 +1371,7 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
 }
 
 int onmt_device_status(onmt_model* m, int* code) {
+  si = step_input(m->d, si, so);
   if (!m || !code) return fail(ONMT_EINVAL, "NULL argument");
   volatile int32_t* e = m->err_host;
   const int32_t kind = *e;

@@ -503,7 +503,8 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
   return hipGetLastError();
 }
 
-// The id checks (tok given) and the two-term copies of a caller's state (split), one launch.
+// The id checks (tok given) and the two-term copies of a caller's state (split; s.h16 and s.feed16 lie in the step's
+// output state), one launch.
 __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, const int32_t* __restrict__ tok,
                                                       const int32_t* __restrict__ parent, int V,
                                                       int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out,
