@@ -151,6 +151,11 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
 /* ---- Decoder step: one evaluation of p(w_t | w_<t, x) for N = B*K rows (Section 2; Figure 1(a)) ----
  * A decoder state buffer holds, fp32: h [dec_layers, N, hidden], c [dec_layers, N, hidden],
  * feed [N, hidden] (the previous attentional vector), in that order, onmt_state_bytes(model, N) bytes.
+ * The rest of the buffer holds copies of h and feed that the library writes. A caller may write h, c and feed
+ * between steps, values of any finite size: a step makes its copies anew, in state_out, and never writes state_in.
+ * Every row of a layer's product carries a power of two of its own there; entries keep 22 bits down to 2^-28 of the
+ * row's largest (of 1 if that is larger, in layers above the first), smaller ones an absolute 2^-50 of it. (Exception: bf16 models whose hidden size is a multiple of 8
+ * read the copies beside the state they are given; for them only c may be written.)
  *
  * onmt_decode_init writes into state_out the decoder's initial state: every layer's (h, c) from the
  * encoder's final step of sentence b = r / K, and feed = 0.

@@ -44,6 +44,8 @@ struct LstmParams {
   int H;                        // real units
   uint16_t* h16;                // optional two-term copy of h_out (kb16 blocks of 32 columns)
   int kb16;
+  const int32_t* in_shift;      // optional (two segments), through c_idx: operands of 2^(kActExp + in_shift) ...
+  const int32_t* out_shift;     // ... and its h16 is to carry 2^(kActExp + out_shift)
   uint16_t* y16;                // optional two-term copy of the layer output, row y_r0 + b, columns as y_out
   int y_kb16, y_r0;
 };
@@ -111,6 +113,7 @@ hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmPara
 hipError_t thin_lstm2(int w_terms, const ThinPair& q, hipStream_t st);
 hipError_t thin_store(int w_terms, const ThinA& a, const ThinW& w, const StoreParams& p, hipStream_t st);
 
+constexpr int kShiftPad = 64;
 // A decoder state of N rows: fp32 h, c [L, N, H] and feed [N, H], and the two-term copies of h (one operand of
 // `plane` halfwords per layer) and feed that the products read (kb blocks of 32 columns).
 struct DecodeState {
@@ -121,10 +124,12 @@ struct DecodeState {
   uint16_t* feed16;
   size_t plane;
   int L, N, H, kb;
+  int32_t* shift;               // [L, N] in whole groups of kShiftPad, written by prepare_step (split; zeros at the end)
 };
 // Rows b * K + k of the state = the encoder's final rows b; feed = 0.
 hipError_t decode_init(const DecodeState& s, const float* final_h, const float* final_c, int B, int K, hipStream_t st);
-// split: the two-term copies from h and feed. tok != NULL: tok_out [N] = tok with invalid ids set to 0; par_out [N]
+// split: the two-term copies from h and feed, each row of a layer's product under a power of two of its own: the copies of
+// h (and of feed, with layer 0's h) are scaled by 2^(kActExp + shift[l, r]). tok != NULL: tok_out [N] = tok with invalid ids set to 0; par_out [N]
 // (parent != NULL) = parent with rows outside [0, N) replaced by the row itself; violations recorded in *err.
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st);

@@ -644,6 +644,8 @@ struct State {
   uint16_t* h16;
   uint16_t* feed16;
   size_t plane;
+  int32_t* split_shift;  // [L, N]: powers of two of the copies an external step makes
+  const int32_t* shift = nullptr;   // those of this state's h16 and feed16 (null: none, as their producers write them)
   // scoring keeps every step's feed16 in one operand of feed16_rows rows, this step's from row feed16_r0 on
   int feed16_r0 = 0, feed16_rows = 0;
 };
@@ -658,13 +660,11 @@ size_t state_layout(const Dims& d, int N, char* base, State* s) {
   t.plane = split16_bytes(N, d.kb(d.H), 2) / 2;
   t.h16 = c.take<uint16_t>((d.L + split_state(d)) * t.plane);
   t.feed16 = c.take<uint16_t>(t.plane);
+  t.split_shift = split_state(d) ? c.take<int32_t>(align_up((size_t)d.L * N, kShiftPad)) : nullptr;
   if (s) *s = t;
   return align_up(c.off);
 }
 
-// The parts of a State the kernels that fill it write.
-DecodeState decode_state(const Dims& d, const State& s, int N) {
-  return DecodeState{s.h, s.c, s.feed, s.h16, s.feed16, s.plane, d.L, N, d.H, d.kb(d.H)};
 // What an external step reads of the state `in` when it writes the state `out`. Copies that the step makes itself go
 // into `out` (a caller's `in` is not written): layer l's h into plane l + 1, which layer l reads while it writes plane
 // l, and the feed into the place of the next one, which is written after layer 0 has read this.
@@ -673,10 +673,15 @@ State step_input(const Dims& d, const State& in, const State& out) {
   if (split_state(d)) {
     s.h16 = out.h16 + out.plane;
     s.feed16 = out.feed16;
+    s.split_shift = out.split_shift;
+    s.shift = out.split_shift;
   }
   return s;
 }
 
+// The parts of a State the kernels that fill it write.
+DecodeState decode_state(const Dims& d, const State& s, int N) {
+  return DecodeState{s.h, s.c, s.feed, s.h16, s.feed16, s.plane, d.L, N, d.H, d.kb(d.H), s.split_shift};
 }
 
 struct StepWs {
@@ -1143,6 +1148,10 @@ int decode_compute(onmt_model* m, const EncWs& w, int B, int S, int K, const Sta
     lp.H = d.H;
     lp.h16 = out.h16 + l * out.plane;
     lp.kb16 = kb;
+    if (in.shift) {   // the next layer's product takes this one's output beside its own row of `in`
+      lp.in_shift = in.shift + (size_t)l * N;
+      if (l + 1 < d.L) lp.out_shift = in.shift + (size_t)(l + 1) * N;
+    }
     if (timing) time_begin(m, st, ONMT_KERNEL_LSTM);
     HIP_TRY(thin_lstm(d.wterms, a, m->dec_t[l].w(), lp, st));
     if (timing) time_end(m, st, ONMT_KERNEL_LSTM);
@@ -1296,6 +1305,7 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
   State si, so;
   state_layout(m->d, N, (char*)state_in, &si);
   state_layout(m->d, N, (char*)state_out, &so);
+  si = step_input(m->d, si, so);
   const bool host = m->validation == ONMT_VALIDATE_HOST;
   volatile int32_t* words = m->err_host;
   if (host) words[1] = 0;
@@ -1303,7 +1313,6 @@ int onmt_decode_step(onmt_model* m, const void* enc_ws, int B, int S, int K, con
                        sw.par_s, m->err_host + (host ? 1 : 0), st));
   if (host) {
     HIP_TRY(hipStreamSynchronize(st));
-  si = step_input(m->d, si, so);
     if (words[1]) {                     // name the value with a second look on the host
       std::vector<int32_t> ht(N), hp(parent ? N : 0);
       HIP_TRY(hipMemcpyAsync(ht.data(), prev_tok, sizeof(int32_t) * N, hipMemcpyDeviceToHost, st));
@@ -1364,6 +1373,7 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
   State si, so;
   state_layout(m->d, N, (char*)state_in, &si);
   state_layout(m->d, N, (char*)state_out, &so);
+  si = step_input(m->d, si, so);
   HIP_TRY(prepare_step(decode_state(m->d, si, N), split_state(m->d), prev_tok, parent, m->cfg.tgt_vocab, sw.tok_s,
                        sw.par_s, m->err_host, st));
   return decode_compute(m, w, B, S, K, si, so, sw.tok_s, parent ? sw.par_s : nullptr, mode, logp, ids, lse, attn, sw,
@@ -1371,7 +1381,6 @@ int onmt_decode_step_noalloc(onmt_model* m, const void* enc_ws, int B, int S, in
 }
 
 int onmt_device_status(onmt_model* m, int* code) {
-  si = step_input(m->d, si, so);
   if (!m || !code) return fail(ONMT_EINVAL, "NULL argument");
   volatile int32_t* e = m->err_host;
   const int32_t kind = *e;

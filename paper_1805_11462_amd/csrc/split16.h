@@ -49,15 +49,18 @@ inline size_t split16_bytes(size_t rows, int kblocks, int terms) {
   return (rows + kFragRows - 1) / kFragRows * kblocks * (size_t)(kFragElems * terms) * 2;
 }
 
-// The two terms of an activation. A value past fp16's range becomes an infinity (with lo = 0, so that its
+// The two terms of a scaled value. One past fp16's range becomes an infinity (with lo = 0, so that its
 // products are infinities too, as they are for an infinite fp32 value), NaN stays NaN.
-__device__ inline void split_act(float x, uint16_t& hi, uint16_t& lo) {
-  const float s = x * (float)(1 << kActExp);
+__device__ inline void split_scaled(float s, uint16_t& hi, uint16_t& lo) {
   const _Float16 h = (_Float16)s;
   const float d = fabsf((float)h) == __builtin_inff() ? 0.f : s - (float)h;
   const _Float16 l = (_Float16)(d * kLoScale);
   hi = __builtin_bit_cast(uint16_t, h);
   lo = __builtin_bit_cast(uint16_t, l);
+}
+// The two terms of an activation.
+__device__ inline void split_act(float x, uint16_t& hi, uint16_t& lo) {
+  split_scaled(x * (float)(1 << kActExp), hi, lo);
 }
 
 // float -> fp16 bits, round to nearest even, on the host (weight packing).

@@ -125,13 +125,14 @@ __device__ inline float thin_sum(const float* red, int r, int c) {
 
 // What the LSTM epilogue adds to this thread's (row, unit) elements: bias, the precomputed input projection
 // (table rows gathered by token id) and the previous cell state, with the columns' scales, all loaded before the
-// main loop.
-template <class C>
+// main loop. SHIFT: rows of an external step's own state, whose operands carry powers of two of their own (a variant,
+// because the null checks alone cost the recurrences 3%).
+template <class C, bool SHIFT>
 struct ThinLstm {
   static constexpr int UPT = C::BN / 4;                          // units per tile
   static constexpr int EPT = (C::BM * UPT + C::NT - 1) / C::NT;  // elements per thread
   float z[EPT][4], c[EPT];
-  int ex[EPT][4];
+  int ex[EPT][4], is[EPT], os[EPT];
 
   __device__ __forceinline__ void load(const LstmParams& p, const int32_t* wexp, int M, int m0, int n0) {
 #pragma unroll
@@ -144,6 +145,10 @@ struct ThinLstm {
       const int grow = !(ok && p.gx) ? 0 : (p.gx_idx ? min((unsigned)p.gx_idx[row], (unsigned)p.gx_rows - 1u) : row * p.gx_S + p.gx_s);
       const int crow = ok && p.c_idx ? p.c_idx[row] : row;
       c[i] = ok && p.c_in ? p.c_in[(size_t)crow * p.ld_c + unit] : 0.f;
+      if constexpr (SHIFT) {
+        is[i] = ok ? p.in_shift[crow] : 0;
+        os[i] = ok && p.out_shift ? p.out_shift[crow] : 0;
+      }
 #pragma unroll
       for (int gt = 0; gt < 4; ++gt) {
         const int col = n0 + cbase + gt * kUnitGroup;
@@ -169,7 +174,8 @@ struct ThinLstm {
         const int cbase = (uu / kUnitGroup) * (4 * kUnitGroup) + (uu % kUnitGroup);
         float zz[4], c_new;
 #pragma unroll
-        for (int gt = 0; gt < 4; ++gt) zz[gt] = ldexpf(thin_sum<C>(red, r, cbase + gt * kUnitGroup), ex[i][gt]) + z[i][gt];
+        for (int gt = 0; gt < 4; ++gt)
+          zz[gt] = ldexpf(thin_sum<C>(red, r, cbase + gt * kUnitGroup), ex[i][gt] - (SHIFT ? is[i] : 0)) + z[i][gt];
         if (p.lens && p.y_s >= p.lens[row]) {
           c_new = c[i];
           h_new = p.h_in ? p.h_in[(size_t)row * p.ld_h_in + unit] : 0.f;
@@ -185,7 +191,7 @@ struct ThinLstm {
       }
       if (p.h16 && row < (M + kFragRows - 1) / kFragRows * kFragRows && unit < p.kb16 * kFragK) {
         uint16_t hi, lo;
-        split_act(h_new, hi, lo);
+        split_act(SHIFT ? ldexpf(h_new, os[i]) : h_new, hi, lo);
         uint16_t* d = p.h16 + split16_at(row, unit, p.kb16, 2);
         d[0] = hi;
         d[kFragElems] = lo;
@@ -201,22 +207,22 @@ struct ThinLstm {
   }
 };
 
-template <class C, int NSEG>
+template <class C, int NSEG, bool SHIFT = false>
 __device__ __forceinline__ void thin_lstm_tile(const ThinA& a, const ThinW& w, const LstmParams& p, int nm, int nblocks,
                                                int bid, float* red) {
   const int L = xcd_remap(bid, nblocks);
   const int m0 = (L % nm) * C::BM, n0 = (L / nm) * C::BN;
-  ThinLstm<C> ep;
+  ThinLstm<C, SHIFT> ep;
   ep.load(p, w.wexp, a.M, m0, n0);
   thin_main<C, NSEG>(a, w, m0, n0, red);
   __syncthreads();
   ep.finish(red, p, a.M, m0, n0);
 }
 
-template <class C, int NSEG>
+template <class C, int NSEG, bool SHIFT>
 __global__ __launch_bounds__(C::NT) void k_thin_lstm(ThinA a, ThinW w, LstmParams p, int nm, int nblocks) {
   __shared__ __attribute__((aligned(16))) float red[C::LDS / 4];
-  thin_lstm_tile<C, NSEG>(a, w, p, nm, nblocks, blockIdx.x, red);
+  thin_lstm_tile<C, NSEG, SHIFT>(a, w, p, nm, nblocks, blockIdx.x, red);
 }
 
 // LSTM products of many rows against one-term weights: 32 x 128 tiles whose rows go through LDS, shared by the four
@@ -228,7 +234,7 @@ struct ThinWide : WideTile<2, 2, 2, 1, 6, 4> {
   static constexpr int BYTES = LDS > PART * 4 ? LDS : PART * 4;
 };
 
-template <int NSEG>
+template <int NSEG, bool SHIFT>
 __global__ __launch_bounds__(ThinWide::NT) void k_thin_lstm_wide(ThinA a, ThinW w, LstmParams p, int nm, int nblocks) {
   using C = ThinWide;
   constexpr int TM = C::TM, TN = C::TN, S1 = NSEG - 1;
@@ -237,7 +243,7 @@ __global__ __launch_bounds__(ThinWide::NT) void k_thin_lstm_wide(ThinA a, ThinW 
   const int m0 = (L % nm) * C::BM, n0 = (L / nm) * C::BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
-  ThinLstm<C> ep;
+  ThinLstm<C, SHIFT> ep;
   ep.load(p, w.wexp, a.M, m0, n0);
   uint32_t aoff[NSEG][C::LPA], woff[TN];
 #pragma unroll
@@ -360,8 +366,10 @@ static bool thin_ok(const ThinA& a, const ThinW& w, int pb) {
 template <class C>
 static hipError_t launch_thin_lstm(const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st) {
   const int nm = (a.M + C::BM - 1) / C::BM, nb = nm * (w.rows / C::BN);
-  if (a.nseg == 1) hipLaunchKernelGGL((k_thin_lstm<C, 1>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
-  else hipLaunchKernelGGL((k_thin_lstm<C, 2>), dim3(nb), dim3(C::NT), 0, st, a, w, p, nm, nb);
+  const dim3 grid(nb), block(C::NT);
+  if (p.in_shift) hipLaunchKernelGGL((k_thin_lstm<C, 2, true>), grid, block, 0, st, a, w, p, nm, nb);
+  else if (a.nseg == 1) hipLaunchKernelGGL((k_thin_lstm<C, 1, false>), grid, block, 0, st, a, w, p, nm, nb);
+  else hipLaunchKernelGGL((k_thin_lstm<C, 2, false>), grid, block, 0, st, a, w, p, nm, nb);
   return hipGetLastError();
 }
 
@@ -405,13 +413,14 @@ static hipError_t launch_thin_lstm2(ThinPair q, hipStream_t st) {
   } while (0)
 
 hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmParams& p, hipStream_t st) {
-  if (!thin_ok(a, w, w_terms)) return hipErrorInvalidValue;
+  if (!thin_ok(a, w, w_terms) || (p.in_shift && a.nseg != 2)) return hipErrorInvalidValue;
   // one-term weights with two or more 32 x 128 tiles for every CU (k_thin_lstm_wide's comment has both sides)
   const int nm = (a.M + ThinWide::BM - 1) / ThinWide::BM, nb = nm * (w.rows / ThinWide::BN);
   if (w_terms == 1 && nb >= 512) {
     const dim3 grid(nb), block(ThinWide::NT);
-    if (a.nseg == 1) hipLaunchKernelGGL(k_thin_lstm_wide<1>, grid, block, 0, st, a, w, p, nm, nb);
-    else hipLaunchKernelGGL(k_thin_lstm_wide<2>, grid, block, 0, st, a, w, p, nm, nb);
+    if (p.in_shift) hipLaunchKernelGGL((k_thin_lstm_wide<2, true>), grid, block, 0, st, a, w, p, nm, nb);
+    else if (a.nseg == 1) hipLaunchKernelGGL((k_thin_lstm_wide<1, false>), grid, block, 0, st, a, w, p, nm, nb);
+    else hipLaunchKernelGGL((k_thin_lstm_wide<2, false>), grid, block, 0, st, a, w, p, nm, nb);
     return hipGetLastError();
   }
   const int i = w_terms == 2 ? thin_shape(kThin2, 2, 1, &a.M, &w.rows) : thin_shape(kThin1, 1, 1, &a.M, &w.rows);
@@ -421,7 +430,7 @@ hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmPara
 }
 
 hipError_t thin_lstm2(int w_terms, const ThinPair& q, hipStream_t st) {
-  if (!thin_ok(q.a[0], q.w[0], w_terms) || !thin_ok(q.a[1], q.w[1], w_terms)) return hipErrorInvalidValue;
+  if (!thin_ok(q.a[0], q.w[0], w_terms) || !thin_ok(q.a[1], q.w[1], w_terms) || q.p[0].in_shift || q.p[1].in_shift) return hipErrorInvalidValue;
   const int M[2] = {q.a[0].M, q.a[1].M}, rows[2] = {q.w[0].rows, q.w[1].rows};
   const int i = w_terms == 2 ? thin_shape(kThin2, 2, 2, M, rows) : thin_shape(kThin1, 1, 2, M, rows);
 #define ONMT_CALL(...) launch_thin_lstm2<__VA_ARGS__>(q, st)
@@ -439,14 +448,14 @@ hipError_t thin_store(int w_terms, const ThinA& a, const ThinW& w, const StorePa
 
 // ---------------------------------------------------------------- decoder state
 
-// Eight consecutive columns (k0 a multiple of 8) of row r of a two-term operand.
-__device__ inline void store_act8(uint16_t* dst, int r, int k0, int kblocks, const float (&v)[8]) {
+// Eight consecutive columns (k0 a multiple of 8) of row r of a two-term operand, scaled by 2^e.
+__device__ inline void store_act8(uint16_t* dst, int r, int k0, int kblocks, const float (&v)[8], int e = kActExp) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint16_t h0, h1, l0, l1;
-    split_act(v[2 * j], h0, l0);
-    split_act(v[2 * j + 1], h1, l1);
+    split_scaled(ldexpf(v[2 * j], e), h0, l0);
+    split_scaled(ldexpf(v[2 * j + 1], e), h1, l1);
     h[j] = h0 | (uint32_t)h1 << 16;
     l[j] = l0 | (uint32_t)l1 << 16;
   }
@@ -504,7 +513,12 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
 }
 
 // The id checks (tok given) and the two-term copies of a caller's state (split; s.h16 and s.feed16 lie in the step's
-// output state), one launch.
+// output state), one launch. A caller's rows may be of any size, so each row of a layer's product gets a power of two
+// of its own: one wave reads what that product reads of the row (layer 0: feed and h, else h), scales its largest
+// finite value to [2^14, 2^15) and records the power. In layers above 0 the same power also scales the output of the
+// layer below, which is at most 1 in size, so there it is at most 2^14.
+constexpr int kMaxChunks = 2;                 // 8-column chunks per lane (H <= 1024)
+
 __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, const int32_t* __restrict__ tok,
                                                       const int32_t* __restrict__ parent, int V,
                                                       int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out,
@@ -529,21 +543,46 @@ __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, 
     }
   }
   if (!split) return;
+  const size_t nshift = (size_t)s.L * s.N;
+  for (size_t i = nshift + i0; i < (nshift + kShiftPad - 1) / kShiftPad * kShiftPad; i += step) s.shift[i] = 0;
+  const int lane = threadIdx.x & 63;
   const int chunks = s.kb * 4, rows = (s.N + kFragRows - 1) / kFragRows * kFragRows;
-  const size_t n = (size_t)(s.L + 1) * rows * chunks;
-  for (size_t i = i0; i < n; i += step) {
-    const int k0 = (int)(i % chunks) * 8, r = (int)(i / chunks % rows), l = (int)(i / chunks / rows);
+  for (size_t i = (size_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; i < (size_t)s.L * rows;
+       i += (size_t)gridDim.x * (blockDim.x / kWave)) {
+    const int r = (int)(i % rows), l = (int)(i / rows);
     const bool on = r < s.N;
-    float v[8];
-    row_chunk((l < s.L ? s.h + (size_t)l * s.N * s.H : s.feed) + (size_t)r * s.H, s.H, k0, on, v);
-    store_act8(l < s.L ? s.h16 + l * s.plane : s.feed16, r, k0, s.kb, v);
+    float h[kMaxChunks][8], f[kMaxChunks][8], m = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMaxChunks; ++j) {
+      const int k0 = (lane + j * kWave) * 8;
+      row_chunk(s.h + ((size_t)l * s.N + r) * s.H, s.H, k0, on, h[j]);
+      row_chunk(s.feed + (size_t)r * s.H, s.H, k0, on && l == 0, f[j]);
+#pragma unroll
+      for (int v = 0; v < 8; ++v) {
+        const float a = fabsf(h[j][v]), b = fabsf(f[j][v]);
+        m = fmaxf(m, fmaxf(a <= 3.402823466e38f ? a : 0.f, b <= 3.402823466e38f ? b : 0.f));
+      }
+    }
+    m = wave_max(m);
+    // m < 2^(biased exponent - 126), also for zero and subnormal values with 1 in the place of their exponent
+    int e = 15 - (max((int)(__builtin_bit_cast(uint32_t, m) >> 23), 1) - 126);
+    if (l > 0) e = min(e, 14);
+    if (on && lane == 0) s.shift[(size_t)l * s.N + r] = e - kActExp;
+#pragma unroll
+    for (int j = 0; j < kMaxChunks; ++j) {
+      const int k0 = (lane + j * kWave) * 8;
+      if (k0 >= chunks * 8) continue;
+      store_act8(s.h16 + l * s.plane, r, k0, s.kb, h[j], e);
+      if (l == 0) store_act8(s.feed16, r, k0, s.kb, f[j], e);
+    }
   }
 }
 
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st) {
   if (!split && !tok) return hipSuccess;
-  const size_t n = split ? (size_t)(s.L + 1) * ((s.N + kFragRows - 1) / kFragRows * kFragRows) * s.kb * 4 : (size_t)s.N;
+  if (split && (!s.shift || s.kb * 4 > kMaxChunks * kWave)) return hipErrorInvalidValue;
+  const size_t n = split ? (size_t)s.L * ((s.N + kFragRows - 1) / kFragRows * kFragRows) * kWave : (size_t)s.N;
   size_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_prepare_step, dim3((unsigned)blocks), dim3(256), 0, st, s, split, tok, parent, V, tok_out,

@@ -65,3 +65,71 @@ def test_a_step_leaves_its_input_state_as_it_is(wdtype, hidden, layers, B, K):
             assert torch.equal(x, y)
         assert torch.equal(a[1], other[1]) and torch.equal(a[2], other[2])
     s.tr.close()
+
+
+def _exact(s):
+    """The step in 64 bits with torch: (h, c, feed)."""
+    t = {k: torch.from_numpy(v).cuda().double() for k, v in s.weights.items()}
+    par, H = s.par.long(), s.w.hidden
+    h, c, feed = (x.double()[..., par, :] for x in (s.h, s.c, s.feed))
+    x = torch.cat([t["E_tgt"][s.tok.long()], feed], 1)
+    hs, cs = [], []
+    for l in range(s.w.dec_layers):
+        z = torch.cat([x, h[l]], 1) @ t[f"dec{l}_W"].t().contiguous() + t[f"dec{l}_b"]
+        i, f, g, o = z.chunk(4, 1)
+        cs.append(torch.sigmoid(f) * c[l] + torch.sigmoid(i) * torch.tanh(g))
+        x = torch.sigmoid(o) * torch.tanh(cs[-1])
+        hs.append(x)
+    mem, keys, _, _ = (v.double() for v in s.tr.enc_views(s.ws, s.B, s.S))
+    e = torch.bmm(x.reshape(s.B, s.K, H), keys.transpose(1, 2).contiguous())
+    off = torch.arange(s.S, device="cuda")[None, None, :] >= s.lens[:, None, None]
+    ctx = torch.bmm(torch.softmax(e.masked_fill(off, -float("inf")), -1), mem).reshape(s.N, H)
+    return torch.stack(hs), torch.stack(cs), torch.tanh(torch.cat([ctx, x], 1) @ t["W_c"].t().contiguous())
+
+
+@pytest.mark.parametrize("wdtype,layers,log2", [
+    ("fp32", 1, -100), ("fp32", 1, -30), ("fp32", 1, 16), ("fp32", 1, 100), ("fp32", 2, 23), ("fp32", 3, -23),
+    ("fp32", 3, 16), ("bf16", 2, 16), ("bf16", 2, -23),
+])
+def test_states_of_any_size(wdtype, layers, log2):
+    # h and feed of size 2^log2 (every third row 2^9 smaller) against weights that bring their products back to size 1,
+    # so that an error of the operands reaches the outputs
+    hidden, emb = 100, 32
+    base = Step(wdtype, hidden, layers, 7, 5)
+    weights = dict(base.weights)
+    base.tr.close()
+    for l in range(layers):
+        W_l = weights[f"dec{l}_W"].copy()
+        W_l[:, emb if l == 0 else hidden:] *= np.float32(2.0) ** -log2
+        weights[f"dec{l}_W"] = W_l
+    s = Step(wdtype, hidden, layers, 7, 5, weights=weights)
+    print(f"[case] states of size 2^{log2} {wdtype} L{layers}", flush=True)
+    size = np.float32(2.0) ** np.where(np.arange(s.N) % 3 == 0, log2 - 9, log2).astype(np.float32)
+    for x in (s.h, s.feed):
+        v = s.rng.uniform(-1, 1, tuple(x.shape)).astype(np.float32) * size[:, None]
+        x.copy_(torch.from_numpy(v))
+    s.c.copy_(torch.from_numpy(s.rng.uniform(-1, 1, tuple(s.c.shape)).astype(np.float32)))
+    got = s.tr.state_views(s.step()[0], s.N)
+    # sums of 200 products of size <= 0.1 with operands good to 2^-22 each, then functions of slope <= 1 (twice over
+    # the layers and the output)
+    for x, y in zip(got, _exact(s)):
+        assert (x.double() - y).abs().max().item() <= 2e-6 * (1 + layers)
+    s.tr.close()
+
+
+@pytest.mark.parametrize("spike", [5e3, 1e6, 3e38])
+def test_single_large_elements_saturate_their_gates(spike):
+    # one element of a row far beyond the rest: the gates it reaches saturate by its sign, the row stays finite
+    s = Step("fp32", 100, 2, 7, 5)
+    print(f"[case] spike {spike}", flush=True)
+    for l in range(2):
+        s.h[l, torch.arange(s.N), torch.arange(s.N) % 100] = spike
+    s.feed[3, 7] = -spike
+    got = s.tr.state_views(s.step()[0], s.N)
+    # |w| >= 1e-5 on a spike of 5e3 leaves no gate between the states beyond the rounding of its product (2^-21 of it)
+    near = 2.0 ** -21 * 0.1 * spike
+    for x, y in zip(got, _exact(s)):
+        assert torch.isfinite(x).all()
+        d = (x.double() - y).abs()
+        assert d.max().item() <= (near if near < 1 else 2) and (d > 1e-4).double().mean().item() <= 1e-3
+    s.tr.close()
