@@ -152,3 +152,18 @@ def test_filters_default_sampled(default):
         forced = O.score_forced(s.model, s.src[b], s.lens[b], toks)
         assert np.abs(forced - out["tok_logp"][b, :n]).max() <= s.tau
         assert ((out["align"][b, :n] >= 0) & (out["align"][b, :n] < s.lens[b])).all()
+
+
+@pytest.mark.parametrize("vocab,K,banned,max_unk", [
+    (300, 5, (5, 17, 200), 0), (1000, 12, tuple(range(4, 90)), 1), (40, 12, tuple(range(4, 38)), -1),
+])
+def test_filters_with_fewer_tiles_than_k(vocab, K, banned, max_unk):
+    w = with_workload(W.get("tiny"), tgt_vocab=vocab, src_vocab=vocab)
+    s = Setup(w, peaked=True)
+    _case("filters_small", vocab=vocab, K=K, n_banned=len(banned), max_unk=max_unk)
+    out = _search(s, K, 8, 0.6, banned=banned, max_unk=max_unk)
+    res = O.beam_search(s.model, s.src, s.lens, K, 8, 0.6, banned=banned, max_unk=max_unk)
+    for b in range(s.src.shape[0]):
+        n = int(out["len"][b])
+        assert list(out["tok"][b, :n]) == res.tokens[b], b
+        assert abs(out["raw"][b] - res.raw[b]) <= s.tau * n

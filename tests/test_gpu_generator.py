@@ -75,3 +75,29 @@ def test_generator_rows_of_large_and_tiny_weights():
     size = feed.abs() @ Ws.abs().t().contiguous() + z.abs() + lse.double()[:, None].abs()
     assert (((logp + lse[:, None]).double() - z).abs() <= size * 2.0 ** -20 + 1e-6).all()
     tr.close()
+
+
+@pytest.mark.parametrize("vocab,K", [
+    (5, 5), (12, 12), (63, 16), (65, 5), (128, 2), (129, 3), (300, 12), (1000, 12), (1920, 16), (1921, 16),
+])
+@pytest.mark.parametrize("kind", ["peaked", "ties", "few"])
+def test_top_k_with_fewer_tiles_than_k(vocab, K, kind):
+    # vocabularies of at most 128 (K - 1) words (and one beyond): "ties" has logits of a few distinct values, "few" fewer
+    # finite logits than K
+    w = with_workload(W.get("tiny"), hidden=64, emb=32, tgt_vocab=vocab, batch=3, beam=K)
+    weights = W.make_weights(w, peaked=True)
+    if kind != "peaked":
+        weights["W_s"] = np.zeros_like(weights["W_s"])
+        weights["b_s"] = (np.arange(vocab) * 7 % 5).astype(np.float32)
+    if kind == "few":
+        weights["b_s"][np.arange(vocab) % max(2, vocab // 2) != 1] = -np.inf
+    tr = translator_for(w, weights)
+    print(f"[case] top-K of {vocab} words, K{K}, {kind}", flush=True)
+    (_, logp, _, _, _), (_, tv, ti, _, _) = _step(tr, w, 3, K)
+    lp = logp.cpu().numpy()
+    ids = np.argsort(-lp, axis=1, kind="stable")[:, :K]
+    want = np.take_along_axis(lp, ids, 1)
+    ids = np.where(np.isfinite(want), ids, 0x7fffffff)       # no candidate
+    np.testing.assert_array_equal(ti.cpu().numpy(), ids)
+    np.testing.assert_array_equal(tv.cpu().numpy(), want)
+    tr.close()
