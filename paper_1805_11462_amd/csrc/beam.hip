@@ -68,7 +68,9 @@ __device__ inline bool filtered(const GenPartials& gp, bool blocked_unk, int c) 
 
 // tm / tq: the row's tile maxima and sums from row_tiles_load (tm is overwritten). The wave writes out_val[k] =
 // logit - lse and out_id[k] for k < K (-inf and the largest id where fewer candidates exist), lane 0 *out_lse.
-// sv / si / qt: this wave's LDS scratch (kSurvivorCap survivors, kQualCap qualifying tile ids).
+// sv / si / qt: this wave's LDS scratch (kSurvivorCap survivors, kQualCap qualifying tile ids). SMALL: logits of fewer
+// tiles than K.
+template <bool SMALL>
 __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], const float (&tq)[kMaxTilesPerLane],
                                                const GenPartials& gp, int row, int K, float* sv, int* si, int* qt,
                                                float* out_val, int32_t* out_id, float* out_lse) {
@@ -99,11 +101,10 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
   };
   const float* lrow = gp.logits ? gp.logits + (size_t)row * gp.ld_logits : nullptr;
   const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  const bool small = lrow && ntiles < K;
-  float sc[kSmallCols];
+  float sc[SMALL ? kSmallCols : 1];
   float theta, cur = ninf;
   int nq = 0;
-  if (small) {             // candidates only, so that theta bounds the allowed ones
+  if constexpr (SMALL) {   // candidates only, so that theta bounds the allowed ones
 #pragma unroll
     for (int j = 0; j < kSmallCols; ++j) {
       const int c = lane + j * kWave;
@@ -152,7 +153,7 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
     }
     n += __popcll(m);
   };
-  if (small) {
+  if constexpr (SMALL) {
 #pragma unroll
     for (int j = 0; j < kSmallCols; ++j)
       if (j * kWave < gp.V) add(sc[j] > ninf && sc[j] >= theta, sc[j], lane + j * kWave);
@@ -247,6 +248,7 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
 
 constexpr int kMergeWaves = 4;
 
+template <bool SMALL>
 __global__ __launch_bounds__(kMergeWaves * kWave) void k_lse_topk(GenPartials gp, int M, int K,
                                                                   float* __restrict__ out_val,
                                                                   int32_t* __restrict__ out_id,
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void k_lse_topk(GenPartials gp
   const size_t base = (size_t)row * gp.ntiles;
   float tm[kMaxTilesPerLane], tq[kMaxTilesPerLane];
   row_tiles_load(gp.pmax + base, gp.psum + base, gp.ntiles, tm, tq);
-  row_merge_wave(tm, tq, gp, row, K, sv[w], si[w], qt[w], out_val + (size_t)row * K,
+  row_merge_wave<SMALL>(tm, tq, gp, row, K, sv[w], si[w], qt[w], out_val + (size_t)row * K,
                  out_id ? out_id + (size_t)row * K : nullptr, out_lse ? out_lse + row : nullptr);
 }
 
@@ -268,7 +270,8 @@ hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, i
                           hipStream_t st) {
   if (gp.ntiles > kWave * kMaxTilesPerLane || K < 1 || K > kMaxBeam || (!gp.logits && !gp.pval)) return hipErrorInvalidValue;
   const dim3 grid((M + kMergeWaves - 1) / kMergeWaves), block(kMergeWaves * kWave);
-  hipLaunchKernelGGL(k_lse_topk, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
+  if (gp.logits && gp.ntiles < K) hipLaunchKernelGGL(k_lse_topk<true>, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
+  else hipLaunchKernelGGL(k_lse_topk<false>, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
   return hipGetLastError();
 }
 
@@ -410,6 +413,7 @@ hipError_t beam_init(const BeamParams& p, int bos, hipStream_t st) {
 // the smaller slot winning ties. Lane r of wave 0 ends up holding the rank-r choice, and the lanes write
 // the outcome together: EOS (or any choice at the last step) goes to the finished pool, which keeps only
 // its best entry by normalised score (earlier rank on ties), the others fill the live slots in rank order.
+template <bool SMALL>
 __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, GenPartials gp, int t, double lp_t) {
   __shared__ float sv[kMaxBeam][kSurvivorCap];
   __shared__ int si[kMaxBeam][kSurvivorCap];
@@ -439,7 +443,7 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
     best_t0 = p.best_t[b];
   }
   if (my_score > ninf) {
-    row_merge_wave(tm, tq, gp, r0 + w, K, sv[w], si[w], qt[w], tkv[w], tki[w], nullptr);
+    row_merge_wave<SMALL>(tm, tq, gp, r0 + w, K, sv[w], si[w], qt[w], tkv[w], tki[w], nullptr);
   }
   __syncthreads();
   if (w != 0) return;
@@ -551,7 +555,9 @@ __global__ __launch_bounds__(kMaxBeam * kWave) void k_beam_step(BeamParams p, Ge
 hipError_t beam_step(const BeamParams& p, const GenPartials& gp, int t, hipStream_t st) {
   if (gp.ntiles > kWave * kMaxTilesPerLane || p.K > kMaxBeam) return hipErrorInvalidValue;
   const double lp_t = std::pow((5.0 + t) / 6.0, p.alpha);     // GNMT length penalty of this step
-  hipLaunchKernelGGL(k_beam_step, dim3(p.B), dim3(p.K * kWave), 0, st, p, gp, t, lp_t);
+  const dim3 grid(p.B), block(p.K * kWave);
+  if (gp.logits && gp.ntiles < p.K) hipLaunchKernelGGL(k_beam_step<true>, grid, block, 0, st, p, gp, t, lp_t);
+  else hipLaunchKernelGGL(k_beam_step<false>, grid, block, 0, st, p, gp, t, lp_t);
   return hipGetLastError();
 }
 
