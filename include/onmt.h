@@ -154,7 +154,7 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
  * The rest of the buffer holds copies of h and feed that the library writes. A caller may write h, c and feed
  * between steps, values of any finite size: a step makes its copies anew, in state_out, and never writes state_in.
  * Every row of a layer's product carries a power of two of its own there; entries keep 22 bits down to 2^-28 of the
- * row's largest (of 1 if that is larger, in layers above the first), smaller ones an absolute 2^-50 of it. (Exception: bf16 models whose hidden size is a multiple of 8
+ * row's largest (of 1 if that is larger, in layers above the first), smaller ones an absolute 2^-50 of it, and an infinity counts as the largest finite value. (Exception: bf16 models whose hidden size is a multiple of 8
  * read the copies beside the state they are given; for them only c may be written.)
  *
  * onmt_decode_init writes into state_out the decoder's initial state: every layer's (h, c) from the

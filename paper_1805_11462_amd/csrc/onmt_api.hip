@@ -334,7 +334,8 @@ struct HostImage {
 
 // n weights as the products take them (bf16 models: rounded).
 void weight_row(const HostImage& img, const float* src, int n, float* dst) {
-  for (int j = 0; j < n; ++j) dst[j] = img.bf16 ? host_bf16_to_f32(f32_to_bf16_bits(src[j])) : src[j];
+  for (int j = 0; j < n; ++j)
+    dst[j] = img.bf16 ? finite_or_nan(host_bf16_to_f32(f32_to_bf16_bits(src[j])), 0x10000u) : finite_or_nan(src[j]);
 }
 
 // Row r of a matrix or embedding table: columns w[i] values of src[i] from K block kb[i] on, under one row exponent.

@@ -10,6 +10,10 @@
 //   hi.hi + (hi.lo + lo.hi) 2^-11
 // with the two parts in separate fp32 accumulators; lo.lo, below 2^-22 of the leading product, is dropped.
 //
+// Infinities: a product of an infinite term and the other operand's zero lo term is NaN, where the fp32 product is an
+// infinity that its gate saturates at. An infinite weight, embedding or state element is therefore carried as the
+// largest finite value of its sign, which the row's scale takes in; NaN stays NaN.
+//
 // Layout: 16 rows x 32 columns form a block of 64 x 16 bytes, lane l = (k % 32 / 8) * 16 + r % 16 holding
 // columns 8 (l / 16) .. + 7 of row l % 16: what lane l of v_mfma_f32_16x16x32_f16 takes. Blocks of a row
 // block follow each other along K, the lo block right after its hi block. A wave thus loads a fragment with one
@@ -48,6 +52,12 @@ __host__ __device__ inline size_t split16_at(size_t r, int k, int kblocks, int t
 }
 inline size_t split16_bytes(size_t rows, int kblocks, int terms) {
   return (rows + kFragRows - 1) / kFragRows * kblocks * (size_t)(kFragElems * terms) * 2;
+}
+
+// An infinite value's largest finite stand-in (`step`: 1, or 0x10000 for values of bf16 precision).
+__device__ __host__ inline float finite_or_nan(float x, uint32_t step = 1) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  return __builtin_bit_cast(float, (u & 0x7fffffffu) == 0x7f800000u ? u - step : u);
 }
 
 // The two terms of a scaled value. One past fp16's range becomes an infinity (with lo = 0, so that its

@@ -515,7 +515,7 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
 // The id checks (tok given) and the two-term copies of a caller's state (split; s.h16 and s.feed16 lie in the step's
 // output state), one launch. A caller's rows may be of any size, so each row of a layer's product gets a power of two
 // of its own: one wave reads what that product reads of the row (layer 0: feed and h, else h), scales its largest
-// finite value to [2^14, 2^15) and records the power. In layers above 0 the same power also scales the output of the
+// value to [2^14, 2^15) and records the power. In layers above 0 the same power also scales the output of the
 // layer below, which is at most 1 in size, so there it is at most 2^14.
 constexpr int kMaxChunks = 2;                 // 8-column chunks per lane (H <= 1024)
 
@@ -559,8 +559,9 @@ __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, 
       row_chunk(s.feed + (size_t)r * s.H, s.H, k0, on && l == 0, f[j]);
 #pragma unroll
       for (int v = 0; v < 8; ++v) {
-        const float a = fabsf(h[j][v]), b = fabsf(f[j][v]);
-        m = fmaxf(m, fmaxf(a <= 3.402823466e38f ? a : 0.f, b <= 3.402823466e38f ? b : 0.f));
+        h[j][v] = finite_or_nan(h[j][v]);
+        f[j][v] = finite_or_nan(f[j][v]);
+        m = fmaxf(m, fmaxf(fabsf(h[j][v]), fabsf(f[j][v])));      // a NaN is passed over
       }
     }
     m = wave_max(m);

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import workloads as W
+from oracle import onmt_oracle as O
 from paper_1805_11462_amd import _lib
 from paper_1805_11462_amd.translator import _ptr, _stream
 from ._gpu import translator_for, with_workload
@@ -133,3 +134,55 @@ def test_single_large_elements_saturate_their_gates(spike):
         d = (x.double() - y).abs()
         assert d.max().item() <= (near if near < 1 else 2) and (d > 1e-4).double().mean().item() <= 1e-3
     s.tr.close()
+
+
+@pytest.mark.parametrize("what", ["state", "weight", "embedding"])
+@pytest.mark.parametrize("wdtype,layers", [("fp32", 1), ("fp32", 3), ("bf16", 2)])
+def test_an_infinite_element_saturates_its_gates(what, wdtype, layers):
+    base = Step(wdtype, 100, layers, 7, 5)
+    weights = {k: v.copy() for k, v in base.weights.items()}
+    base.tr.close()
+    if what == "weight":          # units 3 and 8 of every layer: input gate by the first column of [below], forget by h
+        for l in range(layers):
+            weights[f"dec{l}_W"][3, 32 if l == 0 else 0] = np.inf
+            weights[f"dec{l}_W"][108, -5] = -np.inf
+    s = Step(wdtype, 100, layers, 7, 5, weights=weights)
+    print(f"[case] infinite {what} {wdtype} L{layers}", flush=True)
+    if what == "state":
+        rows = torch.arange(s.N)
+        s.feed[rows[::2], 7] = float("inf")                   # one infinity per row of a layer's product
+        s.h[0, rows[1::2], 99] = -float("inf")
+        s.h[1:, rows, rows % 100] = float("inf")
+    if what == "embedding":
+        s.weights = dict(weights)
+        s.weights["E_tgt"][s.tok[0].item(), 9] = np.inf       # (also of the first step's token: that state is kept)
+        state = s.state.clone()
+        s.tr.close()
+        s.tr = translator_for(s.w, s.weights)
+        s.ws = s.tr.encode(torch.full((s.B, s.S), 5, dtype=torch.int32, device="cuda"), s.lens)
+        s.state = state
+        s.h, s.c, s.feed = s.tr.state_views(state, s.N)
+    for x, y in zip(s.tr.state_views(s.step()[0], s.N), _exact(s)):
+        assert torch.isfinite(y).all()
+        assert (x.double() - y).abs().max().item() <= 1e-5 * (1 + layers)
+    s.tr.close()
+
+
+@pytest.mark.parametrize("wdtype", ["fp32", "bf16"])
+def test_an_infinite_source_embedding_saturates_its_gates(wdtype):
+    # a 2-layer encoder over 136-wide embeddings (five K blocks, no multiple of the projection's stages)
+    w = with_workload(W.get("tiny"), emb=136, hidden=64, enc_layers=2, dec_layers=2, wdtype=wdtype)
+    weights = W.make_weights(w)
+    weights["E_src"][[6, 9], [135, 3]] = np.inf, -np.inf
+    tr = translator_for(w, weights)
+    print(f"[case] infinite embedding {wdtype}", flush=True)
+    src = np.random.default_rng(3).integers(4, 12, (5, 7)).astype(np.int32)
+    lens = np.array([7, 6, 7, 1, 3], np.int32)
+    ws = tr.encode(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda())
+    mem = tr.enc_views(ws, 5, 7)[0].cpu().numpy()
+    src[np.arange(7)[None, :] >= lens[:, None]] = W.PAD_ID
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = O.encode(O.model_from(w, weights), src, lens).memory
+    assert np.isfinite(want).all()
+    np.testing.assert_allclose(mem, want, atol=1e-5, rtol=0)
+    tr.close()
