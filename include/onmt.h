@@ -62,8 +62,13 @@ typedef struct {
                                       projection runs them as three fp16 term products of two-term
                                       scaled splits of both operands, accumulated in fp32, closer to
                                       64 bits than fp32 products); 1 = bf16 weights and MFMA operands
-                                      (activations as bf16 or fp16 terms), fp32 accumulation, cell
-                                      state and softmax */
+                                      (weights as one fp16 term, activations as two), fp32
+                                      accumulation, cell state and softmax. Every product's operands
+                                      are such splits: weights and embeddings keep 22 bits (bf16
+                                      ones: all 8) down to 2^-28 of their row's largest entry (2^-31)
+                                      and smaller ones an absolute 2^-50 (2^-39) of it; the layers'
+                                      own outputs, at most 1, keep 22 bits down to 2^-18 and smaller
+                                      ones an absolute 2^-40 */
   int pad_id, unk_id, bos_id, eos_id;
   int attn_type;                   /* attention score (Section 4.2 names three types, none with biases):
                                       ONMT_ATTN_GENERAL e_s = q . W_a m_s;
@@ -138,7 +143,8 @@ int onmt_model_destroy(onmt_model* model);
  * ids in [0, src_vocab). Positions >= len[b] are ignored. Writes the memory bank, the attention keys
  * (general: W_a m_s; concat: the memory columns of W_a times m_s; dot: none, the scores read the
  * memory) and the final states into enc_ws (>= onmt_encode_ws_bytes(model, B, S_max)), which the
- * decoder calls then read. With host validation (the default) src and len are checked by a kernel the
+ * decoder calls then read (as written here; in their products entries of the memory keep 22 bits from 2^-18 to 4094
+ * in size). With host validation (the default) src and len are checked by a kernel the
  * call waits for (one stream sync), then the encoder is enqueued asynchronously; with device validation
  * nothing waits. The GEMMs read operands through 2 GiB buffer descriptors: a batch whose memory bank
  * (B * S_max rows of the memory width padded to 128 columns, fp32) or decoder state rows (B * beam rows)

@@ -2,9 +2,10 @@
 //
 // Values: an fp32 value x is carried as hi = fp16(s) and lo = fp16((s - hi) 2^11) of s = x 2^e, round to
 // nearest even each, so x = (hi + lo 2^-11) 2^-e to 22 significant bits or better (three values in four are
-// exact to all 24). Activations of the recurrences are outputs of tanh and sigmoid, at most 1 in size, but a
-// caller's own state may hold more: e = kActExp takes values up to 4094 and keeps the full precision down to
-// 3.8e-6, and below that an absolute 5e-13 (e = 10 stopped at 63.9: larger states became infinities).
+// exact to all 24). Activations are outputs of tanh and sigmoid or averages of them, at most 1 in size: their e =
+// kActExp keeps the full precision down to 3.8e-6 and below that an absolute 9.1e-13 (2^-40), and leaves room up to
+// 4094 for a caller that replaces the memory bank. A caller's own decoder state, which may hold anything, gets an
+// exponent per row (k_prepare_step).
 // Weights are scaled per row (e = the exponent that takes the row's largest value to [2^14, 2^15)), so every
 // finite fp32 weight is in range; the kernels undo both scales in one ldexp per output. A product is
 //   hi.hi + (hi.lo + lo.hi) 2^-11

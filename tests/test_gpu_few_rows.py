@@ -76,19 +76,68 @@ def test_decoder_layers(wdtype, hidden, layers, B, K, own_state):
     tr.close()
 
 
-def test_zero_and_tiny_states_stay_exact():
-    # zero weights: h and feed stay zero; tiny weights: the operand split keeps relative precision
-    for scale in (0.0, 1e-4):
-        w = with_workload(W.get("tiny"), batch=3)
-        weights = {k: (v * np.float32(scale)).astype(np.float32) for k, v in W.make_weights(w).items()}
-        tr = translator_for(w, weights)
-        src, lens = W.make_batch(w, batch=3)
-        buf = tr.search_buffers(3, src.shape[1], 2, 4)
-        tr.beam_search(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda(), buf)
-        m = O.model_from(w, weights)
-        for b in range(3):
-            n = int(buf["len"][b])
-            toks = [int(x) for x in buf["tok"][b, :n].cpu()]
-            ref = O.score_forced(m, src[b], lens[b], toks)
-            np.testing.assert_allclose(buf["tok_logp"][b, :n].cpu().numpy(), ref, atol=2e-6)
-        tr.close()
+def test_zero_states_stay_zero():
+    w = with_workload(W.get("tiny"), batch=3)
+    weights = {k: np.zeros_like(v) for k, v in W.make_weights(w).items()}
+    tr = translator_for(w, weights)
+    src, lens = W.make_batch(w, batch=3)
+    buf = tr.search_buffers(3, src.shape[1], 2, 4)
+    tr.beam_search(torch.from_numpy(src).cuda(), torch.from_numpy(lens).cuda(), buf)
+    m = O.model_from(w, weights)
+    for b in range(3):
+        n = int(buf["len"][b])
+        toks = [int(x) for x in buf["tok"][b, :n].cpu()]
+        ref = O.score_forced(m, src[b], lens[b], toks)
+        np.testing.assert_allclose(buf["tok_logp"][b, :n].cpu().numpy(), ref, atol=2e-6)
+    tr.close()
+
+
+@pytest.mark.parametrize("log2", [-6, -14, -24])
+def test_tiny_states_keep_the_precision_of_their_format(log2):
+    # the weights that make the memory and h are small, those that multiply them large, so that an error of the operands
+    # reaches the keys and the feed: operands are good to 2^-22 of the value or an absolute 2^-40 (a product doubles
+    # what it keeps of the first, for the weights' own terms)
+    w = with_workload(W.get("tiny"), batch=5)
+    weights = {k: v.copy() for k, v in W.make_weights(w).items()}
+    H, scale = w.hidden, np.float32(2.0) ** log2
+    for k in ("enc0_fwd_W", "enc0_fwd_b", "dec0_W", "dec0_b"):
+        weights[k] *= scale
+    weights["W_a"] = weights["W_a"] / scale
+    weights["W_c"][:, H:] /= scale                       # columns [context | h]
+    tr = translator_for(w, weights)
+    print(f"[case] tiny states 2^{log2}", flush=True)
+    rng = np.random.default_rng(7)
+    B, S, K = 5, 6, 2
+    src = torch.from_numpy(rng.integers(4, w.src_vocab, (B, S)).astype(np.int32)).cuda()
+    lens = torch.full((B,), S, dtype=torch.int32, device="cuda")
+    ws = tr.encode(src, lens)
+    mem, keys, _, _ = (x.double() for x in tr.enc_views(ws, B, S))
+    assert 0 < mem.abs().max() < 4 * scale               # the encoder's outputs did shrink
+    t = {k: torch.from_numpy(v).cuda().double() for k, v in weights.items()}
+
+    def operand(x):
+        return 2.0 ** -21 * x.abs() + 2.0 ** -40
+
+    def close(got, x, W_, err):
+        want, size = x @ W_.t().contiguous(), W_.abs().t().contiguous()
+        sums = 2.0 ** -22 * (x.abs() @ size)             # the accumulators' roundings, two per 32 products
+        return (got - want).abs(), err @ size + sums + 2.0 ** -23 * want.abs()
+
+    d, bound = close(keys, mem, t["W_a"], operand(mem))
+    assert (d <= bound).all() and keys.abs().max() > 1e-3
+    # the memory itself: sums of 96 products good to 2^-21 each, and functions that keep relative precision near 0
+    enc = O.encode(O.model_from(w, weights), src.cpu().numpy(), lens.cpu().numpy())
+    np.testing.assert_allclose(mem.cpu().numpy(), enc.memory, atol=2e-6 * float(mem.abs().max()), rtol=0)
+
+    N = B * K
+    tok = torch.from_numpy(rng.integers(4, w.tgt_vocab, N).astype(np.int32)).cuda()
+    st, _, _, _, attn = tr.decode_step(ws, B, S, K, tr.decode_init(ws, B, S, K), tok, None, mode=1, want_attn=True)
+    h, _, feed = (x.double() for x in tr.state_views(st, N))
+    ctx = torch.bmm(attn.double().reshape(B, K, S), mem).reshape(N, H)
+    x = torch.cat([ctx, h[0]], 1)
+    err = operand(x) + 2.0 ** -22 * torch.cat([ctx.abs(), torch.zeros_like(h[0])], 1)    # (the context's own sum)
+    size = t["W_c"].abs().t().contiguous()
+    z = x @ t["W_c"].t().contiguous()
+    bound = err @ size + 2.0 ** -22 * (x.abs() @ size) + 2e-7                            # slope <= 1; tanhf's own error
+    assert ((feed - torch.tanh(z)).abs() <= bound).all() and feed.abs().max() > 1e-3
+    tr.close()
