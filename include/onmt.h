@@ -174,7 +174,8 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
  *                   smaller id on ties.
  *   lse [N] (optional) = logsumexp of each row's logits. attn [N, S_max] (optional) = attention weights,
  *   exactly 0 at pads.
- * step_ws holds onmt_step_ws_bytes(model, B, S_max, K) bytes of scratch. With host validation (the default)
+ * step_ws holds onmt_step_ws_bytes(model, B, S_max, K) bytes of scratch, most of it the step's logits (4 bytes per
+ * row and vocabulary entry, for K > 1; where they would pass 16 GiB, 8 K bytes per row and 128 entries instead). With host validation (the default)
  * prev_tok and parent are checked by a kernel the call waits for (one stream sync), then the compute is
  * enqueued asynchronously; with device validation (onmt_set_validation below) nothing waits. */
 size_t onmt_state_bytes(const onmt_model* model, int N);

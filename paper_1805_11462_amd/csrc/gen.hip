@@ -52,7 +52,8 @@ struct GenWide : WideTile<TM, 4, 2, PB, NSTG, D> {
 };
 
 // Top-K lists of a 64 x 128 tile staged in LDS: 4 threads per row, 32 interleaved columns each, K rounds of a
-// 4-lane argmax (larger logit first, smaller id on ties), each thread skipping the columns it gave away.
+// 4-lane argmax (larger logit first, smaller id on ties), each thread skipping the columns it gave away and those
+// that are no candidates (hypothesis filters).
 __device__ inline void gen_lists(const float* Ct, int crow, const GenParams& p, int M, int m0, int n0, int nt, int tid) {
   const int r = tid >> 2, part = tid & 3;
   const int row = m0 + r;
@@ -60,6 +61,14 @@ __device__ inline void gen_lists(const float* Ct, int crow, const GenParams& p, 
   float z[32];
 #pragma unroll
   for (int j = 0; j < 32; ++j) z[j] = Ct[r * crow + 4 * j + part];
+  if (p.pfmax) {
+    const bool unk = p.unk_cnt && row < M && p.max_unk >= 0 && p.unk_cnt[row] >= p.max_unk;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+      const int c = n0 + 4 * j + part;
+      if (c < p.V && ((p.banned_bits && ((p.banned_bits[c >> 5] >> (c & 31)) & 1u)) || (unk && c == p.unk_id))) z[j] = ninf;
+    }
+  }
   const size_t o = ((size_t)row * p.ntiles + nt) * p.K;
   uint32_t taken = 0;
   for (int k = 0; k < p.K; ++k) {
@@ -405,7 +414,7 @@ hipError_t gemm_gen(const Split16& a, const Split16& w, int w_terms, const GenPa
   const uint64_t lim = 1ull << 32;
   if ((w_terms != 1 && w_terms != 2) || a.rows < 1 || w.rows < 1 || w.rows % 128 || a.kblocks < 1 || a.kblocks != w.kblocks ||
       split16_bytes(a.rows, a.kblocks, 2) >= lim || split16_bytes(w.rows, w.kblocks, w_terms) >= lim ||
-      (p.pval && (p.logits || p.K < 1)) || (p.pfmax && !p.logits && !(p.pval && p.K == 1)))
+      (p.pval && (p.logits || p.K < 1)) || (p.pfmax && !p.logits && !p.pval))
     return hipErrorInvalidValue;
   return w_terms == 1 ? gen_dispatch<1>(a, w, p, st) : gen_dispatch<2>(a, w, p, st);
 }

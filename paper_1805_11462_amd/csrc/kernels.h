@@ -93,7 +93,7 @@ struct GenParams {
   float* pmax;                  // [M, ntiles]
   float* psum;                  // [M, ntiles]
   float* pval;                  // optional [M, ntiles, K] top-K lists instead of logits: K = 1, or callers without
-  int32_t* pid;                 // room for logits (no filters then)
+  int32_t* pid;                 // room for logits
   float* logits;                // optional [M, ld_logits]
   int ld_logits;
   const int32_t* want;          // optional [M]: column whose logit is copied to want_logit[row]

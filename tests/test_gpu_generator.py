@@ -101,3 +101,36 @@ def test_top_k_with_fewer_tiles_than_k(vocab, K, kind):
     np.testing.assert_array_equal(ti.cpu().numpy(), ids)
     np.testing.assert_array_equal(tv.cpu().numpy(), want)
     tr.close()
+
+
+def test_batches_of_very_many_rows_keep_top_k_lists():
+    # 32800 rows of 131072 logits would pass 16 GiB: the workspace holds per-tile top-K lists instead, filters included
+    B, S, K, V = 2050, 4, 16, 131072
+    w = with_workload(W.get("tiny"), hidden=36, emb=32, tgt_vocab=V, beam=K)
+    tr = translator_for(w, W.make_weights(w, peaked=True))
+    print(f"[case] lists for {B * K} rows of {V}", flush=True)
+    assert 0 < tr.lib.onmt_step_ws_bytes(tr.handle, B, S, K) < 5 << 30
+    (_, logp, _, lse, _), (_, tv, ti, lse1, _) = _step(tr, w, B, K)
+    assert torch.equal(lse, lse1)
+    for r0 in range(0, B * K, 4096):
+        lp, v, i = logp[r0:r0 + 4096], tv[r0:r0 + 4096], ti[r0:r0 + 4096].long()
+        assert torch.equal(torch.topk(lp, K, dim=1)[0], v) and torch.equal(torch.gather(lp, 1, i), v)
+        i = i.sort(dim=1)[0]
+        assert (i[:, 1:] > i[:, :-1]).all()
+    del logp
+    # the same sentences alone, whose logits fit: the same tokens under filters (margins of a peaked model are far
+    # above rounding), their scores to a few roundings
+    rng = np.random.default_rng(5)
+    src = torch.from_numpy(rng.integers(4, w.src_vocab, (B, S)).astype(np.int32)).cuda()
+    lens = torch.full((B,), S, dtype=torch.int32, device="cuda")
+    free = tr.beam_search(src, lens, tr.search_buffers(B, S, K, 2))["tok"][:, 0]
+    banned = tuple(int(x) for x in torch.unique(free)[:40].cpu() if x != W.EOS_ID)
+    outs = []
+    for s, n in ((src, lens), (src[-8:].contiguous(), lens[-8:].contiguous())):
+        buf = tr.search_buffers(s.shape[0], S, K, 3, banned=banned, max_unk=0)
+        tr.beam_search(s, n, buf)
+        outs.append((buf["tok"][-8:].clone(), buf["raw"][-8:].clone()))
+        assert not set(buf["tok"].flatten().tolist()) & (set(banned) | {W.UNK_ID})
+    assert torch.equal(outs[0][0], outs[1][0])
+    assert (outs[0][1] - outs[1][1]).abs().max() <= 2e-5
+    tr.close()
