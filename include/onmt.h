@@ -158,10 +158,11 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
  * A decoder state buffer holds, fp32: h [dec_layers, N, hidden], c [dec_layers, N, hidden],
  * feed [N, hidden] (the previous attentional vector), in that order, onmt_state_bytes(model, N) bytes.
  * The rest of the buffer holds copies of h and feed that the library writes. A caller may write h, c and feed
- * between steps, values of any finite size: a step makes its copies anew, in state_out, and never writes state_in.
- * Every row of a layer's product carries a power of two of its own there; entries keep 22 bits down to 2^-28 of the
- * row's largest (of 1 if that is larger, in layers above the first), smaller ones an absolute 2^-50 of it, and an infinity counts as the largest finite value. (Exception: bf16 models whose hidden size is a multiple of 8
- * read the copies beside the state they are given; for them only c may be written.)
+ * between steps, values of any finite size: a step makes its copies anew, in state_out, and never writes
+ * state_in. Every row of a layer's product carries a power of two of its own there; entries keep 22 bits down
+ * to 2^-28 of the row's largest (of 1 if that is larger, in layers above the first), smaller ones an absolute
+ * 2^-50 of it, and an infinity counts as the largest finite value. (Exception: bf16 models whose hidden size
+ * is a multiple of 8 read the copies beside the state they are given; for them only c may be written.)
  *
  * onmt_decode_init writes into state_out the decoder's initial state: every layer's (h, c) from the
  * encoder's final step of sentence b = r / K, and feed = 0.
@@ -174,10 +175,11 @@ int onmt_encode(onmt_model* model, const int32_t* src, const int32_t* len, int B
  *                   smaller id on ties.
  *   lse [N] (optional) = logsumexp of each row's logits. attn [N, S_max] (optional) = attention weights,
  *   exactly 0 at pads.
- * step_ws holds onmt_step_ws_bytes(model, B, S_max, K) bytes of scratch, most of it the step's logits (4 bytes per
- * row and vocabulary entry, for K > 1; where they would pass 16 GiB, 8 K bytes per row and 128 entries instead). With host validation (the default)
- * prev_tok and parent are checked by a kernel the call waits for (one stream sync), then the compute is
- * enqueued asynchronously; with device validation (onmt_set_validation below) nothing waits. */
+ * step_ws holds onmt_step_ws_bytes(model, B, S_max, K) bytes of scratch, most of it the step's logits (4
+ * bytes per row and vocabulary entry, for K > 1; where they would pass 16 GiB, 8 K bytes per row and 128
+ * entries instead). With host validation (the default) prev_tok and parent are checked by a kernel the call
+ * waits for (one stream sync), then the compute is enqueued asynchronously; with device validation
+ * (onmt_set_validation below) nothing waits. */
 size_t onmt_state_bytes(const onmt_model* model, int N);
 size_t onmt_step_ws_bytes(const onmt_model* model, int B, int S_max, int K);
 int onmt_decode_init(onmt_model* model, const void* enc_ws, int B, int S_max, int K, void* state_out,
@@ -187,14 +189,15 @@ int onmt_decode_step(onmt_model* model, const void* enc_ws, int B, int S_max, in
                      int32_t* ids, float* lse, float* attn, void* step_ws, size_t step_ws_bytes, void* stream);
 
 /* ---- Input validation ---------------------------------------------------------------------------------
- * ONMT_VALIDATE_HOST (the default): onmt_encode, onmt_decode_step and onmt_beam_search wait for a kernel
- * that checks their device id / length inputs before enqueuing anything else, returning ONMT_EINVAL on a
- * bad value (one stream sync per call). ONMT_VALIDATE_DEVICE: the call does not wait for that kernel; a bad value is replaced by a safe one (a length
- * clamped to [1, S_max], an id by 0, a parent by the row itself), the computation goes on, and the model
- * records the failure. In this mode the encoder steps over all S_max positions (the host does not learn
- * the longest length), which gives the same results. onmt_device_status sets *code to ONMT_OK or
- * ONMT_EINVAL (onmt_last_error then says what was wrong) for the work enqueued since its last call and
- * clears the record; call it after synchronizing the stream(s) the work ran on. It does not synchronize. */
+ * ONMT_VALIDATE_HOST (the default): onmt_encode, onmt_decode_step and onmt_beam_search wait for a kernel that
+ * checks their device id / length inputs before enqueuing anything else, returning ONMT_EINVAL on a bad value
+ * (one stream sync per call). ONMT_VALIDATE_DEVICE: the call does not wait for that kernel; a bad value is
+ * replaced by a safe one (a length clamped to [1, S_max], an id by 0, a parent by the row itself), the
+ * computation goes on, and the model records the failure. In this mode the encoder steps over all S_max
+ * positions (the host does not learn the longest length), which gives the same results. onmt_device_status
+ * sets *code to ONMT_OK or ONMT_EINVAL (onmt_last_error then says what was wrong) for the work enqueued since
+ * its last call and clears the record; call it after synchronizing the stream(s) the work ran on. It does not
+ * synchronize. */
 enum { ONMT_VALIDATE_HOST = 0, ONMT_VALIDATE_DEVICE = 1 };
 int onmt_set_validation(onmt_model* model, int mode);
 int onmt_device_status(onmt_model* model, int* code);
@@ -202,12 +205,13 @@ int onmt_device_status(onmt_model* model, int* code);
 /* ---- Decoder step without allocation ------------------------------------------------------------------
  * For callers that cannot allocate memory or synchronize per call (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): onmt_decode_step without the step_ws argument. Its
- * scratch is a device array of ONMT_NOALLOC_SCRATCH_BYTES built into the library,
- * one per GPU, located when a model is created on that device (or at the first call on it); the call
- * itself allocates nothing and never waits. Inputs are validated on the device as with
+ * scratch is a device array built into the library, one of 3 * ONMT_NOALLOC_SCRATCH_BYTES (48 MiB) per GPU,
+ * located when a model is created on that device (or at the first call on it); the call itself allocates nothing
+ * and never waits. Inputs are validated on the device as with
  * ONMT_VALIDATE_DEVICE (check onmt_device_status). The scratch holds per-tile top-K lists (8 K bytes per row
- * and 128 vocabulary entries) where step_ws holds the step's logits; a step that needs more than
- * ONMT_NOALLOC_SCRATCH_BYTES is refused with ONMT_EUNSUPPORTED (16 MiB holds every workload of
+ * and 128 vocabulary entries) where step_ws holds the step's logits. A step is refused with ONMT_EUNSUPPORTED when
+ * its scratch passes ONMT_NOALLOC_SCRATCH_BYTES, counted with contexts of `hidden` columns (they are stored in blocks
+ * of 16 rows x 32 columns, for which the array has room) and 8 K more bytes per row (16 MiB holds every workload of
  * this library's benchmarks: 320 rows over a 50000-word vocabulary at beam 5 take 7.3 MB). All calls on
  * one GPU share its array, which keeps the last call's contents: calls that overlap on one GPU (on
  * different streams, or from different threads) race and must not be issued. Arguments, outputs and
@@ -254,7 +258,8 @@ int onmt_replace_unk(onmt_model* model, const int32_t* src, int B, int S_max, co
  * For sentence b the decoder is fed BOS, tgt[b, 0], ..., tgt[b, tgt_len[b] - 2] and scores the next target
  * token at every step: out_logp[b, t] = log p(tgt[b, t] | tgt[b, <t], src_b) for t < tgt_len[b], 0 after;
  * out_nll[b] = -sum_t out_logp[b, t] (fp64). tgt [B, T_max] and tgt_len [B] are device int32 arrays
- * (1 <= tgt_len[b] <= T_max, ids in [0, tgt_vocab) below the length), checked by a kernel the call waits for. src/len as in onmt_encode. ws holds onmt_score_ws_bytes(model, B, S_max, T_max) bytes.
+ * (1 <= tgt_len[b] <= T_max, ids in [0, tgt_vocab) below the length), checked by a kernel the call waits for.
+ * src/len as in onmt_encode. ws holds onmt_score_ws_bytes(model, B, S_max, T_max) bytes.
  * out_logp [B, T_max] fp32 and out_nll [B] fp64 are device pointers. Returns when the outputs are
  * written (the stream is synchronized). */
 size_t onmt_score_ws_bytes(const onmt_model* model, int B, int S_max, int T_max);

@@ -52,7 +52,7 @@ R10 GNMT length penalty lp(n) = ((5 + n) / 6) ** alpha, applied to finished
     hypotheses only; n counts EOS.
 R11 max_len = most generated tokens, EOS included.
 R12 bf16 workloads: the oracle runs in fp64 on the bf16-rounded weights. (The GPU path keeps bf16
-    weights and fp32 accumulation; it carries each activation entering a product as two bf16 terms,
+    weights and fp32 accumulation; it carries each activation entering a product as two fp16 terms,
     which keeps the chaotic decoder recurrence within the bf16 tolerance over full-length outputs.)
 R15 Throughput counts target tokens of the 1-best, EOS included.
 R18 Hypothesis filters (Section 4.2 names a limit on unknown words and word-level constraints on the

@@ -158,7 +158,9 @@ __device__ __forceinline__ void row_merge_wave(float (&tm)[kMaxTilesPerLane], co
     for (int j = 0; j < kSmallCols; ++j)
       if (j * kWave < gp.V) add(sc[j] > ninf && sc[j] >= theta, sc[j], lane + j * kWave);
   } else if (nq <= kQualCap && lrow) {
-    constexpr int kBatch = 8;        // K = 5 qualifies 5 or 6 tiles: one round trip (64-sentence search 4.67 -> 4.64 ms)
+    // K = 5 qualifies 5 or 6 tiles: one round trip (64-sentence search 4.67 -> 4.64 ms against batches of 4); K of 8 and
+    // more takes two or three (step of 320 rows x 50000 words at K = 16: 129 us, 233 with lists of every tile)
+    constexpr int kBatch = 8;
     for (int q0 = 0; q0 < nq && n <= kSurvivorCap; q0 += kBatch) {
       float v[kBatch][2];
       int c0[kBatch];
@@ -270,8 +272,8 @@ hipError_t lse_topk_merge(const GenPartials& gp, int M, int K, float* out_val, i
                           hipStream_t st) {
   if (gp.ntiles > kWave * kMaxTilesPerLane || K < 1 || K > kMaxBeam || (!gp.logits && !gp.pval)) return hipErrorInvalidValue;
   const dim3 grid((M + kMergeWaves - 1) / kMergeWaves), block(kMergeWaves * kWave);
-  if (gp.logits && gp.ntiles < K) hipLaunchKernelGGL(k_lse_topk<true>, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
-  else hipLaunchKernelGGL(k_lse_topk<false>, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
+  const auto kernel = gp.logits && gp.ntiles < K ? k_lse_topk<true> : k_lse_topk<false>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, gp, M, K, out_val, out_id, out_lse);
   return hipGetLastError();
 }
 
@@ -556,8 +558,8 @@ hipError_t beam_step(const BeamParams& p, const GenPartials& gp, int t, hipStrea
   if (gp.ntiles > kWave * kMaxTilesPerLane || p.K > kMaxBeam) return hipErrorInvalidValue;
   const double lp_t = std::pow((5.0 + t) / 6.0, p.alpha);     // GNMT length penalty of this step
   const dim3 grid(p.B), block(p.K * kWave);
-  if (gp.logits && gp.ntiles < p.K) hipLaunchKernelGGL(k_beam_step<true>, grid, block, 0, st, p, gp, t, lp_t);
-  else hipLaunchKernelGGL(k_beam_step<false>, grid, block, 0, st, p, gp, t, lp_t);
+  const auto kernel = gp.logits && gp.ntiles < p.K ? k_beam_step<true> : k_beam_step<false>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, p, gp, t, lp_t);
   return hipGetLastError();
 }
 

@@ -2,7 +2,7 @@
 // the log-softmax partials (per row and 128-column tile: largest logit, sum of exponentials) in the epilogue.
 //
 // Operands are two-term fp16 splits in fragment blocks (see split16.h): A the attentional vector, W the
-// weights (fp32 models: both terms; bf16 models: one, which holds them exactly). Products hi.hi go to one
+// weights (fp32 models: both terms; bf16 models: one, exact down to 2^-31 of its row's largest). Products hi.hi go to one
 // fp32 accumulator, hi.lo and lo.hi to a second that is scaled down when the two are added, so three
 // v_mfma_f32_16x16x32_f16 per fp32 product (two for bf16 weights). The dropped lo.lo product lies below 2^-22
 // of the leading one; against 64 bits the sums are closer than fp32 MFMA's, because an accumulator is rounded
@@ -66,7 +66,9 @@ __device__ inline void gen_lists(const float* Ct, int crow, const GenParams& p, 
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
       const int c = n0 + 4 * j + part;
-      if (c < p.V && ((p.banned_bits && ((p.banned_bits[c >> 5] >> (c & 31)) & 1u)) || (unk && c == p.unk_id))) z[j] = ninf;
+      if (c >= p.V) continue;
+      const bool banned = p.banned_bits && ((p.banned_bits[c >> 5] >> (c & 31)) & 1u);
+      if (banned || (unk && c == p.unk_id)) z[j] = ninf;
     }
   }
   const size_t o = ((size_t)row * p.ntiles + nt) * p.K;

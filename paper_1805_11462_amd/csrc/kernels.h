@@ -128,9 +128,10 @@ struct DecodeState {
 };
 // Rows b * K + k of the state = the encoder's final rows b; feed = 0.
 hipError_t decode_init(const DecodeState& s, const float* final_h, const float* final_c, int B, int K, hipStream_t st);
-// split: the two-term copies from h and feed, each row of a layer's product under a power of two of its own: the copies of
-// h (and of feed, with layer 0's h) are scaled by 2^(kActExp + shift[l, r]). tok != NULL: tok_out [N] = tok with invalid ids set to 0; par_out [N]
-// (parent != NULL) = parent with rows outside [0, N) replaced by the row itself; violations recorded in *err.
+// split: the two-term copies from h and feed, each row of a layer's product under a power of two of its own: the
+// copies of h (and of feed, with layer 0's h) are scaled by 2^(kActExp + shift[l, r]). tok != NULL: tok_out [N] =
+// tok with invalid ids set to 0; par_out [N] (parent != NULL) = parent with rows outside [0, N) replaced by the row
+// itself; violations recorded in *err.
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st);
 
@@ -176,7 +177,8 @@ struct AttnExtra {
   int32_t* align;               // [N]: position of the largest weight (smaller position on ties)
 };
 
-// ctx16: the contexts as a two-term operand of ceil32(Hm) columns. v_a != nullptr selects concat scores v_a . tanh(q_k + keys[s]) (q = the projected query); else q_k . keys[s].
+// ctx16: the contexts as a two-term operand of ceil32(Hm) columns. v_a != nullptr selects concat scores v_a .
+// tanh(q_k + keys[s]) (q = the projected query); else q_k . keys[s].
 hipError_t attention(const float* q, int ld_q, const float* keys, const float* v_a, const float* mem,
                      const int32_t* lens, int B, int S_max, int H, int Hm, int K, float* scores, uint16_t* ctx16,
                      float* attn, const AttnExtra& ex, hipStream_t st);

@@ -835,7 +835,7 @@ size_t score_layout(const Dims& d, int B, int S, int T, char* base, ScoreWs* w) 
 
 // Workspace operands that the GEMMs read through buffer descriptors (see kDescLimit): the encoder's
 // memory, layer outputs and keys [B * S, Hm or H], the decoder's state rows and attentional vectors
-// [B * K, Hm or H] (and their bf16 planes), and scoring's attentional vectors of all steps [T * B, H].
+// [B * K, Hm or H] (as two-term operands no wider), and scoring's attentional vectors of all steps [T * B, H].
 int check_ws_limits(const Dims& d, long long B, long long S, long long K, long long T) {
   const long long w = d.Hm > d.H ? d.Hm : d.H;
   const uint64_t enc = (uint64_t)(B * S) * (uint64_t)ceil_to((int)w, kSegK) * 4;

@@ -430,7 +430,8 @@ hipError_t thin_lstm(int w_terms, const ThinA& a, const ThinW& w, const LstmPara
 }
 
 hipError_t thin_lstm2(int w_terms, const ThinPair& q, hipStream_t st) {
-  if (!thin_ok(q.a[0], q.w[0], w_terms) || !thin_ok(q.a[1], q.w[1], w_terms) || q.p[0].in_shift || q.p[1].in_shift) return hipErrorInvalidValue;
+  for (int i = 0; i < 2; ++i)
+    if (!thin_ok(q.a[i], q.w[i], w_terms) || q.p[i].in_shift) return hipErrorInvalidValue;
   const int M[2] = {q.a[0].M, q.a[1].M}, rows[2] = {q.w[0].rows, q.w[1].rows};
   const int i = w_terms == 2 ? thin_shape(kThin2, 2, 2, M, rows) : thin_shape(kThin1, 1, 2, M, rows);
 #define ONMT_CALL(...) launch_thin_lstm2<__VA_ARGS__>(q, st)

@@ -1,9 +1,12 @@
 // Main loop of the GEMMs over many rows (the generator, the encoder's projections and keys): 16 TM x 64 TN tiles of
 // four waves that each take all 16 TM rows and 16 TN columns, operands as split fp16 terms in fragment blocks (split16.h).
 //
-// A wave's weights are its own, so they go straight into registers, D - 1 K blocks ahead, and LDS holds the rows
-// all four waves read, moved there by LDS-destination loads NSTG - 1 blocks ahead: with both operands in LDS its
-// bandwidth was the bound (reads plus stage writes 90% of 128 bytes per clock at 160 x 128 tiles).
+// A wave's weights are its own, so they go straight into registers, and LDS holds the rows all four waves read, moved
+// there by LDS-destination loads: with both operands in LDS its bandwidth was the bound (reads plus stage writes 90% of
+// 128 bytes per clock at 160 x 128 tiles). Weights have D register sets and rows NSTG buffers, but a stage's barrier
+// lets only (NSTG - 2) LPA loads of either kind stay outstanding, since one counter holds both, and the compiler may
+// place a stage's weight loads behind its products: about one stage is in flight whatever D and NSTG are. The tile
+// shapes and limits that were measured (gen_wide_tm, k_thin_lstm_wide, wide_dispatch) hold for this loop.
 #pragma once
 
 #include "common.h"
@@ -94,7 +97,7 @@ __device__ __forceinline__ void wide_main(char* smem, LoadA load_a, __amdgpu_buf
     for (int d = 0; d < D; ++d) {
       const int st = st0 + d;
       // this wave's loads complete in issue order: A(st) has landed when at most the NSTG - 2 younger stages' A
-      // loads are outstanding (weights of younger stages are in the count too, which only waits longer). The
+      // loads are outstanding (weights of younger stages are in the count too, so it waits for more than A(st)). The
       // barrier makes the whole stage visible and frees the buffer multiplied at st - 1; it is the bare
       // instruction, because __syncthreads' fences would also wait for the stages in flight.
       __builtin_amdgcn_s_waitcnt(waitcnt_stage((NSTG - 2) * C::LPA));

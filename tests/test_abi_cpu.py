@@ -125,9 +125,9 @@ def test_library_resolves_every_kernel_it_launches():
     ("fp32", "src_vocab_emb", (1 << 20, 500), (1 << 20, 512)),
     # the same table in bf16: 2^20 x 1016 fits, 2^20 x 1024 does not
     ("bf16", "src_vocab_emb", (1 << 20, 1016), (1 << 20, 1024)),
-    # W_s [tgt_vocab, pad(hidden)]: fp32 models keep it in fp32 (131072 x 3968 fits; hidden 4000 pads to
-    # 4096 columns = 2^31 bytes) besides its bf16 term planes, one descriptor each (131072 x 8064 x 2 bytes
-    # fits, hidden 8100 pads to 8192 columns = 2^31 bytes)
+    # W_s [tgt_vocab, pad(hidden)], counted with columns in whole 128s: 4 bytes each in fp32 models (131072 x 3968
+    # fits; hidden 4000 pads to 4096 columns = 2^31 bytes), 2 in bf16 ones (131072 x 8064 fits, hidden 8100 pads to
+    # 8192 columns = 2^31 bytes)
     ("fp32", "tgt_vocab_hidden", (131072, 3968), (131072, 4000)),
     ("bf16", "tgt_vocab_hidden", (131072, 8064), (131072, 8100)),
 ])

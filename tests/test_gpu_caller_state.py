@@ -186,3 +186,36 @@ def test_an_infinite_source_embedding_saturates_its_gates(wdtype):
     assert np.isfinite(want).all()
     np.testing.assert_allclose(mem, want, atol=1e-5, rtol=0)
     tr.close()
+
+
+@pytest.mark.parametrize("wdtype,hidden", [("fp32", 100), ("bf16", 104)])
+def test_steps_of_edited_states_can_be_captured(wdtype, hidden):
+    # steps captured once and replayed on states that change between the replays: copies and powers of two are made
+    # in the graph, not kept from the capture
+    s = Step(wdtype, hidden, 2, 7, 5)
+    print(f"[case] captured steps {wdtype} H{hidden}", flush=True)
+    tr = s.tr
+    _lib.check(tr.lib.onmt_set_validation(tr.handle, _lib.ONMT_VALIDATE_DEVICE))
+    first = s.state.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        s.step(), s.noalloc()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        a, n = s.step(), s.noalloc()
+    for size in (1.0, 1e6, 1e-9, 1.0):
+        s.state.copy_(first)
+        if wdtype == "fp32":
+            s.h *= size
+            s.feed *= size
+        graph.replay()
+        torch.cuda.synchronize()
+        want = s.step()
+        for got in (a, n):
+            for x, y in zip(tr.state_views(got[0], s.N), tr.state_views(want[0], s.N)):
+                assert torch.equal(x, y)
+            assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    tr.close()

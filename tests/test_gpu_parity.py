@@ -247,12 +247,12 @@ def default_peaked():
 
 
 def test_generator_products_keep_fp32_accuracy(default_peaked):
-    # The fp32 generator multiplies each fp32 weight and activation as three bf16 terms and keeps the six
-    # term products down to 2^-16 of the leading one (Section 2 generator; fp32 workloads). On the GPU's
+    # The fp32 generator multiplies each fp32 weight and activation as two scaled fp16 terms and keeps three of
+    # their products (Section 2 generator; fp32 workloads). On the GPU's
     # own attentional vector, its logits must match the fp64 generator's to fp32 rounding. Compared as
     # differences within a row (log-prob of every word minus that of word 0, so the row's log-sum-exp
     # cancels), with W_s scaled by 10 so that logits reach tens: an fp32 product errs by ~3e-6 there, the
-    # cheaper three-product form (hi.hi + hi.lo + lo.hi) by ~2.4e-5, and the bound sits between them.
+    # same three products of two bf16 terms per operand by ~2.4e-5, and the bound sits between them.
     s = default_peaked
     w = s.w
     B, S = s.src.shape

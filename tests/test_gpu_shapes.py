@@ -2,7 +2,7 @@
 sizes): hidden sizes that are not multiples of 32 (partial gate groups, padded K segments), vocabularies
 that leave a ragged last generator tile, three stacked layers, bidirectional encoders with odd
 per-direction widths, the concat attention type at such sizes, and a bf16 model whose hidden size is not
-a multiple of 8 (its activations are split on load instead of read as pre-split planes). Each shape:
+a multiple of 8 (its state's operand copies are made anew before each step). Each shape:
 three decoder steps against the oracle (full log-distribution, attention, state) and a beam search whose
 every sentence is checked by teacher-forced rescoring and the replay of its decisions. A bf16 model with
 hidden 104 at 256 hypothesis rows runs the decoder layers' LDS-destination main loop (rows gathered by
