@@ -520,13 +520,13 @@ hipError_t decode_init(const DecodeState& s, const float* final_h, const float* 
 // layer below, which is at most 1 in size, so there it is at most 2^14.
 constexpr int kMaxChunks = 2;                 // 8-column chunks per lane (H <= 1024)
 
-__global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, const int32_t* __restrict__ tok,
+// Blocks [0, id_blocks) check the ids, the others copy, so that the two chains of loads run side by side.
+__global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int id_blocks, const int32_t* __restrict__ tok,
                                                       const int32_t* __restrict__ parent, int V,
                                                       int32_t* __restrict__ tok_out, int32_t* __restrict__ par_out,
                                                       int32_t* err) {
-  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
-  if (tok) {
-    for (size_t r = i0; r < (size_t)s.N; r += step) {
+  if ((int)blockIdx.x < id_blocks) {
+    for (size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x; r < (size_t)s.N; r += (size_t)id_blocks * blockDim.x) {
       int t = tok[r];
       if (t < 0 || t >= V) {
         *err = kErrToken;
@@ -542,15 +542,15 @@ __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, 
         par_out[r] = p;
       }
     }
+    return;
   }
-  if (!split) return;
+  const int block = blockIdx.x - id_blocks, blocks = gridDim.x - id_blocks;
   const size_t nshift = (size_t)s.L * s.N;
-  for (size_t i = nshift + i0; i < (nshift + kShiftPad - 1) / kShiftPad * kShiftPad; i += step) s.shift[i] = 0;
+  if (block == 0 && threadIdx.x < (kShiftPad - nshift % kShiftPad) % kShiftPad) s.shift[nshift + threadIdx.x] = 0;
   const int lane = threadIdx.x & 63;
-  const int chunks = s.kb * 4, rows = (s.N + kFragRows - 1) / kFragRows * kFragRows;
-  for (size_t i = (size_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; i < (size_t)s.L * rows;
-       i += (size_t)gridDim.x * (blockDim.x / kWave)) {
-    const int r = (int)(i % rows), l = (int)(i / rows);
+  const unsigned chunks = s.kb * 4, rows = (s.N + kFragRows - 1) / kFragRows * kFragRows;
+  for (unsigned i = block * (256 / kWave) + threadIdx.x / kWave; i < s.L * rows; i += blocks * (256 / kWave)) {
+    const int r = i % rows, l = i / rows;            // L <= 64, N < 2^22 (state operands below 2 GiB)
     const bool on = r < s.N;
     float h[kMaxChunks][8], f[kMaxChunks][8], m = 0.f;
 #pragma unroll
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, 
 #pragma unroll
     for (int j = 0; j < kMaxChunks; ++j) {
       const int k0 = (lane + j * kWave) * 8;
-      if (k0 >= chunks * 8) continue;
+      if (k0 >= (int)chunks * 8) continue;
       store_act8(s.h16 + l * s.plane, r, k0, s.kb, h[j], e);
       if (l == 0) store_act8(s.feed16, r, k0, s.kb, f[j], e);
     }
@@ -582,13 +582,14 @@ __global__ __launch_bounds__(256) void k_prepare_step(DecodeState s, int split, 
 
 hipError_t prepare_step(const DecodeState& s, int split, const int32_t* tok, const int32_t* parent, int V,
                         int32_t* tok_out, int32_t* par_out, int32_t* err, hipStream_t st) {
-  if (!split && !tok) return hipSuccess;
   if (split && (!s.shift || s.kb * 4 > kMaxChunks * kWave)) return hipErrorInvalidValue;
-  const size_t n = split ? (size_t)s.L * ((s.N + kFragRows - 1) / kFragRows * kFragRows) * kWave : (size_t)s.N;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_prepare_step, dim3((unsigned)blocks), dim3(256), 0, st, s, split, tok, parent, V, tok_out,
-                     par_out, err);
+  auto blocks = [](size_t threads) { return (int)((threads + 255) / 256 < 4096 ? (threads + 255) / 256 : 4096); };
+  const int id_blocks = tok ? blocks(s.N) : 0;
+  const size_t rows = (size_t)(s.N + kFragRows - 1) / kFragRows * kFragRows;
+  const int copy_blocks = split ? blocks((size_t)s.L * rows * kWave) : 0;
+  if (id_blocks + copy_blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_prepare_step, dim3(id_blocks + copy_blocks), dim3(256), 0, st, s, id_blocks, tok, parent, V,
+                     tok_out, par_out, err);
   return hipGetLastError();
 }
 
